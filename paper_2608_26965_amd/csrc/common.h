@@ -140,8 +140,8 @@ inline bool col_copy_used(const Prob& P) {
   return P.dtype == CA_BF16 && (P.d == 64 || P.d == 128) && P.xf != CA_XF_NONE &&
          P.xf != CA_XF_RANDOM && P.split == CA_SPLIT_DIAG;
 }
-constexpr int kMats = 8;
-constexpr int kVecs = 8;
+constexpr int kMats = 7;
+constexpr int kVecs = 3;
 constexpr int kNodeInts = 16;
 constexpr int kBins = 4096;       // linear bins of the multi-block split select
 constexpr int kChunk = 4096;      // tokens per block in the multi-block split passes

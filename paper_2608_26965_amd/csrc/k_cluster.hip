@@ -70,11 +70,11 @@ struct Ctx {
 };
 
 // Matrix slots
-enum { M_A0 = 0, M_CK = 1, M_E0 = 2, M_EK = 3, M_C2 = 4, M_C3 = 5, M_TK = 6, M_TQ = 7 };
+enum { M_A0 = 0, M_CK = 1, M_E0 = 2, M_EK = 3, M_C3 = 4, M_TK = 5, M_TQ = 6 };
 // Operand slots (MFMA A operands W^T, split in bf16 hi + lo)
 enum { O_FK = 0, O_TK = 1, O_TQ = 2 };
 // Vector slots
-enum { V_L0 = 0, V_LK = 1, V_MUQ = 2, V_MUK = 3, V_L2 = 4, V_L3 = 5, V_MUR = 6, V_KQ = 7 };
+enum { V_MUQ = 0, V_MUK = 1, V_MUR = 2 };
 
 __device__ __forceinline__ float* mat(const Ctx& C, int bh, int slot) {
   return C.mats + ((size_t)bh * kMats + slot) * C.d * C.d;
@@ -224,9 +224,7 @@ __global__ __launch_bounds__(256) void moments_finish_kernel(Ctx C) {
 struct EighJob {
   int b, s, m;     // matrix B, factor S (-1: none), vector m (-1: none)
   int rank1;       // subtract u u^T
-  int u_out;       // vector slot for u (-1: none)
   int orient;      // orientation vector slot, used when u is not formed
-  int vecs, vals;  // oriented eigenvectors (columns, descending) and eigenvalues
   int t_f;         // factor F of the projection T = F U (-1: T = U)
   int t_out, wop_out;
 };
@@ -330,13 +328,19 @@ __device__ __forceinline__ double recip64(double x) {
 __device__ __forceinline__ int sturm_below(const double2* tq, int s, int t, double x) {
   // A minor that is exactly zero counts as positive: the next one then has
   // the opposite sign of the one before, so the pair adds exactly one change.
+  // The next eight entries are read while the current eight are used; the
+  // last, partial eight run on past the block (tq holds eight more finite
+  // entries) with their changes not counted.
   double p2 = 1.0, p1 = tq[s].x - x;
   int cnt = p1 < 0.0;
+  double2 q[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) q[u] = tq[s + 1 + u];
   int i0 = s + 1;
   for (; i0 + 8 <= t; i0 += 8) {
-    double2 q[8];
+    double2 nq[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) q[u] = tq[i0 + u];
+    for (int u = 0; u < 8; ++u) nq[u] = tq[i0 + 8 + u];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const double p = (q[u].x - x) * p1 - q[u].y * p2;
@@ -348,15 +352,34 @@ __device__ __forceinline__ int sturm_below(const double2* tq, int s, int t, doub
     (void)frexp(fmax(fabs(p1), fabs(p2)), &ex);
     p1 = ldexp(p1, -ex);
     p2 = ldexp(p2, -ex);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) q[u] = nq[u];
   }
-  for (; i0 < t; ++i0) {
-    const double2 q = tq[i0];
-    const double p = (q.x - x) * p1 - q.y * p2;
-    cnt += (p < 0.0) != (p1 < 0.0);
+#pragma unroll
+  for (int u = 0; u < 7; ++u) {
+    const double p = (q[u].x - x) * p1 - q[u].y * p2;
+    cnt += ((p < 0.0) != (p1 < 0.0)) & (i0 + u < t);
     p2 = p1;
     p1 = p;
   }
   return cnt;
+}
+
+// Separately rounded fp32 operations: a product is never fused into the sum
+// that follows it, and the quotient and square root are the correctly rounded
+// ones (the default contraction would otherwise turn a + x * y into an FMA,
+// and the HIP __f*_rn intrinsics are plain operators here).
+__device__ __forceinline__ float add_rn(float a, float b) {
+#pragma clang fp contract(off)
+  return a + b;
+}
+__device__ __forceinline__ float sub_rn(float a, float b) {
+#pragma clang fp contract(off)
+  return a - b;
+}
+__device__ __forceinline__ float mul_rn(float a, float b) {
+#pragma clang fp contract(off)
+  return a * b;
 }
 
 // Pseudo-random start of inverse iteration: +-[0.5, 1.5)
@@ -431,6 +454,22 @@ __device__ __forceinline__ void lds_mm_store(const MMAcc& acc, float* Z, int ld,
   }
 }
 
+// Rows wv, wv + NW, ... (RI of them) of a d x d matrix, CPL columns a lane,
+// zero outside it.
+template <int RI, int CPL, int NW>
+__device__ __forceinline__ void load_square(const float* __restrict__ g, int d, int wv, int lane,
+                                            float (&r)[RI * CPL]) {
+#pragma unroll
+  for (int ii = 0; ii < RI; ++ii)
+#pragma unroll
+    for (int cc = 0; cc < CPL; ++cc) {
+      const int i = wv + NW * ii, j = lane + 64 * cc;
+      const bool in = i < d && j < d;
+      const float x = g[in ? i * d + j : 0];
+      r[ii * CPL + cc] = in ? x : 0.f;
+    }
+}
+
 template <int DM>
 __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJobs J) {
   constexpr int NT = eigh_threads<DM>();
@@ -440,6 +479,7 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
   constexpr int CPL = DM / 64;           // rows (or columns) per lane in a wavefront sweep
   constexpr int NQ = DM / (4 * kEighM);  // float4 column groups per thread in a row pass
   constexpr int RW = DM / kEighM;        // rows per thread in the back-transformation
+  constexpr int RI = DM / NW;            // matrix rows per wavefront in a load or store
   static_assert(CPL >= 1 && NQ >= 1 && RW % 4 == 0, "matrix size");
   extern __shared__ __attribute__((aligned(16))) float esh[];
   float* A = esh;             // [DM][EP]; row k keeps reflector k once reduced
@@ -447,14 +487,16 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
   __shared__ __attribute__((aligned(16))) float vvs[2][NW][DM];  // reflectors, one copy per wave
   __shared__ __attribute__((aligned(16))) float pbuf[2][DM];     // p = A v of the last two steps
   __shared__ float kpart[2][NW];
+  __shared__ __attribute__((aligned(16))) float4 colb[2][DM];  // the next step's column (in its group of 4)
+  __shared__ float last2[2][2];
   __shared__ float trid[2][DM];  // diagonal, off-diagonal of T
-  __shared__ double2 tq[DM];     // scaled (diagonal i, squared off-diagonal i - 1)
+  __shared__ double2 tq[DM + 9]; // scaled (diagonal i, squared off-diagonal i - 1), zeros past d
   __shared__ double es[DM], lam64[DM];
   __shared__ int bs[DM], be[DM], inv[DM];
   __shared__ double sh_tn;
   __shared__ uint64_t sh_link[CPL];
-  __shared__ float uvec[DM], ovec[DM], mvec[DM], lam[DM], sgn[DM];
-  __shared__ int rnk[DM];
+  __shared__ __attribute__((aligned(16))) float ovec[DM];
+  __shared__ float uvec[DM], mvec[DM], lam[DM], sgn[DM];
   const int bh = blockIdx.x, d = C.d, tid = threadIdx.x;
   const EighJob& jb = J.j[blockIdx.y];
   const int lane = tid & 63;
@@ -463,18 +505,23 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
   {
     const float* Bg = mat(C, bh, jb.b);
     const float* Sg = jb.s >= 0 ? mat(C, bh, jb.s) : nullptr;
-    for (int i = wv; i < DM; i += NW)
-#pragma unroll
-      for (int cc = 0; cc < CPL; ++cc) {
-        const int j = lane + 64 * cc;
-        const bool in = i < d && j < d;
-        A[i * EP + j] = in ? Bg[i * d + j] : 0.f;
-        Vt[i * EP + j] = Sg ? (in ? Sg[i * d + j] : 0.f) : 0.f;  // S while it is needed
-      }
+    // every load is issued before the first is used
+    float lb[RI * CPL], ls[RI * CPL];
+    load_square<RI, CPL, NW>(Bg, d, wv, lane, lb);
+    if (Sg) load_square<RI, CPL, NW>(Sg, d, wv, lane, ls);
     if (tid < DM) {
       ovec[tid] = 0.f;
       mvec[tid] = jb.m >= 0 && tid < d ? vec(C, bh, jb.m)[tid] : 0.f;
     }
+    if (tid < 9) tq[DM + tid] = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int ii = 0; ii < RI; ++ii)
+#pragma unroll
+      for (int cc = 0; cc < CPL; ++cc) {
+        const int at = (wv + NW * ii) * EP + lane + 64 * cc;
+        A[at] = lb[ii * CPL + cc];
+        Vt[at] = Sg ? ls[ii * CPL + cc] : 0.f;  // S while it is needed
+      }
     __syncthreads();
     if (jb.m >= 0) {
       // u = S^T m (or m)
@@ -482,6 +529,7 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
         float u;
         if (Sg) {
           float u4[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
           for (int t = 0; t < d; t += 4)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
@@ -515,54 +563,98 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
           const int j = lane + 64 * cc;
           if (j < d) A[i * EP + j] -= uvec[i] * uvec[j];
         }
-    if (jb.u_out >= 0 && tid < d) vec(C, bh, jb.u_out)[tid] = uvec[tid];
     __syncthreads();
   }
   // ---- 1. Householder reduction. Step k: reflector H_k = I - v v^T (|v|^2 = 2,
   // support k+1..d-1) from column k after the update by H_{k-1}; the row pass
   // applies H_{k-1} to the block [k+1, d)^2 and accumulates p = A v; with
   // w = p - (v^T p / 2) v, H A H = A - v w^T - w v^T.
+  //
+  // The matrix is held in registers: the 16 lanes of a DPP row share 4 rows
+  // (rs, rs + DM/4, rs + DM/2, rs + 3 DM/4; rs = 4 * wave + lane / 16, so the
+  // live rows of a step are spread over all wavefronts) and split their float4
+  // column groups (c16, c16 + 16, ...). LDS passes only the vectors (v, p, the
+  // next column), so a step is one chain: column -> norm (fp64) -> v -> p.
+  // Entries of v and p outside the live block are zero, so the pass needs no
+  // masks: dead entries are updated by zeros.
+  // What bounds it: that chain's latency with one wavefront a SIMD (about 2,000
+  // cycles a step). With the matrix in LDS, masks
+  // per entry and two more waits a step it was about 2,400: the whole kernel
+  // took 152 us for 16 problems at d = 64 and 423 us for 80 at d = 128, now 133
+  // and 387 us (with the second inverse-iteration step reusing the first one's
+  // factorisation, and every global read issued ahead of its use).
   const int nref = d > 2 ? d - 2 : 0;
   {
-    // Row pass layout: the 16 lanes of a DPP row share 4 rows (rs, rs + DM/4,
-    // rs + DM/2, rs + 3 DM/4; rs = 4 * wave + lane / 16, so the live rows of
-    // a step are spread over all wavefronts) and split their float4 column
-    // groups (c16, c16 + 16, ...): the vectors are read once per group and
-    // used for 4 rows, and the 16 lanes read an A row contiguously.
     constexpr int RPT = 4;               // rows per lane
     constexpr int NG = DM / 64;          // column groups per lane
     const int c16 = lane & 15, rs = 4 * wv + (lane >> 4);
+    float ar[NG][RPT][4];
+#pragma unroll
+    for (int q = 0; q < NG; ++q)
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) {
+        const float4 a = *reinterpret_cast<const float4*>(
+            &A[(rs + r * (DM / RPT)) * EP + 4 * (c16 + 16 * q)]);
+        ar[q][r][0] = a.x; ar[q][r][1] = a.y; ar[q][r][2] = a.z; ar[q][r][3] = a.w;
+      }
+    // before the first step: no reflector yet, and column 0 as it is
+    if (tid < DM) {
+      colb[1][tid] = *reinterpret_cast<const float4*>(&A[tid * EP]);
+      pbuf[1][tid] = 0.f;
+    }
+#pragma unroll
+    for (int h = 0; h < CPL; ++h) vvs[1][wv][lane + 64 * h] = 0.f;
+    if (tid < NW) kpart[1][tid] = 0.f;
+    __syncthreads();  // A is read: its rows take the reflectors from here
+    float vr[RPT] = {0.f, 0.f, 0.f, 0.f}, pr[RPT] = {0.f, 0.f, 0.f, 0.f};  // v and p at own rows
     for (int k = 0; k < nref; ++k) {
+#pragma clang fp contract(off)
       const int cur = k & 1, prv = cur ^ 1;
       float* vcur = vvs[cur][wv];
       const float* vprv = vvs[prv][wv];
       const float* pprv = pbuf[prv];
-      float Kp = 0.f, vk = 0.f, wk = 0.f;
-      if (k > 0) {
+      float Kp = 0.f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) Kp += kpart[prv][w];
-        Kp *= 0.5f;
-        vk = vprv[k];
-        wk = pprv[k] - Kp * vk;
-      }
+      for (int w = 0; w < NW; ++w) Kp += kpart[prv][w];
+      Kp *= 0.5f;
+      const float* colk = reinterpret_cast<const float*>(colb[prv]) + (k & 3);  // column k
+      const float vk = vprv[k], akk = colk[4 * k];
+      const float wk = __builtin_fmaf(-Kp, vk, pprv[k]);
       // column k below the diagonal (every wavefront, one or two rows a lane)
       float x[CPL];
       double s2 = 0.0;
 #pragma unroll
       for (int h = 0; h < CPL; ++h) {
         const int i = lane + 64 * h;
-        float xi = 0.f;
-        if (i > k && i < d) {
-          xi = A[i * EP + k];
-          if (k > 0) {
-            const float vi = vprv[i], wi = pprv[i] - Kp * vi;
-            xi -= vi * wk + wi * vk;
-          }
-        }
-        x[h] = xi;
-        s2 += (double)xi * (double)xi;
+        const float vi = vprv[i], wi = __builtin_fmaf(-Kp, vi, pprv[i]);
+        const float xi = colk[4 * i] - __builtin_fmaf(wk, vi, vk * wi);
+        x[h] = i > k && i < d ? xi : 0.f;
+        s2 = fma((double)x[h], (double)x[h], s2);  // the product is exact
       }
       s2 = wave_sum(s2);
+      // the block after H_{k-1}, and its column k + 1 for the next step
+      const int kn = k + 1;
+#pragma unroll
+      for (int q = 0; q < NG; ++q) {
+        const int j0 = 4 * (c16 + 16 * q);
+        const float4 vp = *reinterpret_cast<const float4*>(&vprv[j0]);
+        const float4 pp = *reinterpret_cast<const float4*>(&pprv[j0]);
+        const float vpv[4] = {vp.x, vp.y, vp.z, vp.w};
+        const float wpv[4] = {__builtin_fmaf(-Kp, vp.x, pp.x), __builtin_fmaf(-Kp, vp.y, pp.y),
+                              __builtin_fmaf(-Kp, vp.z, pp.z), __builtin_fmaf(-Kp, vp.w, pp.w)};
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) {
+          const float wr = __builtin_fmaf(-Kp, vr[r], pr[r]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            ar[q][r][e] = ar[q][r][e] - __builtin_fmaf(vr[r], wpv[e], wr * vpv[e]);
+        }
+        if ((kn >> 2) == c16 + 16 * q)
+#pragma unroll
+          for (int r = 0; r < RPT; ++r)
+            colb[cur][rs + r * (DM / RPT)] =
+                make_float4(ar[q][r][0], ar[q][r][1], ar[q][r][2], ar[q][r][3]);
+      }
       const int i0 = k + 1;
       float x0 = x[0];
 #pragma unroll
@@ -580,84 +672,75 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
 #pragma unroll
       for (int h = 0; h < CPL; ++h) {
         const int i = lane + 64 * h;
-        float v = 0.f;
-        if (i > k && i < d) v = (float)(((double)x[h] - (i == i0 ? alpha : 0.0)) * scl);
-        vcur[i] = v;
-        if (wv == 0 && i > k && i < d) A[k * EP + i] = v;
+        const float vi = (float)(((double)x[h] - (i == i0 ? alpha : 0.0)) * scl);
+        x[h] = i > k && i < d ? vi : 0.f;
+        vcur[i] = x[h];
       }
-      if (wv == 0 && lane == 0) {
-        trid[0][k] = A[k * EP + k] - (k > 0 ? 2.f * vk * wk : 0.f);
-        trid[1][k] = (float)alpha;
-      }
-      wave_lds_order();
-      // row pass over [k+1, d)^2
-      float vr[RPT], wr[RPT], vc[RPT], acc[RPT];
-      bool rl[RPT];
+      // one wavefront's LDS operations run in order: its reads of v need no wait
+      asm volatile("" ::: "memory");
+      // p = A v over the rows
+      float acc[RPT];
 #pragma unroll
       for (int r = 0; r < RPT; ++r) {
-        const int row = rs + r * (DM / RPT);
-        rl[r] = row > k && row < d;
-        vc[r] = vcur[row];
-        vr[r] = k > 0 ? vprv[row] : 0.f;
-        wr[r] = k > 0 ? pprv[row] - Kp * vr[r] : 0.f;
+        vr[r] = vcur[rs + r * (DM / RPT)];
         acc[r] = 0.f;
       }
 #pragma unroll
       for (int q = 0; q < NG; ++q) {
-        const int j0 = 4 * (c16 + 16 * q);
-        if (j0 + 3 <= k) continue;  // every column of the group is dead
-        const float4 vn = *reinterpret_cast<const float4*>(&vcur[j0]);
+        const float4 vn = *reinterpret_cast<const float4*>(&vcur[4 * (c16 + 16 * q)]);
         const float vnv[4] = {vn.x, vn.y, vn.z, vn.w};
-        float wpv[4] = {0.f, 0.f, 0.f, 0.f}, vpv[4] = {0.f, 0.f, 0.f, 0.f};
-        if (k > 0) {
-          const float4 vp = *reinterpret_cast<const float4*>(&vprv[j0]);
-          const float4 pp = *reinterpret_cast<const float4*>(&pprv[j0]);
-          vpv[0] = vp.x; vpv[1] = vp.y; vpv[2] = vp.z; vpv[3] = vp.w;
-          wpv[0] = pp.x - Kp * vp.x; wpv[1] = pp.y - Kp * vp.y;
-          wpv[2] = pp.z - Kp * vp.z; wpv[3] = pp.w - Kp * vp.w;
-        }
-        bool ok[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) ok[e] = j0 + e > k && j0 + e < d;
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int r = 0; r < RPT; ++r) {
-          if (!rl[r]) continue;
-          const int row = rs + r * (DM / RPT);
-          const float4 a = *reinterpret_cast<const float4*>(&A[row * EP + j0]);
-          float av[4] = {a.x, a.y, a.z, a.w};
-          if (k > 0) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float upd = av[e] - (vr[r] * wpv[e] + wr[r] * vpv[e]);
-              av[e] = ok[e] ? upd : av[e];
-            }
-            *reinterpret_cast<float4*>(&A[row * EP + j0]) = make_float4(av[0], av[1], av[2], av[3]);
-          }
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[r] += ok[e] ? av[e] * vnv[e] : 0.f;
-        }
+          for (int r = 0; r < RPT; ++r) acc[r] = acc[r] + ar[q][r][e] * vnv[e];
       }
-      // row sums over the 16 lanes of the DPP row
+      // row sums over the 16 lanes of the DPP row (every lane gets them)
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) acc[r] = quad_sum(acc[r]);
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) acc[r] = dpp_add<0x141>(acc[r]);  // row_half_mirror
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) acc[r] = dpp_add<0x140>(acc[r]);  // row_mirror
       float vp_part = 0.f;
 #pragma unroll
       for (int r = 0; r < RPT; ++r) {
-        float t = quad_sum(acc[r]);
-        t = dpp_add<0x141>(t);  // row_half_mirror
-        t = dpp_add<0x140>(t);  // row_mirror
         const int row = rs + r * (DM / RPT);
-        if (c16 == 0) {
-          pbuf[cur][row] = rl[r] ? t : 0.f;
-          vp_part += rl[r] ? vc[r] * t : 0.f;
+        pr[r] = row > k && row < d ? acc[r] : 0.f;
+        vp_part = vp_part + vr[r] * pr[r];
+      }
+      if (c16 == 0)
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) pbuf[cur][rs + r * (DM / RPT)] = pr[r];
+      vp_part = dpp_add<0x142, 0xA>(vp_part);  // row_bcast15 into rows 1, 3
+      vp_part = dpp_add<0x143, 0xC>(vp_part);  // row_bcast31 into rows 2, 3: lane 63 holds the sum
+      if (lane == 63) kpart[cur][wv] = vp_part;
+      if (wv == 0) {  // the reflector and T's entries, kept for the later stages
+#pragma unroll
+        for (int h = 0; h < CPL; ++h) A[k * EP + lane + 64 * h] = x[h];
+        if (lane == 0) {
+          trid[0][k] = __builtin_fmaf(-wk, vk + vk, akk);
+          trid[1][k] = (float)alpha;
         }
       }
-      vp_part = wave_sum(vp_part);
-      if (lane == 0) kpart[cur][wv] = vp_part;
       __syncthreads();
     }
     // the last 2 x 2 block after the last reflector
+    if (d >= 2) {
+#pragma unroll
+      for (int q = 0; q < NG; ++q)
+#pragma unroll
+        for (int r = 0; r < RPT; ++r)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int row = rs + r * (DM / RPT), j = 4 * (c16 + 16 * q) + e;
+            if (row >= d - 2 && row < d && j >= d - 2 && j < d)
+              last2[row - (d - 2)][j - (d - 2)] = ar[q][r][e];
+          }
+    }
+    __syncthreads();
     if (tid == 0) {
       if (d == 1) {
-        trid[0][0] = A[0];
+        trid[0][0] = ar[0][0][0];
       } else if (d >= 2) {
         const int i = d - 2, j = d - 1;
         float vi = 0.f, wi = 0.f, vj = 0.f, wj = 0.f;
@@ -671,16 +754,10 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
           wi = pbuf[l][i] - Kp * vi;
           wj = pbuf[l][j] - Kp * vj;
         }
-        trid[0][i] = A[i * EP + i] - 2.f * vi * wi;
-        trid[0][j] = A[j * EP + j] - 2.f * vj * wj;
-        trid[1][i] = A[j * EP + i] - (vj * wi + wj * vi);
+        trid[0][i] = last2[0][0] - 2.f * vi * wi;
+        trid[0][j] = last2[1][1] - 2.f * vj * wj;
+        trid[1][i] = last2[1][0] - (vj * wi + wj * vi);
       }
-    }
-    __syncthreads();
-    // row k < nref holds reflector k in columns k+1..d-1; clear the rest
-    for (int idx = tid; idx < DM * DM; idx += NT) {
-      const int k = idx / DM, j = idx % DM;
-      if (k < nref && j <= k) A[k * EP + j] = 0.f;
     }
     __syncthreads();
   }
@@ -786,10 +863,12 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
     float* z = Vt + (size_t)(live ? g : 0) * EP + SEG * part;
     const double2* tqs = tq + SEG * part;
     const double* ess = es + SEG * part;
+    double r[SEG];     // 1 / pivot of this lane's entries, kept for the second step
+    double lin = 0.0;  // the L entry that leads into this lane's segment
     for (int it = 0; it < 2; ++it) {
-      double r[SEG];  // 1 / pivot of this lane's entries
-      // forward: T - sigma I = L D L^T, y = L^{-1} b (kept in z, scaled);
-      // the quad's lanes take their segments in turn, passing (l, y) on
+      // forward: T - sigma I = L D L^T (first step only), y = L^{-1} b (kept
+      // in z, scaled); the quad's lanes take their segments in turn, passing
+      // (l, y) on
       double lprev = 0.0, yprev = 0.0;
 #pragma unroll
       for (int h = 0; h < kEighM; ++h) {
@@ -799,18 +878,31 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
           yprev = __shfl(yprev, src, 64);
         }
         if (live && part == h) {
+          if (it == 0) {
+            lin = lprev;
 #pragma unroll
-          for (int u = 0; u < SEG; ++u) {
-            if ((u & 7) == 0) asm volatile("" ::: "memory");
-            const double a = tqs[u].x - sigma;
-            const double em = u > 0 ? ess[u - 1] : (h > 0 ? es[SEG * h - 1] : 0.0);
-            double dl = fma(-lprev, em, a);
-            const double y = fma(-lprev, yprev, (double)z[u]);
-            dl = fabs(dl) < kPivMin ? (dl < 0.0 ? -kPivMin : kPivMin) : dl;
-            r[u] = recip64(dl);
-            lprev = ess[u] * r[u];
-            yprev = y;
-            z[u] = (float)(y * kStore);
+            for (int u = 0; u < SEG; ++u) {
+              if ((u & 7) == 0) asm volatile("" ::: "memory");
+              const double a = tqs[u].x - sigma;
+              const double em = u > 0 ? ess[u - 1] : (h > 0 ? es[SEG * h - 1] : 0.0);
+              double dl = fma(-lprev, em, a);
+              const double y = fma(-lprev, yprev, (double)z[u]);
+              dl = fabs(dl) < kPivMin ? (dl < 0.0 ? -kPivMin : kPivMin) : dl;
+              r[u] = recip64(dl);
+              lprev = ess[u] * r[u];
+              yprev = y;
+              z[u] = (float)(y * kStore);
+            }
+          } else {
+            lprev = lin;
+#pragma unroll
+            for (int u = 0; u < SEG; ++u) {
+              if ((u & 7) == 0) asm volatile("" ::: "memory");
+              const double y = fma(-lprev, yprev, (double)z[u]);
+              lprev = ess[u] * r[u];
+              yprev = y;
+              z[u] = (float)(y * kStore);
+            }
           }
         }
       }
@@ -882,6 +974,9 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
     }
   }
   // ---- 4. back-transformation: vector g (rows split over kEighM threads)
+  const bool fv = jb.t_f >= 0;
+  float lf[RI * CPL];  // F of the epilogue, read meanwhile
+  if (fv) load_square<RI, CPL, NW>(mat(C, bh, jb.t_f), d, wv, lane, lf);
   {
     const int g = tid / kEighM, c = tid % kEighM;
     float zr[RW];
@@ -893,17 +988,24 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
       zr[u + 2] = v4.z;
       zr[u + 3] = v4.w;
     }
+    float nv[RW];  // the next reflector, read one step ahead
+    auto fetch = [&](int k) {
+#pragma unroll
+      for (int u = 0; u < RW; u += 4) {
+        const float4 v4 = *reinterpret_cast<const float4*>(&A[k * EP + c * RW + u]);
+        nv[u] = v4.x;
+        nv[u + 1] = v4.y;
+        nv[u + 2] = v4.z;
+        nv[u + 3] = v4.w;
+      }
+    };
+    if (nref > 0) fetch(nref - 1);
     for (int k = nref - 1; k >= 0; --k) {
       float vr[RW];
       float dp[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int u = 0; u < RW; u += 4) {
-        const float4 v4 = *reinterpret_cast<const float4*>(&A[k * EP + c * RW + u]);
-        vr[u] = v4.x;
-        vr[u + 1] = v4.y;
-        vr[u + 2] = v4.z;
-        vr[u + 3] = v4.w;
-      }
+      for (int u = 0; u < RW; ++u) vr[u] = nv[u];
+      fetch(k > 0 ? k - 1 : 0);
 #pragma unroll
       for (int u = 0; u < RW; ++u) dp[u & 3] = __builtin_fmaf(vr[u], zr[u], dp[u & 3]);
       const float dot = quad_sum((dp[0] + dp[1]) + (dp[2] + dp[3]));
@@ -922,9 +1024,15 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
   if (tid < d) {
     lam[tid] = (float)(lam64[tid] * tn);
     float o4[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int t = 0; t < d; t += 4)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) o4[e] = __builtin_fmaf(ovec[t + e], Vc[tid * EP + t + e], o4[e]);
+#pragma unroll 4
+    for (int t = 0; t < d; t += 4) {
+      const float4 ov = *reinterpret_cast<const float4*>(&ovec[t]);
+      const float4 vv = *reinterpret_cast<const float4*>(&Vc[tid * EP + t]);
+      o4[0] = __builtin_fmaf(ov.x, vv.x, o4[0]);
+      o4[1] = __builtin_fmaf(ov.y, vv.y, o4[1]);
+      o4[2] = __builtin_fmaf(ov.z, vv.z, o4[2]);
+      o4[3] = __builtin_fmaf(ov.w, vv.w, o4[3]);
+    }
     const float o = (o4[0] + o4[1]) + (o4[2] + o4[3]);
     sgn[tid] = o < 0.f ? -1.f : 1.f;
   }
@@ -932,42 +1040,27 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
   if (tid < d) {
     const float li = lam[tid];
     int r = 0;
+#pragma unroll 8
     for (int j = 0; j < d; ++j) {
       const float lj = lam[j];
       r += (lj > li) || (lj == li && j < tid);
     }
-    rnk[tid] = r;
     inv[r] = tid;
-    vec(C, bh, jb.vals)[r] = li;
   }
   __syncthreads();
-  float* U = mat(C, bh, jb.vecs);
   float* T = mat(C, bh, jb.t_out);
   bf16* W = jb.wop_out >= 0 ? wop(C, bh, jb.wop_out) : nullptr;
-  // Eigenvector g becomes column rnk[g]: U[r][c] = sgn[g] Vc[g][r], g = inv[c]
-  // (lanes over c: coalesced rows of U)
-  for (int r = wv; r < d; r += NW)
-#pragma unroll
-    for (int cc = 0; cc < CPL; ++cc) {
-      const int c = lane + 64 * cc;
-      if (c < d) {
-        const int g = inv[c];
-        U[r * d + c] = sgn[g] * Vc[g * EP + r];
-      }
-    }
+  // Eigenvector g becomes column rnk[g] of U: U[r][c] = sgn[g] Vc[g][r], g = inv[c].
   // The projection T[r][c] = sgn[g] P[r][g] with P = F V (t_f) or V, and its
   // bf16 operand pair W[c][r] (hi) and W[d * d + c * d + r] (lo).
   const float* P = Vc;  // P[r][g] at Vc[g * EP + r] (V), or at Ac[r * EP + g] (F V)
-  const bool fv = jb.t_f >= 0;
   if (fv) {
     // P = F V: F goes into the A region
-    const float* Sg = mat(C, bh, jb.t_f);
-    for (int i = wv; i < DM; i += NW)
 #pragma unroll
-      for (int cc = 0; cc < CPL; ++cc) {
-        const int j = lane + 64 * cc;
-        Ac[i * EP + j] = i < d && j < d ? Sg[i * d + j] : 0.f;
-      }
+    for (int ii = 0; ii < RI; ++ii)
+#pragma unroll
+      for (int cc = 0; cc < CPL; ++cc)
+        Ac[(wv + NW * ii) * EP + lane + 64 * cc] = lf[ii * CPL + cc];
     __syncthreads();
     MMAcc acc;
     lds_mm<NT>(Ac, false, Vc, true, EP, d, acc);
@@ -976,6 +1069,7 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
     __syncthreads();
     P = Ac;
   }
+#pragma unroll 4
   for (int r = wv; r < d; r += NW)
 #pragma unroll
     for (int cc = 0; cc < CPL; ++cc) {
@@ -986,6 +1080,7 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
       }
     }
   if (W)
+#pragma unroll 4
     for (int c = wv; c < d; c += NW) {
       const int g = inv[c];
 #pragma unroll
@@ -1010,65 +1105,127 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
 // the eigenvalues at zero up to rounding).
 // ---------------------------------------------------------------------------
 
-constexpr int kCholThreads = 256;
-constexpr int kCP = kMaxD + 1;
+// What bounds it: the chain of d elimination steps, one workgroup per matrix.
+// The matrix lives in registers, 4 x 4 entries a thread spread cyclically over
+// a DM/4 x DM/4 thread grid, so a step only passes the next column and the
+// reciprocal of its pivot through LDS: one round trip and one barrier. With
+// the matrix in LDS (read, updated and written there at every step, and the
+// pivot divided in every thread) the 16 problems of an 8-head layer at d = 64
+// took 47.6 us and the 80 problems of a 40-head layer at d = 128 193.8 us; now
+// 21.3 and 54.9 us. The operations on each entry and their order
+// are the same, so the factors are the same bits.
+template <int DM>
+constexpr int chol_threads() {
+  return (DM / 4) * (DM / 4);
+}
 
-__global__ __launch_bounds__(kCholThreads) void cholesky_kernel(Ctx C, int in0, int out0, int in1,
-                                                                 int out1, int pack1) {
-  extern __shared__ __attribute__((aligned(16))) double csh[];  // [d][kCP]
+template <int DM>
+__global__ __launch_bounds__(chol_threads<DM>()) void cholesky_kernel(Ctx C, int in0, int out0,
+                                                                      int in1, int out1,
+                                                                      int pack1) {
+  constexpr int G = DM / 4, FP = DM + 1;
+  __shared__ double col[2][DM];  // the step's column (unscaled), by parity
+  __shared__ double rcp[2];      // 1 / its pivot, 0 for a pivot at or below tol
+  __shared__ double piv[DM], ipiv[DM];
   __shared__ double sh_tol;
+  extern __shared__ __attribute__((aligned(16))) float chf[];  // [DM][FP] the factor (pack only)
   const int bh = blockIdx.x, job = blockIdx.y, d = C.d, tid = threadIdx.x;
-  const int tr = tid >> 4, tc = tid & 15;  // 16 x 16 thread grid
+  const int tr = tid / G, tc = tid % G;
   const float* M = mat(C, bh, job == 0 ? in0 : in1);
   float* F = mat(C, bh, job == 0 ? out0 : out1);
   const int pack = job == 1 ? pack1 : -1;
-  double* A = csh;
-  for (int i = tr; i < d; i += 16)
-    for (int k = tc; k < d; k += 16) A[i * kCP + k] = (double)M[i * d + k];
-  __syncthreads();
+  double A[4][4];  // entry (tr + G a, tc + G b)
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int i = tr + G * a, k = tc + G * b;
+      A[a][b] = i < d && k < d ? (double)M[i * d + k] : 0.0;
+    }
   if (tid < 64) {
     double mx = 0.0;
-    for (int i = tid; i < d; i += 64) mx = fmax(mx, A[i * kCP + i]);
+#pragma unroll
+    for (int i = tid; i < DM; i += 64) mx = fmax(mx, i < d ? (double)M[i * d + i] : 0.0);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
     if (tid == 0) sh_tol = mx * 1e-12;
   }
   __syncthreads();
   const double tol = sh_tol;
+  if (tc == 0) {
+#pragma unroll
+    for (int a = 0; a < 4; ++a) col[0][tr + G * a] = A[a][0];
+    if (tr == 0) rcp[0] = A[0][0] > tol ? 1.0 / A[0][0] : 0.0;
+  }
+  __syncthreads();
   // Elimination on unscaled columns (the order of an L D L^T factorisation):
   // step j subtracts a_ij a_kj / a_jj from the trailing lower triangle (rows
-  // i > j, columns j < k <= i) and leaves column j as it is, so a step reads
-  // only column j and needs one barrier. A pivot at or below tol contributes
-  // nothing and gives a zero column.
-  for (int j = 0; j < d; ++j) {
-    const double dj = A[j * kCP + j];  // the same LDS value in every thread
-    const double inv = dj > tol ? 1.0 / dj : 0.0;
-    for (int i = j + 1 + tr; i < d; i += 16) {
-      const double lij = A[i * kCP + j] * inv;
-      for (int k = j + 1 + tc; k <= i; k += 16) A[i * kCP + k] -= lij * A[k * kCP + j];
+  // i > j, columns j < k <= i) and leaves column j as it is. A pivot at or
+  // below tol contributes nothing and gives a zero column. Entries above the
+  // diagonal hold values that nothing reads.
+#pragma unroll
+  for (int jb = 0; jb < 4; ++jb) {
+    for (int jj = 0; jj < G; ++jj) {
+      const int j = jb * G + jj;
+      if (j >= d) break;
+      const int cur = j & 1;
+      const double inv = rcp[cur];
+      double l[4], ak[4];
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        l[a] = a >= jb ? col[cur][tr + G * a] * inv : 0.0;
+        // columns up to j are final
+        ak[a] = a > jb || (a == jb && tc > jj) ? col[cur][tc + G * a] : 0.0;
+      }
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          if (a >= b && b >= jb) A[a][b] = fma(-l[a], ak[b], A[a][b]);
+      // column j + 1 and the reciprocal of its pivot, for the next step
+      const bool wrap = jj == G - 1;
+      const int jn = j + 1;
+      if (jn < d && tc == (wrap ? 0 : jj + 1)) {
+        double nx[4];
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          nx[a] = wrap && jb < 3 ? A[a][jb < 3 ? jb + 1 : jb] : A[a][jb];
+          if (a >= jb) col[cur ^ 1][tr + G * a] = nx[a];
+        }
+        if (tr == tc) {
+          const double dj = wrap && jb < 3 ? nx[jb < 3 ? jb + 1 : jb] : nx[jb];
+          rcp[cur ^ 1] = dj > tol ? 1.0 / dj : 0.0;
+        }
+      }
+      __syncthreads();
     }
-    __syncthreads();
   }
   // Scale: l_jj = sqrt(a_jj), l_ij = a_ij / l_jj.
-  __shared__ double piv[kMaxD], ipiv[kMaxD];
-  if (tid < d) {
-    const double dj = A[tid * kCP + tid];
-    const double p = dj > tol ? sqrt(dj) : 0.0;
-    piv[tid] = p;
-    ipiv[tid] = p > 0.0 ? 1.0 / p : 0.0;
-  }
+  if (tr == tc)
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const double dj = A[a][a];
+      const double p = dj > tol ? sqrt(dj) : 0.0;
+      piv[tr + G * a] = p;
+      ipiv[tr + G * a] = p > 0.0 ? 1.0 / p : 0.0;
+    }
   __syncthreads();
-  for (int i = tr; i < d; i += 16)
-    for (int k = tc; k <= i; k += 16) A[i * kCP + k] = k == i ? piv[k] : A[i * kCP + k] * ipiv[k];
-  __syncthreads();
-  for (int i = tr; i < d; i += 16)
-    for (int k = tc; k < d; k += 16) F[i * d + k] = k <= i ? (float)A[i * kCP + k] : 0.f;
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int i = tr + G * a, k = tc + G * b;
+      const float f = k > i ? 0.f : (float)(k == i ? piv[k] : A[a][b] * ipiv[k]);
+      if (i < d && k < d) F[i * d + k] = f;
+      if (pack >= 0) chf[i * FP + k] = f;
+    }
   if (pack >= 0) {
     // transposed hi/lo bf16 operand of the factor (the MFMA query pass)
+    __syncthreads();
     bf16* out = wop(C, bh, pack);
-    for (int e = tid; e < d * d; e += kCholThreads) {
+    for (int e = tid; e < d * d; e += chol_threads<DM>()) {
       const int i = e / d, k = e % d;  // out row i (output dim), column k (input dim)
-      const float w = i <= k ? (float)A[k * kCP + i] : 0.f;
+      const float w = chf[k * FP + i];
       const bf16 hi = (bf16)w;
       out[e] = hi;
       out[d * d + e] = (bf16)(w - (float)hi);
@@ -1738,22 +1895,6 @@ __global__ __launch_bounds__(64) void split_choose_kernel(Ctx C, LevelArgs L) {
 // reproducible bit for bit.
 // ---------------------------------------------------------------------------
 
-// Separately rounded fp32 operations: a product is never fused into the sum
-// that follows it, and the quotient and square root are the correctly rounded
-// ones (the default contraction would otherwise turn a + x * y into an FMA,
-// and the HIP __f*_rn intrinsics are plain operators here).
-__device__ __forceinline__ float add_rn(float a, float b) {
-#pragma clang fp contract(off)
-  return a + b;
-}
-__device__ __forceinline__ float sub_rn(float a, float b) {
-#pragma clang fp contract(off)
-  return a - b;
-}
-__device__ __forceinline__ float mul_rn(float a, float b) {
-#pragma clang fp contract(off)
-  return a * b;
-}
 __device__ __forceinline__ float div_rn(float a, float b) { return a / b; }
 __device__ __forceinline__ float sqrt_rn(float a) { return __builtin_sqrtf(a); }
 
@@ -3059,7 +3200,7 @@ namespace {
 // Kernels that use more than 64 KiB of dynamic LDS declare their size once. A
 // refusal is not fatal here: the launch itself reports a real limit.
 constexpr size_t kEighLds = eigh_lds_bytes(kMaxD);
-constexpr size_t kCholLds = (size_t)kMaxD * kCP * sizeof(double);
+constexpr size_t chol_lds_bytes(int dm) { return (size_t)dm * (dm + 1) * sizeof(float); }
 constexpr size_t kQnormLds = (size_t)(kMaxD + 2 * kStage) * kDP * sizeof(float);
 constexpr size_t kProjLds = (size_t)(kMaxD + kStage) * kDP * sizeof(float);
 constexpr size_t kGatherLds = (size_t)kMaxC * kMaxD * sizeof(float);
@@ -3070,8 +3211,8 @@ hipError_t set_lds_limits() {
     (void)hipFuncSetAttribute((const void*)eigh_kernel<64>,
                               hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)eigh_lds_bytes(64));
-    (void)hipFuncSetAttribute((const void*)cholesky_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                        (int)kCholLds);
+    (void)hipFuncSetAttribute((const void*)cholesky_kernel<128>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)chol_lds_bytes(128));
     (void)hipFuncSetAttribute((const void*)qnorm_partial_kernel,
                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)kQnormLds);
     (void)hipFuncSetAttribute((const void*)project_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -3194,12 +3335,16 @@ hipError_t launch_cluster(const Prob& P, const void* q, const void* k, const voi
     EighJobs J;
     if (P.xf == CA_XF_PCA) {
       // principal axes of the centred queries and keys, oriented by the means
-      J.j[0] = {M_A0, -1, -1, 0, -1, V_MUQ, M_E0, V_L0, -1, M_TQ, wq};
-      J.j[1] = {M_CK, -1, -1, 0, -1, V_MUK, M_EK, V_LK, -1, M_TK, wk};
+      J.j[0] = {M_A0, -1, -1, 0, V_MUQ, -1, M_TQ, wq};
+      J.j[1] = {M_CK, -1, -1, 0, V_MUK, -1, M_TK, wk};
     } else {
-      hipLaunchKernelGGL(cholesky_kernel, dim3(BH, 2), dim3(kCholThreads), kCholLds, st, C,
-                         (int)M_A0, (int)M_E0, (int)M_CK, (int)M_EK,
-                         P.dtype == CA_BF16 ? (int)O_FK : -1);
+      const int fk = P.dtype == CA_BF16 ? (int)O_FK : -1;
+      if (d <= 64)
+        hipLaunchKernelGGL(cholesky_kernel<64>, dim3(BH, 2), dim3(chol_threads<64>()),
+                           chol_lds_bytes(64), st, C, (int)M_A0, (int)M_E0, (int)M_CK, (int)M_EK, fk);
+      else
+        hipLaunchKernelGGL(cholesky_kernel<128>, dim3(BH, 2), dim3(chol_threads<128>()),
+                           chol_lds_bytes(128), st, C, (int)M_A0, (int)M_E0, (int)M_CK, (int)M_EK, fk);
       CA_CHECK();
       if (P.xf == CA_XF_METRIC) {
         const size_t qlds = kQnormLds;
@@ -3215,16 +3360,16 @@ hipError_t launch_cluster(const Prob& P, const void* q, const void* k, const voi
         CA_CHECK();
       }
       // keys: C2 = S_q^T C_K S_q, oriented by S_q^T mu_K, T_K = S_q U2
-      J.j[0] = {M_CK, M_E0, V_MUK, 0, V_KQ, -1, M_C2, V_L2, M_E0, M_TK, wk};
+      J.j[0] = {M_CK, M_E0, V_MUK, 0, -1, M_E0, M_TK, wk};
       if (P.xf == CA_XF_ADAPTIVE)
         // queries: cov(q S_k) = S_k^T (Q^T Q / n - mu_Q mu_Q^T) S_k, oriented by
         // S_k^T mu_Q (the mean of q S_k), W_Q = S_k U3; no normalisation
-        J.j[1] = {M_A0, M_EK, V_MUQ, 1, -1, -1, M_C3, V_L3, M_EK, M_TQ, wq};
+        J.j[1] = {M_A0, M_EK, V_MUQ, 1, -1, M_EK, M_TQ, wq};
       else if (mfma)
         // queries: cov(r(q)), oriented by mu_r, W_Q = S_k U3
-        J.j[1] = {M_C3, M_EK, V_MUR, 1, V_MUR, -1, M_C3, V_L3, M_EK, M_TQ, wq};
+        J.j[1] = {M_C3, M_EK, V_MUR, 1, -1, M_EK, M_TQ, wq};
       else
-        J.j[1] = {M_C3, -1, V_MUR, 1, -1, -1, M_C3, V_L3, M_EK, M_TQ, wq};
+        J.j[1] = {M_C3, -1, V_MUR, 1, -1, M_EK, M_TQ, wq};
     }
     if (basic)  // the metric root space: the Cholesky factors are the projections
       hipLaunchKernelGGL(copy_roots_kernel, dim3(BH), dim3(256), 0, st, C, (int)mfma);
