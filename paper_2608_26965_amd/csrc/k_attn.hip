@@ -4,12 +4,13 @@
 // One workgroup per (head, query cluster); the workgroup streams the k
 // selected key-cluster tiles through LDS (double-buffered) and runs an online
 // softmax. bf16: MFMA 32x32x16 with fp32 accumulation, one wavefront per 32
-// queries. fp32: plain FMA, one thread per query.
+// queries. fp32: MFMA 16x16x4, one workgroup per 16 queries.
 #include <math.h>
 
 #include <type_traits>
 
 #include "attn_tile.h"
+#include "f32_tile.h"
 
 namespace ca {
 
@@ -591,114 +592,92 @@ __global__ __launch_bounds__((64 * attn_waves<D, CQ, CK, SPLIT>()),
   if (h == 0) lse[qrow] = (m_fin + __builtin_amdgcn_logf(l_tot)) * kLn2;
 }
 
-// fp32 path: one thread per query, keys streamed through LDS 32 at a time.
+// Keys of the selected clusters as tiles of 16: tile T is tile T % tpc of the
+// list's cluster T / tpc.
 template <int DP>
-__global__ __launch_bounds__(256) void attn_f32_kernel(
+struct ListKeys {
+  const float* kp;         // this head's permuted keys
+  const float* vp;         // and value tiles
+  const int32_t* lst;
+  const int32_t* cnt;      // this head's cluster sizes
+  int nkc, ck, d, tpc, ntile, lane;
+  float scale;
+
+  // cluster and first key of tile T, and the cluster's number of real keys
+  // (no more than there are rows; 0 past the list)
+  __device__ __forceinline__ int tile(int T, int& k0, int& n) const {
+    const int Tc = T < ntile ? T : ntile - 1;
+    const int e = Tc / tpc;
+    k0 = 16 * (Tc - e * tpc);
+    int b = lst[e];
+    b = b < 0 ? 0 : (b >= nkc ? nkc - 1 : b);
+    n = T < ntile ? min(cnt[b], ck) : 0;
+    return b;
+  }
+  __device__ __forceinline__ void rows(int T, f32x4 (&kf)[DP / 16]) const {
+    int k0, n;
+    const int b = tile(T, k0, n);
+    const int j = min(k0 + (lane & 15), ck - 1);  // rows past the cluster are masked
+    f32_load_rows<DP>(kp + ((size_t)b * ck + j) * d, d, lane >> 4, kf);
+  }
+  __device__ __forceinline__ void vals(int T, f32x4 (&vf)[DP / 16]) const {
+    int k0, n;
+    const int b = tile(T, k0, n);
+    const int j0 = k0 + 4 * (lane >> 4);
+#pragma unroll
+    for (int t = 0; t < DP / 16; ++t) {
+      const int dim = 16 * t + (lane & 15);
+      f32x4 v = {0.f, 0.f, 0.f, 0.f};
+      if (dim < d && j0 < n) {
+        const float* p = vp + ((size_t)b * d + dim) * ck + j0;
+        if (j0 + 4 <= n) {
+          v = load4u(p);
+        } else {
+#pragma unroll
+          for (int r = 0; r < 3; ++r)
+            if (j0 + r < n) v[r] = p[r];
+        }
+      }
+      vf[t] = v;
+    }
+  }
+  __device__ __forceinline__ void logits(int T, f32x4& s) const {
+    int k0, n;
+    (void)tile(T, k0, n);
+    const int j0 = k0 + 4 * (lane >> 4);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s[r] = j0 + r < n ? s[r] * scale : -INFINITY;
+  }
+};
+
+// fp32 path: one workgroup per 16 queries of a cluster (f32_tile.h).
+template <int DP>
+__global__ __launch_bounds__(F32Tile<DP>::NT) void attn_f32_kernel(
     const float* __restrict__ qp, const float* __restrict__ kp, const float* __restrict__ vp,
     const int32_t* __restrict__ count_k, const int32_t* __restrict__ lists,
     const int32_t* __restrict__ lens, int nqc, int nkc, int cq, int ck, int d, int k, float scale,
     float* __restrict__ op, float* __restrict__ lse) {
-  // 256 threads: query i of the cluster (qpad = cq rounded up to 64) and key
-  // part part = tid / qpad of parts = 256 / qpad; part p takes keys p, p +
-  // parts, ... of every staged chunk with a softmax state of its own, and the
-  // parts are merged at the end (32 queries at a time through LDS).
-  constexpr int KC = 32, QB = 32;
-  __shared__ float Ksh[KC][DP + 1];
-  __shared__ float Vsh[KC][DP + 1];
-  __shared__ float mrg[(DP + 2) * QB];  // [field][query of the round]
-  const int a = blockIdx.x, bh = blockIdx.y;
-  const int qpad = (cq + 63) / 64 * 64, parts = 256 / qpad;
-  const int i = threadIdx.x % qpad, part = threadIdx.x / qpad;
-  const bool active = i < cq && part < parts;
-  const size_t qrow = ((size_t)bh * nqc + a) * cq + (active ? i : 0);
-  const size_t nk_pad = (size_t)nkc * ck;
-  float q[DP], o[DP];
-#pragma unroll
-  for (int t = 0; t < DP; ++t) {
-    q[t] = (active && t < d) ? qp[qrow * d + t] : 0.f;
-    o[t] = 0.f;
-  }
-  float m = -INFINITY, l = 0.f;
-  const int32_t* lst = lists + ((size_t)bh * nqc + a) * k;
+  __shared__ F32Merge<DP> M;
+  const int qt = (cq + 15) / 16;  // query tiles of a cluster
+  const int a = blockIdx.x / qt, q0 = 16 * (blockIdx.x % qt), bh = blockIdx.y;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const size_t qrow0 = ((size_t)bh * nqc + a) * cq;
+  f32x4 qf[DP / 16];
+  f32_load_rows<DP>(qp + (qrow0 + min(q0 + (lane & 15), cq - 1)) * d, d, lane >> 4, qf);
   const int nt = lens ? min(max(lens[(size_t)bh * nqc + a], 1), k) : k;
-  for (int tt = 0; tt < nt; ++tt) {
-    int b = lst[tt];
-    b = b < 0 ? 0 : (b >= nkc ? nkc - 1 : b);
-    const int cnt = count_k[(size_t)bh * nkc + b];
-    for (int k0 = 0; k0 < cnt; k0 += KC) {
-      const int nk = min(KC, cnt - k0);
-      __syncthreads();
-      for (int e = threadIdx.x; e < KC * DP; e += blockDim.x) {
-        int kk = e / DP, t = e % DP;
-        Ksh[kk][t] = (kk < nk && t < d) ? kp[((size_t)bh * nk_pad + (size_t)b * ck + k0 + kk) * d + t]
-                                        : 0.f;
-      }
-      for (int e = threadIdx.x; e < KC * DP; e += blockDim.x) {
-        int kk = e % KC, t = e / KC;
-        Vsh[kk][t] = (kk < nk && t < d) ? vp[(((size_t)bh * nkc + b) * d + t) * ck + k0 + kk] : 0.f;
-      }
-      __syncthreads();
-      for (int kk = part; kk < nk; kk += parts) {
-        // four partial sums: four short dependency chains instead of one
-        float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-#pragma unroll
-        for (int t = 0; t < DP; t += 4) {
-          s0 = __builtin_fmaf(q[t], Ksh[kk][t], s0);
-          s1 = __builtin_fmaf(q[t + 1], Ksh[kk][t + 1], s1);
-          s2 = __builtin_fmaf(q[t + 2], Ksh[kk][t + 2], s2);
-          s3 = __builtin_fmaf(q[t + 3], Ksh[kk][t + 3], s3);
-        }
-        const float s = ((s0 + s1) + (s2 + s3)) * scale;
-        if (s > m) {
-          const float al = expf(m - s);
-#pragma unroll
-          for (int t = 0; t < DP; ++t) o[t] *= al;
-          l *= al;
-          m = s;
-        }
-        const float pw = expf(s - m);
-        l += pw;
-#pragma unroll
-        for (int t = 0; t < DP; ++t) o[t] = __builtin_fmaf(pw, Vsh[kk][t], o[t]);
-      }
-    }
+  const int tpc = (ck + 15) / 16;
+  const ListKeys<DP> src{kp + (size_t)bh * nkc * ck * d, vp + (size_t)bh * nkc * d * ck,
+                         lists + ((size_t)bh * nqc + a) * k, count_k + (size_t)bh * nkc,
+                         nkc, ck, d, tpc, nt * tpc, lane, scale};
+  F32State<DP> st;
+  f32_online<DP>(src, qf, w, st);
+  f32_merge<DP>(M, st, w, lane);
+  const int nq = min(16, cq - q0);
+  for (int e = threadIdx.x; e < nq * d; e += F32Tile<DP>::NT) {
+    const int q = e / d, t = e - q * d;
+    op[(qrow0 + q0) * d + e] = f32_merged<DP>(M, q, t) * (1.f / M.sum[q]);
   }
-  // merge the key parts into part 0 (a part without keys has l = 0)
-  for (int q0 = 0; q0 < qpad; q0 += QB) {
-    const bool inq = i >= q0 && i < q0 + QB;
-    for (int pp = 1; pp < parts; ++pp) {
-      __syncthreads();
-      if (active && inq && part == pp) {
-        const int j = i - q0;
-        mrg[j] = m;
-        mrg[QB + j] = l;
-#pragma unroll
-        for (int t = 0; t < DP; ++t) mrg[(2 + t) * QB + j] = o[t];
-      }
-      __syncthreads();
-      if (active && inq && part == 0) {
-        const int j = i - q0;
-        const float lb = mrg[QB + j];
-        const float ma = l > 0.f ? m : -INFINITY, mb = lb > 0.f ? mrg[j] : -INFINITY;
-        const float mm = fmaxf(ma, mb);
-        const float mu = mm == -INFINITY ? 0.f : mm;
-        const float sa = expf(ma - mu), sb = expf(mb - mu);
-        l = l * sa + lb * sb;
-#pragma unroll
-        for (int t = 0; t < DP; ++t) o[t] = o[t] * sa + mrg[(2 + t) * QB + j] * sb;
-        m = mu;
-      }
-    }
-  }
-  if (active && part == 0) {
-    const float inv = 1.f / l;
-    // unrolled over DP with a guard: a loop to d would index o[] at run time
-    // and move it to scratch memory
-#pragma unroll
-    for (int t = 0; t < DP; ++t)
-      if (t < d) op[qrow * d + t] = o[t] * inv;
-    lse[qrow] = m + logf(l);
-  }
+  if (threadIdx.x < nq) lse[qrow0 + q0 + threadIdx.x] = M.mx[threadIdx.x] + logf(M.sum[threadIdx.x]);
 }
 
 // Launch order for lists of different lengths. Work of an item (head, query
@@ -853,21 +832,18 @@ hipError_t launch_attn(const Prob& P, const void* qp, const void* kp, const void
 #undef CA_ATTN_CASE
     return hipErrorInvalidValue;
   }
-  dim3 grid(P.nqc, P.BH);
-  const int threads = 256;  // (cq rounded up to 64) x key parts
-  if (P.d <= 32) {
-    hipLaunchKernelGGL(attn_f32_kernel<32>, grid, dim3(threads), 0, st, (const float*)qp,
-                       (const float*)kp, (const float*)vp, count_k, lists, lens, P.nqc, P.nkc,
-                       P.cq, P.ck, P.d, k, scale, (float*)op, lse);
-  } else if (P.d <= 64) {
-    hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(threads), 0, st, (const float*)qp,
-                       (const float*)kp, (const float*)vp, count_k, lists, lens, P.nqc, P.nkc,
-                       P.cq, P.ck, P.d, k, scale, (float*)op, lse);
-  } else {
-    hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(threads), 0, st, (const float*)qp,
-                       (const float*)kp, (const float*)vp, count_k, lists, lens, P.nqc, P.nkc,
-                       P.cq, P.ck, P.d, k, scale, (float*)op, lse);
-  }
+  const dim3 grid(P.nqc * ((P.cq + 15) / 16), P.BH);
+#define CA_ATTN_F32(DP)                                                                        \
+  hipLaunchKernelGGL(attn_f32_kernel<DP>, grid, dim3(F32Tile<DP>::NT), 0, st, (const float*)qp, \
+                     (const float*)kp, (const float*)vp, count_k, lists, lens, P.nqc, P.nkc,    \
+                     P.cq, P.ck, P.d, k, scale, (float*)op, lse)
+  if (P.d <= 32)
+    CA_ATTN_F32(32);
+  else if (P.d <= 64)
+    CA_ATTN_F32(64);
+  else
+    CA_ATTN_F32(128);
+#undef CA_ATTN_F32
   return hipGetLastError();
 }
 

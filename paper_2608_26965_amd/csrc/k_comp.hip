@@ -10,12 +10,13 @@
 // (keys row-major, values transposed, plus the log2 cluster sizes) in the
 // workspace; every query cluster then streams those tiles into LDS with
 // direct-to-LDS copies and contracts them on MFMA exactly like key tiles.
-// fp32: one thread per query.
+// fp32: MFMA 16x16x4, one workgroup per 16 queries.
 #include <math.h>
 
 #include <type_traits>
 
 #include "attn_tile.h"
+#include "f32_tile.h"
 
 namespace ca {
 
@@ -371,9 +372,44 @@ __global__ __launch_bounds__(CQ * 2, (comp_waves_per_simd<D, CQ>())) void comp_b
   if (lse_out && h == 0) lse_out[(size_t)bh * nq + orig] = lse;
 }
 
-// fp32 path: one thread per query, plain FMA; centroids streamed through LDS.
+// The centroids as tiles of 16 keys, the selected ones masked.
 template <int DP>
-__global__ __launch_bounds__(256) void comp_f32_kernel(
+struct CentKeys {
+  const float* ck;          // this head's key centroids
+  const float* cv;          // and value centroids
+  const int32_t* cnt;       // and cluster sizes
+  const uint32_t* selmask;  // LDS bitmap of the selected clusters
+  int nkc, d, ntile, lane;
+  float scale;
+
+  __device__ __forceinline__ void rows(int T, f32x4 (&kf)[DP / 16]) const {
+    const int b = min(16 * T + (lane & 15), nkc - 1);  // rows past the end are masked
+    f32_load_rows<DP>(ck + (size_t)b * d, d, lane >> 4, kf);
+  }
+  __device__ __forceinline__ void vals(int T, f32x4 (&vf)[DP / 16]) const {
+#pragma unroll
+    for (int t = 0; t < DP / 16; ++t) {
+      const int dim = 16 * t + (lane & 15);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int b = 16 * T + 4 * (lane >> 4) + r;
+        vf[t][r] = dim < d && b < nkc ? cv[(size_t)b * d + dim] : 0.f;
+      }
+    }
+  }
+  __device__ __forceinline__ void logits(int T, f32x4& s) const {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int b = 16 * T + 4 * (lane >> 4) + r;
+      const bool on = b < nkc && !((selmask[b >> 5] >> (b & 31)) & 1u);
+      s[r] = on ? s[r] * scale + logf((float)cnt[on ? b : 0]) : -INFINITY;
+    }
+  }
+};
+
+// fp32 path: one workgroup per 16 queries of a cluster (f32_tile.h).
+template <int DP>
+__global__ __launch_bounds__(F32Tile<DP>::NT) void comp_f32_kernel(
     const float* __restrict__ qp, const float* __restrict__ cent_k,
     const float* __restrict__ cent_v, const int32_t* __restrict__ count_k,
     const int32_t* __restrict__ lists, const int32_t* __restrict__ lens, int nq, int H, int nqc,
@@ -381,88 +417,64 @@ __global__ __launch_bounds__(256) void comp_f32_kernel(
     const float* __restrict__ lse_s,
     const int32_t* __restrict__ perm_q, float* __restrict__ out, float* __restrict__ lse_out,
     Lay lo) {
-  constexpr int KC = 32;
-  __shared__ float Ksh[KC][DP + 1];
-  __shared__ float Vsh[KC][DP + 1];
-  __shared__ float bias[KC];
+  constexpr int NT = F32Tile<DP>::NT;
+  __shared__ F32Merge<DP> M;
   __shared__ uint32_t selmask[kMaskWords];
-  const int a = blockIdx.x, bh = blockIdx.y, i = threadIdx.x;
-  const int prow = a * cq + i;
-  const bool active = i < cq && prow < nq;
-  const size_t qrow = ((size_t)bh * nqc + a) * cq + (i < cq ? i : 0);
+  __shared__ float ws[16], wc[16];  // weights of the sparse part and of the merged centroid part
+  __shared__ size_t orow[16];
+  const int qt = (cq + 15) / 16;
+  const int a = blockIdx.x / qt, q0 = 16 * (blockIdx.x % qt), bh = blockIdx.y;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, tid = threadIdx.x;
+  const size_t qrow0 = ((size_t)bh * nqc + a) * cq;
   const int nsel = lens ? min(max(lens[(size_t)bh * nqc + a], 1), k) : k;
   const bool do_comp = enable && nsel < nkc;
-  float q[DP], o[DP];
-#pragma unroll
-  for (int t = 0; t < DP; ++t) {
-    q[t] = (i < cq && t < d) ? qp[qrow * d + t] : 0.f;
-    o[t] = 0.f;
-  }
-  float m = -INFINITY, l = 0.f;
+  const int nrow = min(min(16, cq - q0), nq - (a * cq + q0));  // real rows of the tile
+  if (nrow <= 0) return;
   if (do_comp) {
-    const int nwords = (nkc + 31) >> 5;
-    for (int e = i; e < nwords; e += blockDim.x) selmask[e] = 0u;
+    f32x4 qf[DP / 16];
+    f32_load_rows<DP>(qp + (qrow0 + min(q0 + (lane & 15), cq - 1)) * d, d, lane >> 4, qf);
+    // tiles past the end read the bitmap up to the next whole step
+    const int ntile = (nkc + 15) / 16;
+    const int nwords = min(kMaskWords, (nkc + 31) / 32);
+    for (int e = tid; e < nwords; e += NT) selmask[e] = 0u;
     __syncthreads();
     const int32_t* lst = lists + ((size_t)bh * nqc + a) * k;
-    for (int e = i; e < nsel; e += blockDim.x) {
-      int b = lst[e];
+    for (int e = tid; e < nsel; e += NT) {
+      const int b = lst[e];
       if (b >= 0 && b < nkc) atomicOr(&selmask[b >> 5], 1u << (b & 31));
     }
-    for (int b0 = 0; b0 < nkc; b0 += KC) {
-      const int nb = min(KC, nkc - b0);
-      __syncthreads();
-      for (int e = i; e < KC * DP; e += blockDim.x) {
-        const int r = e / DP, t = e % DP;
-        const bool in = r < nb && t < d;
-        Ksh[r][t] = in ? cent_k[((size_t)bh * nkc + b0 + r) * d + t] : 0.f;
-        Vsh[r][t] = in ? cent_v[((size_t)bh * nkc + b0 + r) * d + t] : 0.f;
-      }
-      for (int e = i; e < KC; e += blockDim.x) {
-        const int b = b0 + e;
-        bias[e] = (e < nb && !((selmask[b >> 5] >> (b & 31)) & 1u))
-                      ? logf((float)count_k[(size_t)bh * nkc + b])
-                      : -INFINITY;
-      }
-      __syncthreads();
-      for (int r = 0; r < nb; ++r) {
-        if (bias[r] == -INFINITY) continue;
-        float s = 0.f;
-#pragma unroll
-        for (int t = 0; t < DP; ++t) s = __builtin_fmaf(q[t], Ksh[r][t], s);
-        s = s * scale + bias[r];
-        if (s > m) {
-          const float al = expf(m - s);
-#pragma unroll
-          for (int t = 0; t < DP; ++t) o[t] *= al;
-          l *= al;
-          m = s;
-        }
-        const float pw = expf(s - m);
-        l += pw;
-#pragma unroll
-        for (int t = 0; t < DP; ++t) o[t] = __builtin_fmaf(pw, Vsh[r][t], o[t]);
-      }
+    __syncthreads();
+    const CentKeys<DP> src{cent_k + (size_t)bh * nkc * d, cent_v + (size_t)bh * nkc * d,
+                           count_k + (size_t)bh * nkc, selmask, nkc, d, ntile, lane, scale};
+    F32State<DP> st;
+    f32_online<DP>(src, qf, w, st);
+    f32_merge<DP>(M, st, w, lane);
+  }
+  if (tid < nrow) {
+    const int prow = a * cq + q0 + tid;
+    const float ls = lse_s[qrow0 + q0 + tid];
+    float wq = 1.f, wcq = 0.f, lse = ls;
+    if (do_comp && M.sum[tid] > 0.f) {
+      const float lc = M.mx[tid] + logf(M.sum[tid]);
+      const float mm = fmaxf(ls, lc);
+      lse = mm + logf(expf(ls - mm) + expf(lc - mm));
+      wq = expf(ls - lse);
+      wcq = expf(lc - lse) * (1.f / M.sum[tid]);
     }
+    ws[tid] = wq;
+    wc[tid] = wcq;
+    int orig = perm_q[(size_t)bh * nq + prow];
+    orig = orig < 0 ? 0 : (orig >= nq ? nq - 1 : orig);
+    orow[tid] = row_off(bh, orig, lo);
+    if (lse_out) lse_out[(size_t)bh * nq + orig] = lse;
   }
-  if (!active) return;
-  const float ls = lse_s[qrow];
-  float ws = 1.f, wc = 0.f, lse = ls, inv_c = 0.f;
-  if (l > 0.f) {
-    const float lc = m + logf(l);
-    const float mm = fmaxf(ls, lc);
-    lse = mm + logf(expf(ls - mm) + expf(lc - mm));
-    ws = expf(ls - lse);
-    wc = expf(lc - lse);
-    inv_c = 1.f / l;
+  __syncthreads();
+  for (int e = tid; e < nrow * d; e += NT) {
+    const int q = e / d, t = e - q * d;
+    float x = ws[q] * op[(qrow0 + q0) * d + e];
+    if (do_comp) x += wc[q] * f32_merged<DP>(M, q, t);
+    out[orow[q] + t] = x;
   }
-  int orig = perm_q[(size_t)bh * nq + prow];
-  orig = orig < 0 ? 0 : (orig >= nq ? nq - 1 : orig);
-  float* orow = out + row_off(bh, orig, lo);
-  // unrolled over DP with a guard, so that o[] stays in registers
-#pragma unroll
-  for (int t = 0; t < DP; ++t)
-    if (t < d) orow[t] = ws * op[qrow * d + t] + wc * (o[t] * inv_c);
-  if (lse_out) lse_out[(size_t)bh * nq + orig] = lse;
 }
 
 template <int D, int CQ>
@@ -520,14 +532,12 @@ hipError_t launch_comp(const Prob& P, const void* qp, const float* cent_k, const
 #undef CA_COMP_CASE
     return hipErrorInvalidValue;
   }
-  dim3 grid(P.nqc, P.BH);
-  const int threads = ((P.cq + 63) / 64) * 64;
+  const dim3 grid(P.nqc * ((P.cq + 15) / 16), P.BH);
 #define CA_COMP_F32(DP)                                                                       \
-  hipLaunchKernelGGL(comp_f32_kernel<DP>, grid, dim3(threads), 0, st, (const float*)qp,       \
-                     cent_k, cent_v, count_k, lists, lens, P.nq, P.H, P.nqc, P.nkc, P.cq, P.d, \
-                     k,                                                                       \
-                     scale, enable, (const float*)op, lse, perm_q, (float*)out, lse_out,      \
-                     P.lo)
+  hipLaunchKernelGGL(comp_f32_kernel<DP>, grid, dim3(F32Tile<DP>::NT), 0, st,                 \
+                     (const float*)qp, cent_k, cent_v, count_k, lists, lens, P.nq, P.H, P.nqc, \
+                     P.nkc, P.cq, P.d, k, scale, enable, (const float*)op, lse, perm_q,       \
+                     (float*)out, lse_out, P.lo)
   if (P.d <= 32)
     CA_COMP_F32(32);
   else if (P.d <= 64)

@@ -1,6 +1,8 @@
 """Kernels at the edges of their tiles and ranges, against the oracle."""
 import pytest
 
+from tests.test_gpu_attention import test_block_sparse_attention_parity as _attention_parity
+from tests.test_gpu_attention import test_compensation_parity as _compensation_parity
 from tests.test_gpu_cluster import test_cluster_parity as _cluster_parity
 
 pytestmark = pytest.mark.gpu
@@ -16,3 +18,56 @@ pytestmark = pytest.mark.gpu
 ])
 def test_transform_edges(dt, d, xf):
     _cluster_parity(dt, 900, d, 32, xf)
+
+
+# fp32 attention and compensation: tiles of 16 queries and 16 keys in clusters
+# smaller, larger and no multiple of them; head dimensions that leave part of a
+# 16-wide tile empty; a remainder cluster; every cluster kept (nothing to
+# compensate).
+F32_EDGES = [
+    # d, cq, ck, n, k
+    (4, 1, 1, 37, 5), (20, 2, 2, 61, 9), (100, 16, 4, 203, 11), (64, 32, 8, 130, 7),
+    (128, 256, 256, 700, 2), (32, 64, 128, 1000, 8), (36, 128, 32, 555, 17),
+]
+
+
+@pytest.mark.parametrize("d,cq,ck,n,k", F32_EDGES)
+def test_f32_attention_edges(d, cq, ck, n, k):
+    _attention_parity("f32", d, cq, ck, n, k)
+    _compensation_parity("f32", d, cq, ck, n, k, True)
+
+
+def test_f32_four_byte_alignment():
+    """Dense fp32 tensors need no more than their own 4-byte alignment: the
+    same bits from inputs and outputs that start one float past a 16-byte
+    boundary."""
+    import torch
+    import paper_2608_26965_amd as ca
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    H, n, d, c, k = 2, 300, 20, 32, 4
+    p = ca.Problem(1, H, n, n, d, c, c, torch.float32)
+
+    def rnd(*shape):
+        return torch.randn(*shape, device="cuda", generator=g)
+
+    def off(x):  # a copy one float into a buffer
+        b = torch.empty(x.numel() + 1, dtype=x.dtype, device="cuda")
+        b[1:] = x.reshape(-1)
+        return b[1:].view(x.shape)
+
+    qp, kp, vp = rnd(H, p.nq_pad, d), rnd(H, p.nk_pad, d), rnd(H, p.nkc, d, c)
+    kbar, vbar = rnd(H, p.nkc, d), rnd(H, p.nkc, d)
+    cnt = torch.full((H, p.nkc), c, dtype=torch.int32, device="cuda")
+    cnt[:, -1] = n - (p.nkc - 1) * c
+    lists = torch.stack([torch.randperm(p.nkc, device="cuda", generator=g)[:k].sort().values
+                         for _ in range(H * p.nqc)]).view(H, p.nqc, k).to(torch.int32)
+    perm = torch.arange(n, dtype=torch.int32, device="cuda").repeat(H, 1)
+    got = []
+    for f in (lambda x: x, off):
+        op, lse = ca.block_sparse_attn(p, f(qp), f(kp), f(vp), cnt, lists, k)
+        out, _ = ca.compensate(p, f(qp), f(kbar), f(vbar), cnt, lists, k, f(op), f(lse), perm,
+                               out=f(torch.zeros(p.shape(n), device="cuda")))
+        got.append((op, lse, out))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
