@@ -309,6 +309,37 @@ __device__ __forceinline__ double wave_sum(double x) {
   const int lo = __builtin_amdgcn_readlane((int)b, 63), hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
   return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
+// Largest value of the wavefront (NaN only if all are), returned to every lane
+template <int CTRL>
+__device__ __forceinline__ float dpp_max(float x) {
+  return fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(
+                      __float_as_int(x), __float_as_int(x), CTRL, 0xF, 0xF, false)));
+}
+__device__ __forceinline__ float wave_max(float x) {
+  x = dpp_max<0xB1>(x);   // quad_perm [1, 0, 3, 2]
+  x = dpp_max<0x4E>(x);   // quad_perm [2, 3, 0, 1]
+  x = dpp_max<0x141>(x);  // row_half_mirror
+  x = dpp_max<0x140>(x);  // row_mirror
+  x = fmaxf(fmaxf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 0)),
+                  __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 16))),
+            fmaxf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 32)),
+                  __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 48))));
+  return x;
+}
+// Inclusive sum over the lanes up to this one
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ int dpp_shift_add(int x) {
+  return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ int wave_scan(int x) {
+  x = dpp_shift_add<0x111>(x);       // row_shr:1
+  x = dpp_shift_add<0x112>(x);       // row_shr:2
+  x = dpp_shift_add<0x114>(x);       // row_shr:4
+  x = dpp_shift_add<0x118>(x);       // row_shr:8
+  x = dpp_shift_add<0x142, 0xA>(x);  // row_bcast15 into rows 1, 3
+  x = dpp_shift_add<0x143, 0xC>(x);  // row_bcast31 into rows 2, 3
+  return x;
+}
 __device__ __forceinline__ float read_lane(float x, int l) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
 }
@@ -1723,6 +1754,13 @@ __global__ __launch_bounds__(256, 2) void project_mfma_kernel(Ctx C) {
 // Recursive split
 // ---------------------------------------------------------------------------
 
+// Position of subsample row j of m in a node of `size` tokens (at most 2^22):
+// floor((2j + 1) size / (2m)).
+__device__ __forceinline__ int sample_pos(int j, int size, int m) {
+  const uint32_t x = (uint32_t)(2 * j + 1) * (uint32_t)size;
+  return (int)((m & (m - 1)) == 0 ? x >> (__builtin_ctz(m) + 1) : x / (uint32_t)(2 * m));
+}
+
 // Highest-variance coordinate of the node's subsample, computed by one
 // wavefront: lane t owns coordinates t and t + 64. fp64, two passes over the
 // rows in order, mean = sum/m, variance = sum((y - mean)^2)/m, no contraction;
@@ -1742,7 +1780,7 @@ __device__ int choose_coordinate(const float* __restrict__ Y, int d, const int32
     const int j = lane + 64 * h;
     int r = 0;
     if (j < m) {
-      const int p = start + (int)(((int64_t)(2 * j + 1) * size) / (2 * m));
+      const int p = start + sample_pos(j, size, m);
       r = identity ? p : idx[p];
     }
     row[h] = r;
@@ -1804,6 +1842,119 @@ __device__ int choose_coordinate(const float* __restrict__ Y, int d, const int32
   return bt;
 }
 
+// The same choice by several wavefronts and mostly in fp32. The fp64 sums above
+// run in one fixed order, 2 m dependent additions a coordinate; but they decide
+// only where two coordinates' variances come close. So each of P wavefronts
+// sums d = v - s and d^2 (s: the value of subsample row 0) over every P-th
+// sample row in fp32, and with S and Q the sums over all rows,
+// Q/m - (S/m)^2 is within (3m + 16) 2^-24 Q/m of the exact variance whatever
+// the order (each d carries one rounding, a sum of m terms at most m, and
+// S^2 <= m Q; the fp64 variance's own error is below 2^-40 of it). A coordinate
+// whose lower bound is above every other's upper bound is the choice; where
+// none is (close calls, ties, constant or non-finite samples), the fp64 sums
+// decide. Mean and variance also give the range of the select's bins.
+//
+// What bounds it: the latency of the sample rows. One wavefront with the fp64
+// sums took 12,000 to 17,500 cycles a node at d = 64 and 56,000 at d = 128, most
+// of them in dependent fp64 operations; now 4,200 to 8,900 and 14,000.
+struct Moments {
+  float s0, S, Q;  // the shift, the sum and the sum of squares of v - s0
+};
+
+// Wavefront part `part` of P: coordinates lane + 64 h over sample rows part,
+// part + P, ...; off[h]: byte offset of sample row lane + 64 h.
+// U rows are in flight at a time.
+template <int H, int U>
+__device__ __forceinline__ void sample_moments(const float* __restrict__ Y, int d, int m,
+                                               const uint32_t (&off)[2], int part, int P,
+                                               int lane, Moments (&mo)[H]) {
+  const char* base = reinterpret_cast<const char*>(Y);
+  uint32_t lo[H];
+  float S[H][2], Q[H][2];
+  const uint32_t o0 = (uint32_t)__builtin_amdgcn_readlane((int)off[0], 0);
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    const int t = lane + 64 * h;
+    lo[h] = 4u * (uint32_t)(t < d ? t : 0);
+    mo[h].s0 = *reinterpret_cast<const float*>(base + (o0 + lo[h]));
+    S[h][0] = S[h][1] = Q[h][0] = Q[h][1] = 0.f;
+  }
+  for (int j0 = part; j0 < m; j0 += U * P) {
+    float v[U][H];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = min(j0 + u * P, m - 1);
+      const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)(j < 64 ? off[0] : off[1]), j & 63);
+#pragma unroll
+      for (int h = 0; h < H; ++h) v[u][h] = *reinterpret_cast<const float*>(base + (o + lo[h]));
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int h = 0; h < H; ++h) {
+        const float dv = j0 + u * P < m ? v[u][h] - mo[h].s0 : 0.f;
+        S[h][u & 1] += dv;
+        Q[h][u & 1] = __builtin_fmaf(dv, dv, Q[h][u & 1]);
+      }
+  }
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    mo[h].S = S[h][0] + S[h][1];
+    mo[h].Q = Q[h][0] + Q[h][1];
+  }
+}
+
+// The choice from the moments over all sample rows (one wavefront): the
+// coordinate, or -1 where the bounds leave it open; its mean and variance.
+template <int H>
+__device__ __forceinline__ int choose_by_bounds(const Moments (&mo)[H], int d, int m, int lane,
+                                                float* mean, float* var_out) {
+  const float inv = 1.f / (float)m, eps = (float)(3 * m + 16) * 0x1p-24f;
+  float lo[H], hi[H], var[H], best = -INFINITY;
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    const float a = mo[h].S * inv, q = mo[h].Q * inv;
+    var[h] = q - a * a;
+    const float e = eps * q + 0x1p-110f;  // the second term: squares that underflow
+    lo[h] = lane + 64 * h < d ? var[h] - e : -INFINITY;
+    hi[h] = var[h] + e;
+    best = fmaxf(best, lo[h]);
+  }
+  best = wave_max(best);
+  uint64_t open[H];
+  int n = 0;
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    open[h] = __ballot(lane + 64 * h < d && !(hi[h] < best));  // NaN stays open
+    n += __popcll(open[h]);
+  }
+  if (n != 1) return -1;
+  int t = 0;
+  float a = 0.f, v = 0.f;
+#pragma unroll
+  for (int h = 0; h < H; ++h)
+    if (open[h]) {
+      const int l = __builtin_ctzll(open[h]);
+      t = 64 * h + l;
+      a = read_lane(mo[h].s0 + mo[h].S * inv, l);
+      v = read_lane(var[h], l);
+    }
+  *mean = a;
+  *var_out = v;
+  return t;
+}
+
+// Origin and scale of nb linear bins over mean +- 4 sd (scale 0, one bin,
+// where there is no spread). Any range serves: bins only narrow the exact
+// select down, so hardware reciprocal square roots do.
+__device__ __forceinline__ void bin_range(float mean, float var, int nb, float* lo, float* scale) {
+  const float rs = __builtin_amdgcn_rsqf(var);  // 1 / sd
+  float l = mean - 4.f * (var * rs), s = 0.125f * (float)nb * rs;
+  if (!(var > 0.f) || !isfinite(l) || !isfinite(s)) l = s = 0.f;
+  *lo = l;
+  *scale = s;
+}
+
 // Multi-block levels. A node's split threshold is its m_L-th smallest key,
 // found exactly in two steps:
 //   keys:   every chunk block gathers its keys and counts them into kBins
@@ -1828,13 +1979,13 @@ __device__ __forceinline__ float key_value(uint32_t key) {
   return __uint_as_float((key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key);
 }
 
-// Bin of a key: floor((v - lo) * scale) clamped to [0, kBins); infinities and
+// Bin of a key: floor((v - lo) * scale) clamped to [0, nb); infinities and
 // NaNs go to the end bin their key order puts them in.
-__device__ __forceinline__ int lin_bin(uint32_t key, float lo, float scale) {
-  if (key >= 0xFF800000u) return kBins - 1;  // +inf, positive NaNs
-  if (key <= 0x007FFFFFu) return 0;          // -inf, negative NaNs
+__device__ __forceinline__ int lin_bin(uint32_t key, float lo, float scale, int nb = kBins) {
+  if (key >= 0xFF800000u) return nb - 1;  // +inf, positive NaNs
+  if (key <= 0x007FFFFFu) return 0;       // -inf, negative NaNs
   float t = (key_value(key) - lo) * scale;
-  t = fminf(fmaxf(t, 0.f), (float)(kBins - 1));
+  t = fminf(fmaxf(t, 0.f), (float)(nb - 1));
   return (int)t;
 }
 
@@ -1848,29 +1999,56 @@ struct LevelArgs {
   int32_t* idx_out;
 };
 
-__global__ __launch_bounds__(64) void split_choose_kernel(Ctx C, LevelArgs L) {
+constexpr int kChooseWaves = 4;
+
+template <int H>
+__global__ __launch_bounds__(64 * kChooseWaves) void split_choose_kernel(Ctx C, LevelArgs L) {
+  __shared__ float2 part[kChooseWaves][64 * H];
   const int pid = blockIdx.y, side = pid / C.BH, bh = pid % C.BH, node = blockIdx.x;
   const Side& S = C.s[side];
   if (L.level >= S.big) return;
   int start, size;
   node_range(S.n, S.c, L.level, node, &start, &size);
   int32_t* ns = node_ptr(C, pid, node);
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int d = C.d;
   if (size <= S.c) {
-    if (lane == 0) ns[0] = -1;
+    if (threadIdx.x == 0) ns[0] = -1;
     return;
   }
   const int32_t* idx = L.idx_in + (size_t)pid * C.nmax;
-  double mean, var;
-  const int js = choose_coordinate<64>(S.y + (size_t)bh * S.n * C.d, C.d, idx, L.first, start, size,
-                                   lane, &mean, &var);
-  if (lane == 0) {
-    const double sd = sqrt(var);
-    float lo = (float)(mean - 4.0 * sd), scale = (float)((double)kBins / (8.0 * sd));
-    if (!(sd > 0.0) || !isfinite(lo) || !isfinite(scale)) {
-      lo = 0.f;
-      scale = 0.f;  // one bin: the select step falls back to streaming
+  const float* Y = S.y + (size_t)bh * S.n * d;
+  const int m = size < d ? size : d;
+  uint32_t off[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int p = start + sample_pos(min(lane + 64 * h, m - 1), size, m);
+    off[h] = 4u * (uint32_t)d * (uint32_t)(L.first ? p : idx[p]);
+  }
+  Moments mo[H];
+  sample_moments<H, 32>(Y, d, m, off, w, kChooseWaves, lane, mo);
+#pragma unroll
+  for (int h = 0; h < H; ++h) part[w][lane + 64 * h] = make_float2(mo[h].S, mo[h].Q);
+  __syncthreads();
+  if (w != 0) return;
+#pragma unroll
+  for (int i = 1; i < kChooseWaves; ++i)
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      mo[h].S += part[i][lane + 64 * h].x;
+      mo[h].Q += part[i][lane + 64 * h].y;
     }
+  float mean, var;
+  int js = choose_by_bounds<H>(mo, d, m, lane, &mean, &var);
+  if (js < 0) {
+    double dmean, dvar;
+    js = choose_coordinate<32>(Y, d, idx, L.first, start, size, lane, &dmean, &dvar);
+    mean = (float)dmean;
+    var = (float)dvar;
+  }
+  if (lane == 0) {
+    float lo, scale;
+    bin_range(mean, var, kBins, &lo, &scale);
     const int mL = left_size(size, S.c);
     ns[0] = js;
     ns[10] = 0;
@@ -2758,40 +2936,74 @@ __global__ __launch_bounds__(256) void split_scatter_kernel(Ctx C, LevelArgs L) 
 }
 
 // Remaining levels of one node (at most the side's tail size) in one
-// workgroup: per level every active sub-node picks its coordinate (one
-// wavefront each), keys are gathered, a four-pass 8-bit radix select runs on
-// per-sub-node LDS histograms, and a block-wide scan partitions stably.
+// workgroup. Thread t holds positions 256 w + 64 u + lane of the node (w, lane:
+// its wavefront and lane; u = 0 .. 3) with their tokens and the range of the
+// sub-node that each lies in. Per level:
+//   choose     the coordinate of every sub-node (8 wavefronts share the sample
+//              rows of the first levels' few sub-nodes)
+//   keys       every position's coordinate, counted into linear bins of its
+//              sub-node over mean +- 4 sd of the sample
+//   select     the bin that holds the wanted rank, then the rank among that
+//              bin's keys by counting (one wavefront a sub-node; more than 64
+//              keys there: six radix passes of 6 bits over them)
+//   partition  ballots of the keys below and equal to the threshold give every
+//              position's place in its half
+//
+// What bounds it: small layers, the chain of barriers and memory trips, where
+// choice, radix passes over the block and a partition through LDS prefix sums
+// took 40,000 cycles a level for 1,024 tokens (now 17,000); large ones, the
+// lines fetched for one coordinate of each scattered token. Times of the
+// kernel: 63 -> 32 us (one head, 1,024 tokens), 123 -> 89 (8 heads,
+// 65,521 tokens), 898 -> 668 (16 heads, 262,144), all at d = 64; 1,623 ->
+// 742 (40 heads, 75,600 tokens, d = 128).
 constexpr int kTailThreads = 512;
+constexpr int kTailWaves = kTailThreads / 64;
+constexpr int kTailPer = kTail / kTailThreads;
 constexpr int kMaxSub = 32;
+constexpr int kTailBins = 2048;  // bins of a level, shared evenly by its sub-nodes (at least 64 each)
+static_assert(kTailPer == 4 && kTail / 64 <= 64, "position layout");
 
-__device__ __forceinline__ int scan_tail(int x, int* wsum) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int v = x;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(v, o, 64);
-    if (lane >= o) v += y;
+// Exact select by one wavefront: the rank-th smallest of keys[0, n), six bits
+// at a time, high first. *rank becomes the rank among the keys equal to it.
+__device__ uint32_t wave_radix_select(const uint32_t* keys, int n, int* rank, uint32_t* cnt,
+                                      int lane) {
+  uint32_t thr = 0u;
+  int r = *rank;
+  for (int shift = 26; shift >= -4; shift -= 6) {
+    const int sh = shift < 0 ? 0 : shift;            // the last pass holds two bits
+    const uint32_t mask = shift < 0 ? 3u : 63u;
+    const int above = shift < 0 ? 2 : sh + 6;
+    cnt[lane] = 0u;
+    wave_lds_order();
+#pragma unroll 4
+    for (int i = lane; i < n; i += 64) {
+      const uint32_t key = keys[i];
+      if (above >= 32 || (key >> above) == (thr >> above)) atomicAdd(&cnt[(key >> sh) & mask], 1u);
+    }
+    wave_lds_order();
+    const int c = (int)cnt[lane];
+    const int incl = wave_scan(c);
+    const uint64_t hit = __ballot(r >= incl - c && r < incl);
+    const int digit = hit ? __builtin_ctzll(hit) : 0;
+    r -= __builtin_amdgcn_readlane(incl - c, digit);
+    thr |= (uint32_t)digit << sh;
+    wave_lds_order();
   }
-  if (lane == 63) wsum[w] = v;
-  __syncthreads();
-  int base = 0;
-#pragma unroll
-  for (int i = 0; i < kTailThreads / 64; ++i)
-    if (i < w) base += wsum[i];
-  __syncthreads();
-  return base + v - x;
+  *rank = r;
+  return thr;
 }
 
+template <int H>
 __global__ __launch_bounds__(kTailThreads, 4) void split_tail_kernel(Ctx C, int parity0, int parity1) {
-  __shared__ int32_t ia[kTail], ib[kTail];
+  __shared__ int32_t idx[kTail];
   __shared__ uint32_t keys[kTail];
-  __shared__ int scan[kTail + 1];
-  __shared__ int hist[kMaxSub][256];
-  __shared__ int sub_start[2 * kMaxSub + 2], sub_size[2 * kMaxSub + 2];
-  __shared__ int sub_js[2 * kMaxSub + 2], sub_thr[2 * kMaxSub + 2], sub_rank[2 * kMaxSub + 2];
-  __shared__ int act_list[kMaxSub], act_of[2 * kMaxSub + 2];
-  __shared__ int wsum[kTailThreads / 64];
-  __shared__ int sh_nact;
+  __shared__ int hist[kTailBins];
+  __shared__ uint32_t cand[kTail];  // the ranks' bins' keys, kTail >> r for each sub-node
+  __shared__ float2 part[kTailWaves][64 * H];
+  __shared__ uint64_t mless[kTail / 64], meq[kTail / 64];
+  __shared__ int sub_js[kMaxSub], sub_rank[kMaxSub], sub_bin[kMaxSub], sub_n[kMaxSub];
+  __shared__ uint32_t sub_thr[kMaxSub];
+  __shared__ float sub_lo[kMaxSub], sub_scale[kMaxSub];
   const int pid = blockIdx.y, side = pid / C.BH, bh = pid % C.BH, node = blockIdx.x;
   const Side& S = C.s[side];
   if (node >= (1 << S.big)) return;
@@ -2800,209 +3012,270 @@ __global__ __launch_bounds__(kTailThreads, 4) void split_tail_kernel(Ctx C, int 
   const int par = side == 0 ? parity0 : parity1;
   const bool identity = S.big == 0;
   const int32_t* src = (par ? C.idx1 : C.idx0) + (size_t)pid * C.nmax;
-  for (int o = threadIdx.x; o < size; o += kTailThreads) ia[o] = identity ? start + o : src[start + o];
   const float* Y = S.y + (size_t)bh * S.n * C.d;
-  const int d = C.d, c = S.c;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int32_t* cur = ia;
-  int32_t* nxt = ib;
-  const int nsub_levels = S.levels - S.big;
-  for (int r = 0; r < nsub_levels; ++r) {
-    const int nslots = 1 << r;
-    __syncthreads();
-    if (threadIdx.x < 64) {
-      // Sub-node ranges at this level (relative to the node), one lane per
-      // slot (at most tail / c <= 64 slots), and the active list.
-      const int sl = threadIdx.x;
-      int st = 0, s = size;
-      if (sl < nslots) {
-        for (int b = r - 1; b >= 0; --b) {
-          const int bit = (sl >> b) & 1;
-          const int mL = s > c ? left_size(s, c) : s;
-          if (bit) {
-            st += mL;
-            s -= mL;
-          } else {
-            s = mL;
-          }
-        }
-      }
-      const bool act = sl < nslots && s > c;
-      const uint64_t am = __ballot(act);
-      if (sl < nslots) {
-        const int rank = (int)__popcll(am & ((1ull << sl) - 1ull));
-        sub_start[sl] = st;
-        sub_size[sl] = s;
-        act_of[sl] = act ? rank : -1;
-        if (act) act_list[rank] = sl;
-      }
-      if (sl == 0) {
-        sub_start[nslots] = size;
-        sh_nact = (int)__popcll(am);
+  const float* ycol = S.ycol ? S.ycol + (size_t)bh * kColCopy * S.n : nullptr;
+  const int d = C.d, c = S.c, lc = __builtin_ctz(c);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  auto left = [&](int s) { return (((s + c - 1) >> lc) >> 1) << lc; };  // left_size
+  // range of sub-node sl of level r
+  auto sub_range = [&](int r, int sl, int* st, int* sz) {
+    int a = 0, s = size;
+    for (int b = r - 1; b >= 0; --b) {
+      const int mL = s > c ? left(s) : s;
+      if ((sl >> b) & 1) {
+        a += mL;
+        s -= mL;
+      } else {
+        s = mL;
       }
     }
-    __syncthreads();
-    const int nact = sh_nact;
-    if (nact == 0) break;
-    // coordinate choice: one wavefront per active sub-node
-    for (int a = w; a < nact; a += kTailThreads / 64) {
-      const int sl = act_list[a];
-      const int js = choose_coordinate<64>(Y, d, cur, false, sub_start[sl], sub_size[sl], lane);
-      if (lane == 0) {
-        sub_js[sl] = js;
-        sub_thr[sl] = 0;
-        sub_rank[sl] = left_size(sub_size[sl], c) - 1;
-      }
-    }
-    __syncthreads();
-    // keys; slot of position o by binary search over the sub-node starts
-    {
-      constexpr int PT = kTail / kTailThreads;
-      int gsl[PT], grow[PT];
+    *st = a;
+    *sz = s;
+  };
+  int row[kTailPer], st[kTailPer], sz[kTailPer], sl[kTailPer];
+  uint32_t kv[kTailPer];
 #pragma unroll
-      for (int u = 0; u < PT; ++u) {
-        const int o = threadIdx.x + kTailThreads * u;
-        // The last slot starting at or before o is the non-empty slot holding
-        // o: empty slots start where the next non-empty slot starts.
-        int lo = 0, hi = nslots - 1;
-        while (lo < hi) {
-          const int mid = (lo + hi + 1) >> 1;
-          if (sub_start[mid] <= o)
-            lo = mid;
-          else
-            hi = mid - 1;
-        }
-        gsl[u] = lo;
-        grow[u] = o < size && act_of[lo] >= 0 ? cur[o] : -1;
-      }
-      // the chosen coordinate, from the coordinate-major copy when it holds
-      // it (the nodes of a head run together, so they share its lines)
-      float gv[PT];
-#pragma unroll
-      for (int u = 0; u < PT; ++u) {
-        gv[u] = 0.f;
-        if (grow[u] >= 0) {
-          const int js = sub_js[gsl[u]];
-          gv[u] = S.ycol && js < kColCopy ? S.ycol[((size_t)bh * kColCopy + js) * S.n + grow[u]]
-                                          : Y[(size_t)grow[u] * d + js];
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < PT; ++u) {
-        const int o = threadIdx.x + kTailThreads * u;
-        if (o < size) {
-          scan[o] = gsl[u];  // slot id (temporarily)
-          keys[o] = grow[u] >= 0 ? ordered_bits(gv[u]) : 0u;
-        }
-      }
-    }
-    // four 8-bit digit passes
-    for (int pass = 0; pass < 4; ++pass) {
-      const int shift = 24 - 8 * pass;
-      const int mshift = shift + 8;
-      __syncthreads();
-      for (int e = threadIdx.x; e < nact * 256; e += kTailThreads) hist[e / 256][e % 256] = 0;
-      __syncthreads();
-      for (int o = threadIdx.x; o < size; o += kTailThreads) {
-        const int sl = scan[o], a = act_of[sl];
-        if (a < 0) continue;
-        const uint32_t key = keys[o];
-        const uint32_t pre = (uint32_t)sub_thr[sl];
-        if (mshift == 32 || (key >> mshift) == (pre >> mshift))
-          atomicAdd(&hist[a][(key >> shift) & 255], 1);
-      }
-      __syncthreads();
-      for (int a = w; a < nact; a += kTailThreads / 64) {
-        const int sl = act_list[a];
-        const int rank = sub_rank[sl];
-        int cnt[4], sum = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          cnt[i] = hist[a][4 * lane + i];
-          sum += cnt[i];
-        }
-        int incl = sum;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const int y = __shfl_up(incl, o, 64);
-          if (lane >= o) incl += y;
-        }
-        const int before = incl - sum;
-        if (rank >= before && rank < incl) {
-          int acc = before;
-          for (int i = 0; i < 4; ++i) {
-            if (rank < acc + cnt[i]) {
-              sub_thr[sl] = (int)((uint32_t)sub_thr[sl] | ((uint32_t)(4 * lane + i) << shift));
-              sub_rank[sl] = rank - acc;
-              break;
-            }
-            acc += cnt[i];
-          }
-        }
-      }
-    }
-    __syncthreads();
-    // stable partition: scan of packed (less, equal) counts in position order
-    constexpr int per = kTail / kTailThreads;
-    const int o0 = threadIdx.x * per;
-    int less = 0, eq = 0;
-    for (int o = o0; o < o0 + per && o < size; ++o) {
-      const int sl = scan[o];
-      if (act_of[sl] < 0) continue;
-      const uint32_t thr = (uint32_t)sub_thr[sl];
-      less += keys[o] < thr;
-      eq += keys[o] == thr;
-    }
-    const int packed0 = scan_tail((less << 16) | eq, wsum);
-    // exclusive prefix at every position (packed), then per-sub-node offsets
-    int run = packed0;
-    int slots_local[per];
-    for (int u = 0; u < per; ++u) {
-      const int o = o0 + u;
-      if (o >= size) break;
-      const int sl = scan[o];
-      slots_local[u] = sl;
-      const uint32_t thr = (uint32_t)sub_thr[sl];
-      const bool act = act_of[sl] >= 0;
-      const int inc = act ? (((keys[o] < thr) ? 1 : 0) << 16) | ((keys[o] == thr) ? 1 : 0) : 0;
-      scan[o] = run;  // overwrite slot id by the exclusive prefix
-      run += inc;
-    }
-    __syncthreads();
-    int newpos[per];
-    for (int u = 0; u < per; ++u) {
-      const int o = o0 + u;
-      if (o >= size) break;
-      const int sl = slots_local[u];
-      const int st = sub_start[sl];
-      if (act_of[sl] < 0) {
-        newpos[u] = o;
-        continue;
-      }
-      const int base = scan[st];
-      const int rel = scan[o] - base;
-      const int lb = rel >> 16, eb = rel & 0xFFFF;
-      const uint32_t thr = (uint32_t)sub_thr[sl];
-      const int need_eq = sub_rank[sl] + 1;
-      const int mL = left_size(sub_size[sl], c);
-      const int Lo = lb + min(eb, need_eq);
-      const bool left = keys[o] < thr || (keys[o] == thr && eb < need_eq);
-      const int rel_dst = left ? Lo : mL + (o - st - Lo);
-      newpos[u] = (rel_dst >= 0 && rel_dst < sub_size[sl]) ? st + rel_dst : -1;
-    }
-    __syncthreads();
-    for (int u = 0; u < per; ++u) {
-      const int o = o0 + u;
-      if (o >= size) break;
-      if (newpos[u] >= 0) nxt[newpos[u]] = cur[o];
-    }
-    int32_t* t = cur;
-    cur = nxt;
-    nxt = t;
+  for (int u = 0; u < kTailPer; ++u) {
+    const int o = 256 * w + 64 * u + lane;
+    row[u] = o < size ? (identity ? start + o : src[start + o]) : 0;
+    st[u] = 0;
+    sz[u] = o < size ? size : 0;  // positions past the node take part in nothing
+    sl[u] = 0;
+    idx[o] = row[u];
+    hist[tid + kTailThreads * u] = 0;
   }
+  if (tid < kMaxSub) sub_n[tid] = 0;
   __syncthreads();
+  const int nclus = (size + c - 1) >> lc;
+  const int nlev = S.levels - S.big;
+  // a level splits nothing once every sub-node is one cluster (the right
+  // halves are the larger ones: ceil(nclus / 2^r) clusters)
+  for (int r = 0; r < nlev && ((nclus + (1 << r) - 1) >> r) >= 2; ++r) {
+    const int nsub = 1 << r;
+    const int nb = kTailBins >> r;       // bins per sub-node, 64 << lb of them
+    const int lb = 5 - r;                // bin b is counted at (b % 2^lb) * 64 + b / 2^lb:
+    const int cap = kTail >> r;          // the scan reads 64 of them side by side
+    // ---- choose
+    {
+      const int P = nsub < kTailWaves ? kTailWaves >> r : 1;  // wavefronts per sub-node
+      auto finish = [&](int s, int a, int z, int m, const Moments (&mo)[H]) {
+        float mean, var;
+        int js = choose_by_bounds<H>(mo, d, m, lane, &mean, &var);
+        if (js < 0) {
+          double dmean, dvar;
+          js = choose_coordinate<16>(Y, d, idx, false, a, z, lane, &dmean, &dvar);
+          mean = (float)dmean;
+          var = (float)dvar;
+        }
+        if (lane == 0) {
+          sub_js[s] = js;
+          bin_range(mean, var, nb, &sub_lo[s], &sub_scale[s]);
+        }
+      };
+      auto moments = [&](int a, int z, int m, int p, Moments (&mo)[H]) {
+        uint32_t off[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          off[h] = 4u * (uint32_t)d * (uint32_t)idx[a + sample_pos(min(lane + 64 * h, m - 1), z, m)];
+        if (m <= 16 * P)
+          sample_moments<H, 16>(Y, d, m, off, p, P, lane, mo);
+        else
+          sample_moments<H, 32>(Y, d, m, off, p, P, lane, mo);
+      };
+      if (P > 1) {
+        const int s = w / P, p = w % P;
+        int a, z;
+        sub_range(r, s, &a, &z);
+        const int m = min(z, d);
+        const bool act = z > c;
+        Moments mo[H];
+        if (act) {
+          moments(a, z, m, p, mo);
+#pragma unroll
+          for (int h = 0; h < H; ++h) part[w][lane + 64 * h] = make_float2(mo[h].S, mo[h].Q);
+        }
+        __syncthreads();
+        if (act && p == 0) {
+          for (int i = 1; i < P; ++i)
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+              const float2 x = part[w + i][lane + 64 * h];
+              mo[h].S += x.x;
+              mo[h].Q += x.y;
+            }
+          finish(s, a, z, m, mo);
+        }
+      } else {
+        for (int s = w; s < nsub; s += kTailWaves) {
+          int a, z;
+          sub_range(r, s, &a, &z);
+          if (z <= c) continue;
+          const int m = min(z, d);
+          Moments mo[H];
+          moments(a, z, m, 0, mo);
+          finish(s, a, z, m, mo);
+        }
+      }
+    }
+    __syncthreads();
+    // ---- keys and their bins
+    float v[kTailPer];
+#pragma unroll
+    for (int u = 0; u < kTailPer; ++u) {
+      v[u] = 0.f;
+      if (sz[u] > c) {
+        const int js = sub_js[sl[u]];
+        // the chosen coordinate, from the coordinate-major copy when it holds
+        // it (the nodes of a head run together, so they share its lines)
+        v[u] = ycol && js < kColCopy ? ycol[(size_t)js * S.n + row[u]] : Y[(size_t)row[u] * d + js];
+      }
+    }
+    int bin[kTailPer];
+#pragma unroll
+    for (int u = 0; u < kTailPer; ++u) {
+      kv[u] = ordered_bits(v[u]);
+      bin[u] = -1;
+      if (sz[u] > c) {
+        keys[256 * w + 64 * u + lane] = kv[u];
+        bin[u] = lin_bin(kv[u], sub_lo[sl[u]], sub_scale[sl[u]], nb);
+        atomicAdd(&hist[sl[u] * nb + ((bin[u] & ((1 << lb) - 1)) << 6) + (bin[u] >> lb)], 1);
+      }
+    }
+    __syncthreads();
+    // ---- select: the bin of the rank
+    for (int s = w; s < nsub; s += kTailWaves) {
+      int a, z;
+      sub_range(r, s, &a, &z);
+      if (z <= c) continue;
+      const int rank = left(z) - 1;
+      const int* hs = hist + s * nb;
+      int sum = 0;  // of the 2^lb bins lane * 2^lb ..
+      if (lb == 5) {
+#pragma unroll
+        for (int i = 0; i < 32; ++i) sum += hs[64 * i + lane];
+      } else {
+#pragma unroll 4
+        for (int i = 0; i < (1 << lb); ++i) sum += hs[64 * i + lane];
+      }
+      const int before = wave_scan(sum) - sum;
+      const uint64_t hl = __ballot(rank >= before && rank < before + sum);
+      const int l = hl ? __builtin_ctzll(hl) : 0;
+      const int cnt = lane < (1 << lb) ? hs[64 * lane + l] : 0;  // lane l's bins, one a lane
+      const int acc = wave_scan(cnt) - cnt + __builtin_amdgcn_readlane(before, l);
+      if (rank >= acc && rank < acc + cnt) {
+        sub_bin[s] = (l << lb) + lane;
+        sub_rank[s] = rank - acc;
+      }
+    }
+    __syncthreads();
+    // ---- that bin's keys
+#pragma unroll
+    for (int u = 0; u < kTailPer; ++u) {
+      if (bin[u] >= 0 && bin[u] == sub_bin[sl[u]]) {
+        const int i = atomicAdd(&sub_n[sl[u]], 1);
+        if (i < cap) cand[sl[u] * cap + i] = kv[u];
+      }
+    }
+    __syncthreads();
+    // ---- the rank-th of them
+    for (int s = w; s < nsub; s += kTailWaves) {
+      int a, z;
+      sub_range(r, s, &a, &z);
+      if (z <= c) continue;
+      const int n = __builtin_amdgcn_readfirstlane(sub_n[s]);
+      uint32_t thr;
+      int rank;
+      if (n <= 64) {
+        const int want = sub_rank[s];
+        const uint32_t key = lane < n ? cand[s * cap + lane] : 0xFFFFFFFFu;
+        int less = 0, eq = 0;
+#pragma unroll 4
+        for (int j = 0; j < n; ++j) {
+          const uint32_t kj = (uint32_t)__builtin_amdgcn_readlane((int)key, j);
+          less += kj < key;
+          eq += kj == key;
+        }
+        const uint64_t hit = __ballot(lane < n && want >= less && want < less + eq);
+        const int l = hit ? __builtin_ctzll(hit) : 0;
+        thr = (uint32_t)__builtin_amdgcn_readlane((int)key, l);
+        rank = want - __builtin_amdgcn_readlane(less, l);
+      } else {
+        const bool part_only = n <= cap;  // else more keys than the list holds: over all
+        rank = part_only ? sub_rank[s] : left(z) - 1;
+        thr = wave_radix_select(part_only ? cand + s * cap : keys + a, part_only ? n : z, &rank,
+                                reinterpret_cast<uint32_t*>(hist) + 64 * s, lane);
+      }
+      if (lane == 0) {
+        sub_thr[s] = thr;
+        sub_rank[s] = rank;
+        sub_n[s] = 0;
+      }
+    }
+    __syncthreads();
+    // ---- stable partition
+    uint64_t bl[kTailPer], be[kTailPer];
+#pragma unroll
+    for (int u = 0; u < kTailPer; ++u) {
+      const bool act = sz[u] > c;
+      const uint32_t thr = act ? sub_thr[sl[u]] : 0u;
+      hist[tid + kTailThreads * u] = 0;  // for the next level
+      bl[u] = __ballot(act && kv[u] < thr);
+      be[u] = __ballot(act && kv[u] == thr);
+      if (lane == 0) {
+        mless[4 * w + u] = bl[u];
+        meq[4 * w + u] = be[u];
+      }
+    }
+    __syncthreads();
+    {
+      // (below, equal) counts of the rows of 64 positions before row `lane`
+      int pre = 0;
+      if (lane < kTail / 64) pre = (__popcll(mless[lane]) << 16) | __popcll(meq[lane]);
+      pre = wave_scan(pre) - pre;
+#pragma unroll
+      for (int u = 0; u < kTailPer; ++u) {
+        const int o = 256 * w + 64 * u + lane;
+        int dst = o;
+        // the counts before the sub-node's first position
+        const int sr = st[u] >> 6;
+        const uint64_t low = (1ull << (st[u] & 63)) - 1ull;
+        int at0 = __shfl(pre, sr, 64);
+        at0 += (__popcll(mless[sr] & low) << 16) | __popcll(meq[sr] & low);
+        if (sz[u] > c) {
+          const uint64_t before = (1ull << lane) - 1ull;
+          const int at = __builtin_amdgcn_readlane(pre, 4 * w + u) +
+                         ((__popcll(bl[u] & before) << 16) | __popcll(be[u] & before));
+          const int rel = at - at0, lb = rel >> 16, eb = rel & 0xFFFF;
+          const uint32_t thr = sub_thr[sl[u]];
+          const int need_eq = sub_rank[sl[u]] + 1;
+          const int mL = left(sz[u]);
+          const int Lo = lb + min(eb, need_eq);
+          const bool goes = kv[u] < thr || (kv[u] == thr && eb < need_eq);
+          const int rd = goes ? Lo : mL + (o - st[u] - Lo);
+          dst = rd >= 0 && rd < sz[u] ? st[u] + rd : -1;
+        }
+        if (dst >= 0) idx[dst] = row[u];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kTailPer; ++u) {
+      const int o = 256 * w + 64 * u + lane;
+      row[u] = idx[o];
+      const int mL = sz[u] > c ? left(sz[u]) : sz[u];
+      const bool right = o - st[u] >= mL && sz[u] > c;
+      sl[u] = 2 * sl[u] + (right ? 1 : 0);
+      st[u] += right ? mL : 0;
+      sz[u] = right ? sz[u] - mL : mL;
+    }
+  }
   int32_t* perm = S.perm + (size_t)bh * S.n;
-  for (int o = threadIdx.x; o < size; o += kTailThreads) perm[start + o] = cur[o];
+#pragma unroll
+  for (int u = 0; u < kTailPer; ++u) {
+    const int o = 256 * w + 64 * u + lane;
+    if (o < size) perm[start + o] = row[u];
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -3414,7 +3687,8 @@ hipError_t launch_cluster(const Prob& P, const void* q, const void* k, const voi
                            blds, st, C, L);
     }
     else
-      hipLaunchKernelGGL(split_choose_kernel, dim3(1 << l, 2 * BH), dim3(64), 0, st, C, L);
+      hipLaunchKernelGGL((d <= 64 ? split_choose_kernel<1> : split_choose_kernel<2>),
+                         dim3(1 << l, 2 * BH), dim3(64 * kChooseWaves), 0, st, C, L);
     CA_CHECK();
     const dim3 kgrid(cpn, 1 << l, 2 * BH);
     if (!basic)
@@ -3438,8 +3712,8 @@ hipError_t launch_cluster(const Prob& P, const void* q, const void* k, const voi
       hipLaunchKernelGGL(copy_order_kernel, dim3((C.nmax + 255) / 256 < 1024 ? (C.nmax + 255) / 256 : 1024, 2 * BH),
                          dim3(256), 0, st, C, W.big_q & 1, W.big_k & 1);
     else
-      hipLaunchKernelGGL(split_tail_kernel, dim3(nodes, 2 * BH), dim3(kTailThreads), 0, st, C,
-                         W.big_q & 1, W.big_k & 1);
+      hipLaunchKernelGGL((d <= 64 ? split_tail_kernel<1> : split_tail_kernel<2>), dim3(nodes, 2 * BH),
+                         dim3(kTailThreads), 0, st, C, W.big_q & 1, W.big_k & 1);
     CA_CHECK();
   }
   {

@@ -71,3 +71,16 @@ def test_f32_four_byte_alignment():
         got.append((op, lse, out))
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+# The in-workgroup levels of the split: nodes at the tail size and one token to
+# each side, nodes of one wavefront's positions, clusters of one token (six
+# levels, 32 sub-nodes), clusters larger than a row of 64 positions, and bf16
+# coordinates as they are (runs of equal keys at every threshold).
+@pytest.mark.parametrize("dt,n,d,c,xf", [
+    ("bf16", 2048, 64, 64, "none"), ("bf16", 2049, 64, 32, "none"), ("bf16", 2047, 128, 16, "none"),
+    ("f32", 63, 8, 1, "none"), ("f32", 65, 3, 1, "none"), ("bf16", 4097, 128, 128, "metric"),
+    ("bf16", 1500, 64, 256, "pca"), ("f32", 700, 100, 2, "none"),
+])
+def test_split_tail_edges(dt, n, d, c, xf):
+    _cluster_parity(dt, n, d, c, xf)
