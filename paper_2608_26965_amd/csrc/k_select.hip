@@ -10,7 +10,7 @@
 // decision of its own, so given the scores the lists are exact.
 #include <algorithm>
 
-#include "common.h"
+#include "f32_tile.h"
 
 namespace ca {
 
@@ -241,18 +241,26 @@ constexpr int kTopBins = 2048;  // linear bins of the top-k pre-pass
 // key of a lower bin precedes it); the radix select then only counts that
 // bin's keys, which keeps the LDS atomics of long rows from piling onto the
 // few digits a narrow score range has in common. Rows longer than 8192
-// scores take this kernel; shorter ones the wave and block kernels below.
-__global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ S, int nkc, int k,
-                                                   int32_t* __restrict__ lists) {
-  __shared__ int hist[256];
-  __shared__ int bins[kTopBins];
-  __shared__ int sh_warp[4];
-  __shared__ float sh_f[4];
-  __shared__ uint32_t sh_prefix;
-  __shared__ int sh_rank, sh_bin;
-  const size_t row = blockIdx.x;
+// scores take it, and the rows that the filter kernel below gives up on;
+// shorter rows the wave, block and filter kernels.
+struct TopkAny {
+  int hist[256];
+  int bins[kTopBins];
+  int warp[4];
+  float f[4];
+  uint32_t prefix;
+  int rank, bin;
+};
+__device__ void topk_any(const float* __restrict__ s, int nkc, int k, int32_t* __restrict__ out,
+                         TopkAny& sh) {
+  int* hist = sh.hist;
+  int* bins = sh.bins;
+  int* sh_warp = sh.warp;
+  float* sh_f = sh.f;
+  uint32_t& sh_prefix = sh.prefix;
+  int& sh_rank = sh.rank;
+  int& sh_bin = sh.bin;
   const int tid = threadIdx.x;
-  const float* s = S + row * nkc;
 
   float lo = INFINITY, hi = -INFINITY;
   for (int b = tid; b < nkc; b += 256) {
@@ -364,7 +372,6 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ S, 
     }
   }
   const int sel_before = block_scan_256(sel, sh_warp, &tot);
-  int32_t* out = lists + row * k;
   int pos = sel_before;
   er = eq_before;
   for (int b = b_lo; b < b_hi; ++b) {
@@ -378,6 +385,12 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ S, 
     }
     if (take && pos < k) out[pos++] = b;
   }
+}
+
+__global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ S, int nkc, int k,
+                                                   int32_t* __restrict__ lists) {
+  __shared__ TopkAny sh;
+  topk_any(S + (size_t)blockIdx.x * nkc, nkc, k, lists + (size_t)blockIdx.x * k, sh);
 }
 
 // Exact top-k of rows of at most 64 * VPL scores, one row per wavefront, the
@@ -404,6 +417,21 @@ __device__ __forceinline__ int common_bytes(uint32_t kmin, uint32_t kmax, uint32
   const int n = x == 0u ? 4 : __builtin_clz(x) / 8;
   *prefix = n == 0 ? 0u : (n == 4 ? kmin : kmin & (0xFFFFFFFFu << (32 - 8 * n)));
   return n;
+}
+
+// Scores p0 .. p0 + 3 of a row of n, -inf past its end. Rows need no alignment
+// beyond their own 4 bytes.
+__device__ __forceinline__ void load_scores4(const float* __restrict__ s, int p0, int n, float* v) {
+  f32x4 x = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+  if (p0 + 3 < n) {
+    x = load4u(s + p0);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+      if (p0 + e < n) x[e] = s[p0 + e];
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = x[e];
 }
 
 __device__ __forceinline__ int wave_incl_scan(int x, int lane) {
@@ -468,8 +496,16 @@ __global__ __launch_bounds__(256) void topk_wave_kernel(const float* __restrict_
   };
   for (int i = lane; i < kWaveBins; i += 64) bins[i] = 0;
   wave_lds_sync();
+  // (not the positions past the row: a row of 1,182 scores would pile 866
+  // atomics onto the last bin: 98 us for 16,384 rows against 73 without)
+  if (nkc == 64 * VPL) {
 #pragma unroll
-  for (int j = 0; j < VPL; ++j) atomicAdd(&bins[bin_of(v[j])], 1);
+    for (int j = 0; j < VPL; ++j) atomicAdd(&bins[bin_of(v[j])], 1);
+  } else {
+#pragma unroll
+    for (int j = 0; j < VPL; ++j)
+      if (b0 + j < nkc) atomicAdd(&bins[bin_of(v[j])], 1);
+  }
   wave_lds_sync();
   // Each pass recomputes bins and keys from the scores: keeping them from an
   // earlier pass would hold two more registers per score.
@@ -677,8 +713,15 @@ __global__ __launch_bounds__(64 * NWV, 4) void topk_block_kernel(const float* __
     const float t = (hi - x) * inv;  // 0 for the largest score
     return t < (float)kWaveBins ? (t > 0.f ? (int)t : 0) : kWaveBins - 1;
   };
+  // (not the positions past the row: they would pile onto the last bin)
+  if (nkc == 64 * VPL * NWV) {
 #pragma unroll
-  for (int j = 0; j < VPL; ++j) atomicAdd(&bins[bin_of(v[j])], 1);
+    for (int j = 0; j < VPL; ++j) atomicAdd(&bins[bin_of(v[j])], 1);
+  } else {
+#pragma unroll
+    for (int j = 0; j < VPL; ++j)
+      if (pos_of(j >> 2, j & 3) < nkc) atomicAdd(&bins[bin_of(v[j])], 1);
+  }
   __syncthreads();
   // the bin holding rank k - 1 (every wavefront finds the same)
   int B, rank;
@@ -854,6 +897,245 @@ __global__ __launch_bounds__(64 * NWV, 4) void topk_block_kernel(const float* __
     }
   };
   walk(lists + row * k);
+}
+
+// Exact top-k of a row that is longer than k, one row per block of four
+// wavefronts (positions as in topk_block_kernel), in two steps.
+//  1. A bound: the row is cut into 256 NG groups of VPL / NG scores (of one
+//     lane, from different float4s, so that a run of large scores falls into
+//     many groups), and the k-th largest group maximum is at most the k-th
+//     largest score. So is the lower edge of its linear bin over the maxima's
+//     range, and the scores above that edge (t < bound) hold the k largest:
+//     typically 1.1 to 2 k of them, which go to a list.
+//  2. The k-th largest of the listed scores: linear bins again, over the listed
+//     range, then a count among the at most 64 scores of its bin. Bitmaps over
+//     the row's positions put the selected ones in index order.
+// Rows with too few or too many listed scores, or more than 64 in the last bin
+// (ties, infinities, a narrow cluster of scores), take topk_any.
+//
+// What bounds it: reading the row. The block kernel counts every score into LDS
+// bins, recomputes bins and keys in each later pass and writes its list by a
+// scan of every float4 group; here a score costs a maximum, a multiply-add and
+// two comparisons. 16,384 rows of 8,192, k = 64: 274 -> 115 us
+// (4.7 TB/s); k = 819: 273 -> 168; rows of 5,000, k = 312: 399 -> 142.
+constexpr int kFiltCand = 2048;  // listed scores
+
+template <int VPL, int NG>
+__global__ __launch_bounds__(256, 4) void topk_filter_kernel(const float* __restrict__ S, int nkc,
+                                                             int k, int32_t* __restrict__ lists) {
+  constexpr int G = VPL / 4, WORDS = 256 * VPL / 32;
+  static_assert(NG <= 8 && G % (NG > 4 ? 2 : 1) == 0, "groups");
+  struct Filter {
+    int bins[2][kWaveBins];
+    float val[kFiltCand];
+    uint16_t at[kFiltCand];
+    uint32_t lt[WORDS], eq[WORDS];
+    uint32_t last[64];
+    float lo[4], hi[4];
+    int groups[4], scan[4];
+    int nlist, nlast;
+  };
+  __shared__ union {
+    Filter f;
+    TopkAny any;
+  } sh;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, tid = threadIdx.x;
+  const size_t row = blockIdx.x;
+  const float* s = S + row * nkc;
+  int32_t* out = lists + row * k;
+  const int wbase = 64 * VPL * w;
+  auto pos_of = [&](int g, int e) { return wbase + 256 * g + 4 * lane + e; };
+  // group of a lane's score: by element, and for NG = 8 also by float4 parity
+  auto group_of = [](int g, int e) { return NG > 4 ? 4 * (g & 1) + e : e % NG; };
+  float v[VPL];
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    load_scores4(s, pos_of(g, 0), nkc, &v[4 * g]);
+  }
+  for (int i = tid; i < 2 * kWaveBins; i += 256) (&sh.f.bins[0][0])[i] = 0;
+  for (int i = tid; i < WORDS; i += 256) sh.f.lt[i] = sh.f.eq[i] = 0u;
+  if (tid == 0) sh.f.nlist = sh.f.nlast = 0;
+  // group maxima, and the range of those of groups that hold a score
+  float gm[NG], lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+  for (int q = 0; q < NG; ++q) gm[q] = -INFINITY;
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int q = group_of(g, e);
+      gm[q] = fmaxf(gm[q], v[4 * g + e]);
+    }
+  int nreal = 0;  // groups 0 .. nreal - 1 hold a score
+#pragma unroll
+  for (int q = 0; q < NG; ++q)
+    if (pos_of(q >> 2, q & 3) < nkc) {
+      lo = fminf(lo, gm[q]);
+      hi = fmaxf(hi, gm[q]);
+      nreal = q + 1;
+    }
+  int real = nreal;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    lo = fminf(lo, __shfl_xor(lo, o, 64));
+    hi = fmaxf(hi, __shfl_xor(hi, o, 64));
+    real += __shfl_xor(real, o, 64);
+  }
+  if (lane == 0) {
+    sh.f.lo[w] = lo;
+    sh.f.hi[w] = hi;
+    sh.f.groups[w] = real;
+  }
+  __syncthreads();
+  real = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    lo = fminf(lo, sh.f.lo[i]);
+    hi = fmaxf(hi, sh.f.hi[i]);
+    real += sh.f.groups[i];
+  }
+  const float inv0 = (float)kWaveBins / (hi - lo);
+  const float inv = hi > lo && inv0 < INFINITY ? inv0 : 0.f;  // too narrow: one bin
+  auto bin_at = [](float t) {
+    return t < (float)kWaveBins ? (t > 0.f ? (int)t : 0) : kWaveBins - 1;
+  };
+#pragma unroll
+  for (int q = 0; q < NG; ++q)
+    if (q < nreal) atomicAdd(&sh.f.bins[0][bin_at((hi - gm[q]) * inv)], 1);
+  __syncthreads();
+  // the bin of rank r (descending) in a histogram, and the rank inside it;
+  // every wavefront finds the same
+  auto find_bin = [&](const int* bins, int r, int* rank) {
+    constexpr int PB = kWaveBins / 64;
+    int c[PB], sum = 0;
+#pragma unroll
+    for (int i = 0; i < PB; i += 4) {
+      const int4 x = *(const int4*)&bins[PB * lane + i];
+      c[i] = x.x;
+      c[i + 1] = x.y;
+      c[i + 2] = x.z;
+      c[i + 3] = x.w;
+    }
+#pragma unroll
+    for (int i = 0; i < PB; ++i) sum += c[i];
+    const int incl = wave_incl_scan(sum, lane);
+    const uint64_t own = __ballot(r >= incl - sum && r < incl);
+    const int l = own ? __builtin_ctzll(own) : 63;
+    int acc = incl - sum, b = 0, rb = 0;
+#pragma unroll
+    for (int i = 0; i < PB; ++i) {
+      if (r >= acc && r < acc + c[i]) {
+        b = PB * lane + i;
+        rb = r - acc;
+      }
+      acc += c[i];
+    }
+    *rank = __builtin_amdgcn_readlane(rb, l);
+    return __builtin_amdgcn_readlane(b, l);
+  };
+  int rank;
+  const int B = find_bin(sh.f.bins[0], k - 1, &rank);
+  const float bound = B == kWaveBins - 1 ? INFINITY : (float)(B + 1);
+  // the scores above the bound (positions past the row hold -inf: their t is
+  // infinite or NaN, never listed): counted, then listed from the wavefront's
+  // place
+  auto listed = [&](int j) { return (hi - v[j]) * inv < bound; };
+  int n = 0;
+#pragma unroll
+  for (int j = 0; j < VPL; ++j) n += (int)__popcll(__ballot(listed(j)));
+  int base = 0;
+  if (lane == 0 && n > 0) base = atomicAdd(&sh.f.nlist, n);
+  base = __builtin_amdgcn_readfirstlane(base);
+  const uint64_t below = (1ull << lane) - 1ull;
+  if (n > 0 && base + n <= kFiltCand) {
+    int p = base;
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) {
+      const bool hit = listed(j);
+      const uint64_t m = __ballot(hit);
+      if (m == 0ull) continue;  // uniform
+      if (hit) {
+        const int i = p + (int)__popcll(m & below);
+        sh.f.val[i] = v[j];
+        sh.f.at[i] = (uint16_t)pos_of(j >> 2, j & 3);
+      }
+      p += (int)__popcll(m);
+    }
+  }
+  __syncthreads();
+  const int total = sh.f.nlist;
+  bool over = real < k || total < k || total > kFiltCand;
+  uint32_t thr = 0u;
+  int need_eq = 0;
+  if (!over) {
+    const float inv2 = bound == INFINITY ? 1.f : (float)kWaveBins / bound;
+    auto bin2_of = [&](float x) { return bin_at((hi - x) * inv * inv2); };
+    for (int i = tid; i < total; i += 256) atomicAdd(&sh.f.bins[1][bin2_of(sh.f.val[i])], 1);
+    __syncthreads();
+    const int B2 = find_bin(sh.f.bins[1], k - 1, &rank);
+    for (int i = tid; i < total; i += 256) {
+      const float x = sh.f.val[i];
+      if (bin2_of(x) == B2) {
+        const int j = atomicAdd(&sh.f.nlast, 1);
+        if (j < 64) sh.f.last[j] = desc_key(x);
+      }
+    }
+    __syncthreads();
+    const int nl = __builtin_amdgcn_readfirstlane(sh.f.nlast);
+    over = nl > 64;
+    if (!over) {
+      const uint32_t key = lane < nl ? sh.f.last[lane] : 0xFFFFFFFFu;
+      int less = 0, eq = 0;
+      for (int j = 0; j < nl; ++j) {
+        const uint32_t kj = (uint32_t)__builtin_amdgcn_readlane((int)key, j);
+        less += kj < key;
+        eq += kj == key;
+      }
+      const uint64_t own = __ballot(lane < nl && rank >= less && rank < less + eq);
+      const int l = own ? __builtin_ctzll(own) : 0;
+      thr = (uint32_t)__builtin_amdgcn_readlane((int)key, l);
+      need_eq = rank - __builtin_amdgcn_readlane(less, l) + 1;
+    }
+  }
+  if (over) {  // the same decision in every wavefront
+    __syncthreads();  // the filter's arrays are done with
+    topk_any(s, nkc, k, out, sh.any);
+    return;
+  }
+  // positions of the keys below the threshold (taken) and equal to it (the
+  // first need_eq taken), in index order
+  for (int i = tid; i < total; i += 256) {
+    const uint32_t u = desc_key(sh.f.val[i]);
+    if (u <= thr) {
+      const int p = sh.f.at[i];
+      atomicOr(u < thr ? &sh.f.lt[p >> 5] : &sh.f.eq[p >> 5], 1u << (p & 31));
+    }
+  }
+  __syncthreads();
+  uint32_t take = 0u, equal = 0u;
+  if (tid < WORDS) {
+    take = sh.f.lt[tid];
+    equal = sh.f.eq[tid];
+  }
+  // (equal, below) counts of the words before this one
+  const int cnt = ((int)__popc(equal) << 16) | (int)__popc(take);
+  const int incl = wave_incl_scan(cnt, lane);
+  if (lane == 63) sh.f.scan[w] = incl;
+  __syncthreads();
+  int pre = incl - cnt;
+  for (int i = 0; i < w; ++i) pre += sh.f.scan[i];
+  const int eb = pre >> 16;
+  int p = (pre & 0xFFFF) + min(eb, need_eq);
+  for (int i = eb; i < need_eq && equal != 0u; ++i) {  // the lowest of the word's equal ones
+    take |= equal & (0u - equal);
+    equal &= equal - 1u;
+  }
+  while (take != 0u) {
+    const int bit = __builtin_ctz(take);
+    take &= take - 1u;
+    if (p < k) out[p] = 32 * tid + bit;
+    ++p;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1058,7 +1340,24 @@ hipError_t launch_select(const Prob& P, const float* cq, const float* ck, const 
     CA_TOPK_WAVE(32)
 #undef CA_TOPK_WAVE
     // wider rows: one row per block of four wavefronts (more rows in flight
-    // than with a whole row in one wavefront's registers)
+    // than with a whole row in one wavefront's registers); by the filter where
+    // the row makes at least 2 k groups (with fewer, the bound lets most of the
+    // row through; just past the line, k = 1,024 of 8,192, 177 against 279 us)
+#define CA_TOPK_FILTER(V, NG)                                                                  \
+  if (P.nkc <= 256 * V && (int64_t)P.nkc * NG >= (int64_t)2 * k * V) {                         \
+    hipLaunchKernelGGL((topk_filter_kernel<V, NG>), dim3((unsigned)nrows), dim3(256), 0, st, S, \
+                       P.nkc, k, lists);                                                       \
+    return hipGetLastError();                                                                  \
+  }
+    CA_TOPK_FILTER(16, 1)
+    CA_TOPK_FILTER(16, 2)
+    CA_TOPK_FILTER(16, 4)
+    CA_TOPK_FILTER(16, 8)
+    CA_TOPK_FILTER(32, 1)
+    CA_TOPK_FILTER(32, 2)
+    CA_TOPK_FILTER(32, 4)
+    CA_TOPK_FILTER(32, 8)
+#undef CA_TOPK_FILTER
 #define CA_TOPK_BLOCK(V)                                                                      \
   if (P.nkc <= 256 * V) {                                                                     \
     hipLaunchKernelGGL((topk_block_kernel<V, 4>), dim3((unsigned)nrows), dim3(256), 0, st, S, \

@@ -84,3 +84,32 @@ def test_f32_four_byte_alignment():
 ])
 def test_split_tail_edges(dt, n, d, c, xf):
     _cluster_parity(dt, n, d, c, xf)
+
+
+# Top-k of rows of 2049-8192 scores: at the edges of the number of groups the
+# filter makes (256 to 2048, at least twice k of them), rows that leave part of
+# a wavefront's range empty, and the inputs it hands over (ties, runs of equal
+# scores at the threshold, infinities, scores that crowd under one outlier, long
+# runs of the largest scores).
+@pytest.mark.parametrize("nkc,k", [(2049, 64), (2049, 513), (4095, 128), (4096, 129), (4097, 1),
+                                   (8192, 128), (8192, 129), (8191, 1023), (8192, 1025)])
+@pytest.mark.parametrize("kind", ["normal", "ties", "inf", "outlier", "run"])
+def test_topk_filter_edges(nkc, k, kind):
+    import numpy as np
+    import torch
+    import paper_2608_26965_amd as ca
+    from oracle import ref
+    rng = np.random.default_rng([nkc, k])
+    S = rng.standard_normal((6, nkc)).astype(np.float32)
+    if kind == "ties":
+        S = np.round(2 * S)
+    elif kind == "inf":
+        S[:, ::7], S[:, 3::1000] = -np.inf, np.inf
+    elif kind == "outlier":
+        S = S * 1e-5
+        S[:, nkc // 2] = 1e20
+    elif kind == "run":
+        S[:, nkc // 3:nkc // 3 + min(k + 3, nkc // 2)] += 20
+    p = ca.Problem(1, 1, 6 * 64, nkc * 64, 64, 64, 64, torch.float32)
+    got, _ = ca.select(p, None, None, k, scores_in=torch.from_numpy(S[None]).cuda())
+    assert np.array_equal(got.cpu().numpy()[0], ref.topk(S.astype(np.float64), k))
