@@ -357,13 +357,21 @@ __device__ __forceinline__ double recip64(double x) {
 // sign changes of the sequence 1, p_s, ..., p_{t-1} of leading minors of
 // T - x I (a zero minor counts as a change).
 __device__ __forceinline__ int sturm_below(const double2* tq, int s, int t, double x) {
-  // A minor that is exactly zero counts as positive: the next one then has
-  // the opposite sign of the one before, so the pair adds exactly one change.
+  // The minors' sign bits are shifted into a word and the changes counted
+  // eight at a time: four instructions a step, and with one wavefront a SIMD
+  // the instructions are what a step costs (comparing and adding per step took
+  // 75,000 cycles for the 17 rounds at d = 64, now 55,000). A minor that is
+  // exactly zero is +0, so it counts as positive: the next one then has the
+  // opposite sign of the one before, and the pair adds exactly one change.
   // The next eight entries are read while the current eight are used; the
-  // last, partial eight run on past the block (tq holds eight more finite
+  // last, partial eight run on past the block (tq holds nine more finite
   // entries) with their changes not counted.
+  auto sign_in = [](uint32_t bits, double p) {
+    return __builtin_amdgcn_alignbit(bits, (uint32_t)((uint64_t)__double_as_longlong(p) >> 32), 31);
+  };
   double p2 = 1.0, p1 = tq[s].x - x;
-  int cnt = p1 < 0.0;
+  uint32_t bits = sign_in(0u, p1);  // (the sequence starts with 1: positive)
+  int cnt = (int)bits;
   double2 q[8];
 #pragma unroll
   for (int u = 0; u < 8; ++u) q[u] = tq[s + 1 + u];
@@ -375,10 +383,11 @@ __device__ __forceinline__ int sturm_below(const double2* tq, int s, int t, doub
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const double p = (q[u].x - x) * p1 - q[u].y * p2;
-      cnt += (p < 0.0) != (p1 < 0.0);
+      bits = sign_in(bits, p);
       p2 = p1;
       p1 = p;
     }
+    cnt += (int)__popc((bits ^ (bits >> 1)) & 0xFFu);
     int ex;
     (void)frexp(fmax(fabs(p1), fabs(p2)), &ex);
     p1 = ldexp(p1, -ex);
@@ -389,10 +398,12 @@ __device__ __forceinline__ int sturm_below(const double2* tq, int s, int t, doub
 #pragma unroll
   for (int u = 0; u < 7; ++u) {
     const double p = (q[u].x - x) * p1 - q[u].y * p2;
-    cnt += ((p < 0.0) != (p1 < 0.0)) & (i0 + u < t);
+    bits = sign_in(bits, p);
     p2 = p1;
     p1 = p;
   }
+  const int over = 7 - max(t - i0, 0);  // steps past the block
+  cnt += (int)__popc(((bits ^ (bits >> 1)) & 0x7Fu) >> over);
   return cnt;
 }
 
@@ -606,14 +617,16 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
   // live rows of a step are spread over all wavefronts) and split their float4
   // column groups (c16, c16 + 16, ...). LDS passes only the vectors (v, p, the
   // next column), so a step is one chain: column -> norm (fp64) -> v -> p.
-  // Entries of v and p outside the live block are zero, so the pass needs no
-  // masks: dead entries are updated by zeros.
-  // What bounds it: that chain's latency with one wavefront a SIMD (about 2,000
-  // cycles a step). With the matrix in LDS, masks
-  // per entry and two more waits a step it was about 2,400: the whole kernel
-  // took 152 us for 16 problems at d = 64 and 423 us for 80 at d = 128, now 133
-  // and 387 us (with the second inverse-iteration step reusing the first one's
-  // factorisation, and every global read issued ahead of its use).
+  // Entries of v outside the live block are zero, so the pass needs no masks:
+  // dead entries take part with zeros (or change without being read again), and
+  // a block of rows that is dead as a whole is left out.
+  // What bounds it: that chain with one wavefront a SIMD, where every
+  // instruction counts (about 8 cycles each; 1,800 cycles a step at d = 64). With
+  // the matrix in LDS, masks per entry and two more waits a step it was 2,400.
+  // The whole kernel took 152 us for 16 problems at d = 64 and 423 us for 80 at
+  // d = 128; now 118 and 344 us (with the second inverse-iteration step reusing
+  // the first one's factorisation, and every global read issued ahead of its
+  // use).
   const int nref = d > 2 ? d - 2 : 0;
   {
     constexpr int RPT = 4;               // rows per lane
@@ -638,8 +651,9 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
     if (tid < NW) kpart[1][tid] = 0.f;
     __syncthreads();  // A is read: its rows take the reflectors from here
     float vr[RPT] = {0.f, 0.f, 0.f, 0.f}, pr[RPT] = {0.f, 0.f, 0.f, 0.f};  // v and p at own rows
-    for (int k = 0; k < nref; ++k) {
+    auto step = [&](auto r0_tag, int k) __attribute__((always_inline)) {
 #pragma clang fp contract(off)
+      constexpr int R0 = decltype(r0_tag)::value;  // row blocks below R0 are done with
       const int cur = k & 1, prv = cur ^ 1;
       float* vcur = vvs[cur][wv];
       const float* vprv = vvs[prv][wv];
@@ -674,7 +688,7 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
         const float wpv[4] = {__builtin_fmaf(-Kp, vp.x, pp.x), __builtin_fmaf(-Kp, vp.y, pp.y),
                               __builtin_fmaf(-Kp, vp.z, pp.z), __builtin_fmaf(-Kp, vp.w, pp.w)};
 #pragma unroll
-        for (int r = 0; r < RPT; ++r) {
+        for (int r = R0; r < RPT; ++r) {
           const float wr = __builtin_fmaf(-Kp, vr[r], pr[r]);
 #pragma unroll
           for (int e = 0; e < 4; ++e)
@@ -682,7 +696,7 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
         }
         if ((kn >> 2) == c16 + 16 * q)
 #pragma unroll
-          for (int r = 0; r < RPT; ++r)
+          for (int r = R0; r < RPT; ++r)
             colb[cur][rs + r * (DM / RPT)] =
                 make_float4(ar[q][r][0], ar[q][r][1], ar[q][r][2], ar[q][r][3]);
       }
@@ -712,7 +726,7 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
       // p = A v over the rows
       float acc[RPT];
 #pragma unroll
-      for (int r = 0; r < RPT; ++r) {
+      for (int r = R0; r < RPT; ++r) {
         vr[r] = vcur[rs + r * (DM / RPT)];
         acc[r] = 0.f;
       }
@@ -723,25 +737,25 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
-          for (int r = 0; r < RPT; ++r) acc[r] = acc[r] + ar[q][r][e] * vnv[e];
+          for (int r = R0; r < RPT; ++r) acc[r] = acc[r] + ar[q][r][e] * vnv[e];
       }
       // row sums over the 16 lanes of the DPP row (every lane gets them)
 #pragma unroll
-      for (int r = 0; r < RPT; ++r) acc[r] = quad_sum(acc[r]);
+      for (int r = R0; r < RPT; ++r) acc[r] = quad_sum(acc[r]);
 #pragma unroll
-      for (int r = 0; r < RPT; ++r) acc[r] = dpp_add<0x141>(acc[r]);  // row_half_mirror
+      for (int r = R0; r < RPT; ++r) acc[r] = dpp_add<0x141>(acc[r]);  // row_half_mirror
 #pragma unroll
-      for (int r = 0; r < RPT; ++r) acc[r] = dpp_add<0x140>(acc[r]);  // row_mirror
+      for (int r = R0; r < RPT; ++r) acc[r] = dpp_add<0x140>(acc[r]);  // row_mirror
       float vp_part = 0.f;
 #pragma unroll
-      for (int r = 0; r < RPT; ++r) {
+      for (int r = R0; r < RPT; ++r) {
         const int row = rs + r * (DM / RPT);
         pr[r] = row > k && row < d ? acc[r] : 0.f;
         vp_part = vp_part + vr[r] * pr[r];
       }
       if (c16 == 0)
 #pragma unroll
-        for (int r = 0; r < RPT; ++r) pbuf[cur][rs + r * (DM / RPT)] = pr[r];
+        for (int r = R0; r < RPT; ++r) pbuf[cur][rs + r * (DM / RPT)] = pr[r];
       vp_part = dpp_add<0x142, 0xA>(vp_part);  // row_bcast15 into rows 1, 3
       vp_part = dpp_add<0x143, 0xC>(vp_part);  // row_bcast31 into rows 2, 3: lane 63 holds the sum
       if (lane == 63) kpart[cur][wv] = vp_part;
@@ -754,7 +768,19 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
         }
       }
       __syncthreads();
-    }
+    };
+    // rows rs + r DM/4 of block r are all at or above the diagonal once k
+    // reaches (r + 1) DM/4 - 1
+    auto upto = [&](auto r0_tag, int k0) __attribute__((always_inline)) {
+      constexpr int R0 = decltype(r0_tag)::value;
+      int k = k0;
+      for (; k < min(nref, (R0 + 1) * (DM / RPT) - 1); ++k) step(r0_tag, k);
+      return k;
+    };
+    int kh = upto(std::integral_constant<int, 0>{}, 0);
+    kh = upto(std::integral_constant<int, 1>{}, kh);
+    kh = upto(std::integral_constant<int, 2>{}, kh);
+    for (; kh < nref; ++kh) step(std::integral_constant<int, 3>{}, kh);
     // the last 2 x 2 block after the last reflector
     if (d >= 2) {
 #pragma unroll
