@@ -96,37 +96,51 @@ __global__ __launch_bounds__(256) void comp_stage_kernel(const float* __restrict
   }
 }
 
-// Centroids per LDS stage: a whole tile of 128 at d = 64; half a tile at
-// d = 128, so that two stages and the mask take 74 KB instead of 140 KB and
-// two workgroups share a CU.
-template <int D>
-constexpr int comp_stage_cents() {
-  return D == 128 ? kCompTile / 2 : kCompTile;
+// Centroids per LDS stage: half a tile, so that two stages and the masks take
+// 42 KB at d = 64 and 75 KB at d = 128: three and two workgroups a CU. (Whole
+// tiles at d = 64 took 75 KB.)
+constexpr int kCompStage = kCompTile / 2;
+
+// Query clusters per workgroup. All query clusters of a head stream the same
+// centroid tiles and differ only in the selection mask, so clusters of 64 share
+// a workgroup of four wavefronts two by two, with a mask and a bias row each.
+// What bounds the kernel is the latency of a stage (copy, logits, softmax,
+// value product, three barriers), hence the wavefronts in flight: with a
+// workgroup of two wavefronts per cluster of 64 and whole-tile stages a SIMD
+// held one; now three at d = 64 and two at d = 128. 8 heads, 131,072 tokens,
+// clusters of 64 x 128, k = 64 of 1,024: 695 -> 439 us
+// (query clusters of 128, one a workgroup: 466 -> 403); 40 heads, 20,000
+// tokens, d = 128, clusters of 64, k = 40 of 313: 418 -> 283.
+template <int CQ>
+constexpr int comp_clusters() {
+  return CQ == 64 ? 2 : 1;
 }
 
 // Waves per SIMD (the second launch bound): as many workgroups as the LDS
-// (two stages and the selection mask) allows, capped at two waves per SIMD.
-template <int D, int CQ>
+// (two stages and the selection masks) allows, capped at three waves per SIMD.
+template <int D, int CQ, int NQ>
 constexpr int comp_waves_per_simd() {
-  constexpr int lds = 2 * (comp_stage_cents<D>() * (4 * D + 4)) + kMaskWords * 4;
+  constexpr int nw = NQ * CQ / 32;
+  constexpr int lds = 2 * kCompStage * (4 * D + 4 + 4 * NQ) + kMaskWords * 4;
   constexpr int by_lds = (160 * 1024) / lds;
-  constexpr int by_waves = 8 / (CQ / 32);
+  constexpr int by_waves = 12 / nw;
   constexpr int blocks = by_lds < by_waves ? (by_lds < 1 ? 1 : by_lds) : by_waves;
-  return blocks * (CQ / 32) / 4 < 1 ? 1 : blocks * (CQ / 32) / 4;
+  return blocks * nw / 4 < 1 ? 1 : blocks * nw / 4;
 }
 
-template <int D, int CQ>
-__global__ __launch_bounds__(CQ * 2, (comp_waves_per_simd<D, CQ>())) void comp_bf16_kernel(
+template <int D, int CQ, int NQ>
+__global__ __launch_bounds__(CQ * 2 * NQ, (comp_waves_per_simd<D, CQ, NQ>())) void comp_bf16_kernel(
     const bf16* __restrict__ qp, const char* __restrict__ tiles,
     const int32_t* __restrict__ lists, const int32_t* __restrict__ lens, int nq, int H, int nqc,
     int nkc, int ntile, int k, float sl2, int enable, const bf16* __restrict__ op,
     const float* __restrict__ lse_s,
     const int32_t* __restrict__ perm_q, bf16* __restrict__ out, float* __restrict__ lse_out,
     Lay lo, int total) {
-  constexpr int NW = CQ / 32;
+  constexpr int QC = CQ / 32;      // wavefronts of a cluster
+  constexpr int NW = NQ * QC;
   constexpr int T = NW * 64;
-  constexpr int CT = kCompTile;               // centroids per staged tile
-  constexpr int HC = comp_stage_cents<D>();   // centroids per LDS stage
+  constexpr int CT = kCompTile;    // centroids per staged tile
+  constexpr int HC = kCompStage;   // centroids per LDS stage
   constexpr int SUB = CT / HC;                // stages per tile
   constexpr int MT = HC / 32;
   constexpr int KS = D / 16;
@@ -147,13 +161,18 @@ __global__ __launch_bounds__(CQ * 2, (comp_waves_per_simd<D, CQ>())) void comp_b
   // than 2^8 (log2 units): exponentials then stay below 256, exact in fp32.
   constexpr float kLazy = 8.0f;
   __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE];
+  constexpr int MWORDS = kMaskWords / NQ;  // mask words of a cluster
   __shared__ uint32_t selmask[kMaskWords];
+  __shared__ __attribute__((aligned(16))) float cbias[NQ][HC];  // the stage's masked bias rows
 
   const int item = xcd_remap(blockIdx.x, total);
-  const int bh = item / nqc, a = item - bh * nqc;
+  const int per_head = (nqc + NQ - 1) / NQ;
+  const int bh = item / per_head, a0 = (item - bh * per_head) * NQ;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, l32 = lane & 31;
+  const int sub = w / QC;                  // this wavefront's cluster of the workgroup's
+  const int a = min(a0 + sub, nqc - 1);    // (a head's last workgroup may hold fewer)
   const size_t nq_pad = (size_t)nqc * CQ;
-  const int prow = a * CQ + 32 * w + l32;  // row inside this head's permuted order
+  const int prow = a * CQ + 32 * (w - sub * QC) + l32;  // row inside this head's permuted order
   const size_t qrow = (size_t)bh * nq_pad + prow;
   const int nwords = (nkc + 31) >> 5;
 
@@ -166,13 +185,18 @@ __global__ __launch_bounds__(CQ * 2, (comp_waves_per_simd<D, CQ>())) void comp_b
 
   // Operands of the final merge, loaded up front so that their latency
   // overlaps the set-up instead of ending the kernel.
-  const bool row_ok = prow < nq;
+  const bool row_ok = prow < nq && a0 + sub < nqc;
   float ls = 0.f;
   int orig = 0;
   bf16x4 s4[DT][4];
-  // this query cluster's list length (uniform; clamped for memory safety)
-  const int nsel = lens ? min(max(lens[(size_t)bh * nqc + a], 1), k) : k;
-  const bool do_comp = enable && nsel < nkc;
+  // list length of cluster c of the workgroup (uniform; clamped for memory safety)
+  auto list_len = [&](int c) {
+    return lens ? min(max(lens[(size_t)bh * nqc + a0 + c], 1), k) : k;
+  };
+  bool do_comp = false;  // some cluster has an unselected centroid
+#pragma unroll
+  for (int c = 0; c < NQ; ++c)
+    if (a0 + c < nqc) do_comp = do_comp || (enable && list_len(c) < nkc);
   const char* th = tiles + (size_t)bh * ntile * TILE;
   const TileCopy<KROW, KLD, NW> kcopy(w, lane);
   const TileCopy<VROW, VLD, NW, 2 * CT> vcopy(w, lane);
@@ -191,7 +215,9 @@ __global__ __launch_bounds__(CQ * 2, (comp_waves_per_simd<D, CQ>())) void comp_b
   };
   bf16x8 qreg[KS];
   if (do_comp) {
-    for (int i = tid; i < nwords; i += T) selmask[i] = 0u;
+#pragma unroll
+    for (int c = 0; c < NQ; ++c)  // a cluster that does not exist selects every centroid
+      for (int i = tid; i < nwords; i += T) selmask[c * MWORDS + i] = a0 + c < nqc ? 0u : ~0u;
     // The first two tiles are copied before the selection is known (a tile
     // whose centroids are all selected is then skipped, not un-copied).
     issue(0, 0);
@@ -212,10 +238,15 @@ __global__ __launch_bounds__(CQ * 2, (comp_waves_per_simd<D, CQ>())) void comp_b
   if (do_comp) {
     wait_lgkm();
     raw_barrier();  // selmask cleared
-    const int32_t* lst = lists + ((size_t)bh * nqc + a) * k;
-    for (int i = tid; i < nsel; i += T) {
-      int b = lst[i];
-      if (b >= 0 && b < nkc) atomicOr(&selmask[b >> 5], 1u << (b & 31));
+#pragma unroll
+    for (int c = 0; c < NQ; ++c) {
+      if (a0 + c >= nqc) break;
+      const int32_t* lst = lists + ((size_t)bh * nqc + a0 + c) * k;
+      const int nsel = list_len(c);
+      for (int i = tid; i < nsel; i += T) {
+        int b = lst[i];
+        if (b >= 0 && b < nkc) atomicOr(&selmask[c * MWORDS + (b >> 5)], 1u << (b & 31));
+      }
     }
     // Retire every load issued so far, including the first two tile copies
     // (a wait the compiler sees), so that no compiler-inserted vmcnt wait
@@ -230,7 +261,8 @@ __global__ __launch_bounds__(CQ * 2, (comp_waves_per_simd<D, CQ>())) void comp_b
       const int e0 = g * (HC / 32);
       for (int e = e0; e < e0 + HC / 32 && e < nwords; ++e) {
         const uint32_t wmask = e == nwords - 1 && (nkc & 31) ? (1u << (nkc & 31)) - 1u : ~0u;
-        any |= (~selmask[e] & wmask) != 0u;
+#pragma unroll
+        for (int c = 0; c < NQ; ++c) any |= (~selmask[c * MWORDS + e] & wmask) != 0u;
       }
       return __builtin_amdgcn_readfirstlane(any) != 0;
     };
@@ -256,11 +288,15 @@ __global__ __launch_bounds__(CQ * 2, (comp_waves_per_simd<D, CQ>())) void comp_b
       if (tile_live(g)) {
         const char* ks = smem + S * STAGE;
         const char* vs = ks + KBYTES;
-        float* bias = (float*)(smem + S * STAGE + KBYTES + VBYTES);
+        const float* srow = (const float*)(smem + S * STAGE + KBYTES + VBYTES);
+        const float* bias = cbias[sub];
         // Selected clusters are covered by the sparse part: drop them here.
-        if (tid < HC) {
-          const int b = g * HC + tid;
-          if (b < nkc && ((selmask[b >> 5] >> (b & 31)) & 1u)) bias[tid] = -INFINITY;
+        // (The rows were last read before the barrier that ended the stage.)
+        static_assert(NQ * HC <= T, "one bias entry a thread");
+        if (tid < NQ * HC) {
+          const int c = tid / HC, t = tid % HC, b = g * HC + t;
+          const bool sel = b < nkc && ((selmask[c * MWORDS + (b >> 5)] >> (b & 31)) & 1u);
+          cbias[c][t] = sel ? -INFINITY : srow[t];
         }
         f32x16 sacc[MT];
 #pragma unroll
@@ -483,7 +519,6 @@ hipError_t run_bf16(const Prob& P, const void* qp, const float* cent_k, const fl
                     float scale, int enable, const void* op, const float* lse,
                     const int32_t* perm_q, void* out, float* lse_out, char* tiles,
                     hipStream_t st) {
-  const int total = P.BH * P.nqc;
   const int ntile = (P.nkc + kCompTile - 1) / kCompTile;
   const bool do_comp = enable && (k < P.nkc || lens);
   if (do_comp) {
@@ -491,10 +526,21 @@ hipError_t run_bf16(const Prob& P, const void* qp, const float* cent_k, const fl
     hipLaunchKernelGGL(comp_stage_kernel<D>, dim3(ntile, P.BH, 2), dim3(256), 0, st, cent_k,
                        cent_v, count_k, P.nkc, ntile, tiles);
   }
-  hipLaunchKernelGGL((comp_bf16_kernel<D, CQ>), dim3(total), dim3(CQ * 2), 0, st,
-                     (const bf16*)qp, (const char*)tiles, lists, lens, P.nq, P.H, P.nqc, P.nkc, ntile, k,
-                     scale * kLog2e, enable, (const bf16*)op, lse, perm_q, (bf16*)out, lse_out,
-                     P.lo, total);
+  auto launch = [&](auto nq_tag) {
+    constexpr int NQ = decltype(nq_tag)::value;
+    const int total = P.BH * ((P.nqc + NQ - 1) / NQ);
+    hipLaunchKernelGGL((comp_bf16_kernel<D, CQ, NQ>), dim3(total), dim3(CQ * 2 * NQ), 0, st,
+                       (const bf16*)qp, (const char*)tiles, lists, lens, P.nq, P.H, P.nqc, P.nkc,
+                       ntile, k, scale * kLog2e, enable, (const bf16*)op, lse, perm_q, (bf16*)out,
+                       lse_out, P.lo, total);
+  };
+  // clusters that share a workgroup share the mask words (with enable = 0 the
+  // key clusters may be any number, and no mask is formed)
+  constexpr int NQ = comp_clusters<CQ>();
+  if (NQ == 1 || !do_comp || P.nkc <= kMaskWords * 32 / NQ)
+    launch(std::integral_constant<int, NQ>{});
+  else
+    launch(std::integral_constant<int, 1>{});
   return hipGetLastError();
 }
 

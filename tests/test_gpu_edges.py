@@ -113,3 +113,44 @@ def test_topk_filter_edges(nkc, k, kind):
     p = ca.Problem(1, 1, 6 * 64, nkc * 64, 64, 64, 64, torch.float32)
     got, _ = ca.select(p, None, None, k, scores_in=torch.from_numpy(S[None]).cuda())
     assert np.array_equal(got.cpu().numpy()[0], ref.topk(S.astype(np.float64), k))
+
+
+# bf16 compensation: two query clusters of 64 share a workgroup; heads with an
+# odd number of clusters (the last one alone), a single one, a remainder.
+@pytest.mark.parametrize("d,n,k", [(64, 130, 2), (64, 40, 1), (128, 300, 3), (128, 64, 1),
+                                   (64, 256, 4)])
+def test_compensation_cluster_pairs(d, n, k):
+    _compensation_parity("bf16", d, 64, 64, n, k, True)
+
+
+def test_compensation_many_key_clusters():
+    """More key clusters than two query clusters' masks hold together (32,768):
+    one query cluster a workgroup."""
+    import numpy as np
+    import torch
+    import paper_2608_26965_amd as ca
+    from oracle import ref
+    from tests import gpu_util as G
+    from synth import bf16_round
+    rng = np.random.default_rng(9)
+    n, nkc, d, c, k = 150, 33000, 64, 64, 40
+    Q = bf16_round(rng.standard_normal((1, n, d)).astype(np.float32))
+    kbar = rng.standard_normal((nkc, d)).astype(np.float32)
+    vbar = rng.standard_normal((nkc, d)).astype(np.float32)
+    p = ca.Problem(1, 1, n, nkc * c, d, c, c, torch.bfloat16)
+    perm = rng.permutation(n).astype(np.int32)
+    lists = G.random_lists(rng, 1, p.nqc, nkc, k)
+    cq_n, ck_n = G.counts(n, c), np.full(nkc, c, np.int32)
+    o_s = bf16_round(rng.standard_normal((n, d)).astype(np.float32)).astype(np.float64)
+    l_s = rng.standard_normal(n) + 8.0  # about the log of the keys kept
+    op = np.zeros((1, p.nq_pad, d), np.float32)
+    lse = np.zeros((1, p.nq_pad), np.float32)
+    op[0, :n], lse[0, :n] = o_s[perm], l_s[perm]
+    out, lse_out = ca.compensate(
+        p, G.permuted_rows(Q, perm[None], c, torch.bfloat16), G.dev(kbar[None]), G.dev(vbar[None]),
+        G.dev(ck_n[None], torch.int32), G.dev(lists, torch.int32), k, G.dev(op, torch.bfloat16),
+        G.dev(lse), G.dev(perm[None], torch.int32), want_lse=True)
+    o_w, l_w = ref.compensate(Q[0].astype(np.float64), kbar, vbar, ck_n, perm, cq_n, lists[0], o_s,
+                              lse[0, :n][np.argsort(perm)].astype(np.float64), 1 / 8)
+    assert np.abs(G.host(out)[0, 0] - o_w).max() <= G.TOL["bf16"]
+    assert np.abs(G.host(lse_out)[0] - l_w).max() <= 1e-4 * np.abs(l_w).max()
