@@ -108,6 +108,7 @@ __device__ __forceinline__ void acc_outer(float (*A)[kDP], float (*B)[kDP], int 
     const int blk = threadIdx.x + 256 * q;
     if (blk >= nb) break;
     const int bi = blk / d4, bj = blk % d4;
+#pragma unroll 8
     for (int r = 0; r < rows; ++r) {
       const float4 a = *(const float4*)&A[r][4 * bi];
       const float4 b = *(const float4*)&B[r][4 * bj];
@@ -161,6 +162,7 @@ __global__ __launch_bounds__(256) void moments_partial_kernel(Ctx C) {
     __syncthreads();
     acc_outer(X, X, rows, d4, acc);
     if (threadIdx.x < d)
+#pragma unroll 8
       for (int r = 0; r < rows; ++r) csum += X[r][threadIdx.x];
   }
   float* out = C.mom_part + ((size_t)pid * C.nblk + blk) * (d * d + d);
@@ -168,45 +170,69 @@ __global__ __launch_bounds__(256) void moments_partial_kernel(Ctx C) {
   if (threadIdx.x < d) out[d * d + threadIdx.x] = csum;
 }
 
-// Sum of nb partials p[0], p[stride], ... in fp64: eight independent running
-// sums (so the loads overlap), combined in a fixed order (deterministic).
-__device__ __forceinline__ double sum_partials(const float* p, size_t stride, int nb) {
-  double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  int b = 0;
-  for (; b + 8 <= nb; b += 8) {
+// The finishing kernels sum nb partials p[0], p[stride], ... in fp64 as eight
+// interleaved sums added pairwise (a fixed order, so deterministic), by one
+// thread an element (U = 1, its loads eight at a time) or by eight (U = 8, one
+// sum each, exchanged through LDS). One thread an element is all load latency
+// where the elements are few: the moments of 8 heads (64 partials) took 9.5 us
+// against 7.1, of one fp32 head 8.9 against 5.0; eight are too little work a
+// workgroup where the elements are many: 67 us against 30 on 40 heads at
+// d = 128. The line between (2^18 elements over all heads and both sides) is
+// their middle.
+template <int U>
+__device__ __forceinline__ double sum_partials(const float* p, size_t stride, int nb,
+                                               double (*sh)[256 / U], bool in) {
+  if constexpr (U == 1) {
+    double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (!in) return 0.0;
+    int b = 0;
+    for (; b + 8 <= nb; b += 8) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) acc[u] += (double)p[(size_t)(b + u) * stride];
+      for (int u = 0; u < 8; ++u) acc[u] += (double)p[(size_t)(b + u) * stride];
+    }
+    for (; b < nb; ++b) acc[b & 7] += (double)p[(size_t)b * stride];
+    return ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+  } else {
+    static_assert(U == 8, "eight interleaved sums");
+    const int u = threadIdx.x / (256 / U), e = threadIdx.x % (256 / U);
+    double acc = 0.0;
+    if (in) {
+#pragma unroll 8
+      for (int b = u; b < nb; b += 8) acc += (double)p[(size_t)b * stride];
+    }
+    sh[u][e] = acc;
+    __syncthreads();
+    return ((sh[0][e] + sh[1][e]) + (sh[2][e] + sh[3][e])) +
+           ((sh[4][e] + sh[5][e]) + (sh[6][e] + sh[7][e]));
   }
-  for (; b < nb; ++b) acc[b & 7] += (double)p[(size_t)b * stride];
-  return ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
 }
 
-// Reduces the moment partials in fp64, one element per thread, and writes
-// the matrices the eigensolver starts from:
+// Reduces the moment partials and writes the matrices the eigensolver starts
+// from:
 //   queries: metric -> Q^T Q / n;  pca -> centred covariance of Q
 //   keys:    centred covariance of K (both modes)
-// plus the means. Grid: (element blocks, BH, side).
+// plus the means. Grid: (element blocks of 256 / U, BH, side).
+template <int U>
 __global__ __launch_bounds__(256) void moments_finish_kernel(Ctx C) {
-  const int side = blockIdx.z, bh = blockIdx.y, d = C.d;
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= d * d + d) return;
+  __shared__ double sh[3][U][256 / U];
+  const int side = blockIdx.z, bh = blockIdx.y, d = C.d, dd = d * d;
+  const int e = blockIdx.x * (256 / U) + threadIdx.x % (256 / U);
   const int pid = side * C.BH + bh;
-  const size_t stride = (size_t)d * d + d;
+  const size_t stride = (size_t)dd + d;
   const float* part = C.mom_part + (size_t)pid * C.nblk * stride;
+  const bool centred = side == 1 || C.xf == CA_XF_PCA;
+  const bool in = e < dd + d, cov = e < dd && centred;
+  const int i = e / d, j = e % d;
   const double n = (double)C.s[side].n;
-  if (e >= d * d) {
-    const int t = e - d * d;
-    vec(C, bh, side == 0 ? V_MUQ : V_MUK)[t] = (float)(sum_partials(part + e, stride, C.nblk) / n);
+  double v = sum_partials<U>(part + e, stride, C.nblk, sh[0], in) / n;
+  const double mi = sum_partials<U>(part + dd + i, stride, C.nblk, sh[1], cov) / n;
+  const double mj = sum_partials<U>(part + dd + j, stride, C.nblk, sh[2], cov) / n;
+  if (!in || threadIdx.x >= 256 / U) return;
+  if (e >= dd) {
+    vec(C, bh, side == 0 ? V_MUQ : V_MUK)[e - dd] = (float)v;
     return;
   }
-  const bool centred = side == 1 || C.xf == CA_XF_PCA;
-  const int i = e / d, j = e % d;
-  double v = sum_partials(part + e, stride, C.nblk) / n;
-  if (centred) {
-    const double mi = sum_partials(part + d * d + i, stride, C.nblk) / n;
-    const double mj = sum_partials(part + d * d + j, stride, C.nblk) / n;
-    v -= mi * mj;
-  }
+  if (centred) v -= mi * mj;
   mat(C, bh, side == 0 ? M_A0 : M_CK)[e] = (float)v;
 }
 
@@ -1326,6 +1352,7 @@ __global__ __launch_bounds__(256) void qnorm_partial_kernel(Ctx C) {
     for (int e = threadIdx.x; e < kStage * d4; e += 256) {
       const int r = e / d4, j4 = e % d4;
       float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+#pragma unroll 8
       for (int t = 0; t < d; ++t) {
         const float xv = X[r][t];
         const float4 s4 = *(const float4*)&Sk[t * kDP + 4 * j4];
@@ -1338,17 +1365,25 @@ __global__ __launch_bounds__(256) void qnorm_partial_kernel(Ctx C) {
     }
     __syncthreads();
     // one wave per row: 1/|rho|
-    for (int r = w; r < kStage; r += 4) {
-      float s = 0.f;
-      for (int t = lane; t < d; t += 64) s = __builtin_fmaf(R[r][t], R[r][t], s);
+    float ss[kStage / 4];  // rows w, w + 4, ...: their reductions overlap
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-      if (lane == 0) {
-        const float inv = s > 0.f ? 1.f / sqrtf(s) : 0.f;
+    for (int q = 0; q < kStage / 4; ++q) {
+      const int r = w + 4 * q;
+      ss[q] = 0.f;
+      for (int t = lane; t < d; t += 64) ss[q] = __builtin_fmaf(R[r][t], R[r][t], ss[q]);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+      for (int q = 0; q < kStage / 4; ++q) ss[q] += __shfl_xor(ss[q], o, 64);
+#pragma unroll
+    for (int q = 0; q < kStage / 4; ++q)
+      if (lane == q) {
+        const int r = w + 4 * q;
+        const float inv = ss[q] > 0.f ? 1.f / sqrtf(ss[q]) : 0.f;
         invs[r] = inv;
         if (r < rows) C.inv_q[(size_t)bh * S.n + rs + r] = inv;
       }
-    }
     __syncthreads();
     for (int e = threadIdx.x; e < kStage * 4 * d4; e += 256) {
       const int r = e / (4 * d4), t = e % (4 * d4);
@@ -1357,6 +1392,7 @@ __global__ __launch_bounds__(256) void qnorm_partial_kernel(Ctx C) {
     __syncthreads();
     acc_outer(R, R, rows, d4, acc);
     if (threadIdx.x < d)
+#pragma unroll 8
       for (int r = 0; r < rows; ++r) csum += R[r][threadIdx.x];
   }
   float* out = C.qn_part + ((size_t)bh * C.nblk + blk) * (d * d + d);
@@ -1364,8 +1400,7 @@ __global__ __launch_bounds__(256) void qnorm_partial_kernel(Ctx C) {
   if (threadIdx.x < d) out[d * d + threadIdx.x] = csum;
 }
 
-// Means of the query-representation partials (fp64 reduction, one element
-// per thread): M_C3 <- sum/n of the d x d part, V_MUR <- sum/n of the vector
+// Means of the query-representation partials: M_C3 <- sum/n of the d x d part, V_MUR <- sum/n of the vector
 // part. The partials hold either r r^T and r (then cov(r) = M_C3 - mu mu^T),
 // or inv^2 x x^T and inv x (then cov(r) = S_k^T M_C3 S_k - u u^T with
 // u = S_k^T V_MUR); the eigensolver's prologue forms cov(r).
@@ -1375,7 +1410,7 @@ __global__ __launch_bounds__(256) void qnorm_finish_kernel(Ctx C) {
   if (e >= d * d + d) return;
   const size_t stride = (size_t)d * d + d;
   const float* part = C.qn_part + (size_t)bh * C.nblk * stride;
-  const double v = sum_partials(part + e, stride, C.nblk) / (double)C.s[0].n;
+  const double v = sum_partials<1>(part + e, stride, C.nblk, nullptr, true) / (double)C.s[0].n;
   if (e < d * d)
     mat(C, bh, M_C3)[e] = (float)v;
   else
@@ -1442,6 +1477,7 @@ __global__ __launch_bounds__(256) void project_kernel(Ctx C) {
     for (int e = threadIdx.x; e < rows * d4; e += 256) {
       const int r = e / d4, j4 = e % d4;
       float a[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
       for (int t = 0; t < d; ++t) {
         const float xv = X[r][t];
         const float4 t4 = *(const float4*)&T[t * kDP + 4 * j4];
@@ -3627,8 +3663,10 @@ hipError_t launch_cluster(const Prob& P, const void* q, const void* k, const voi
     else
       hipLaunchKernelGGL(moments_partial_kernel, dim3(C.nblk, 2 * BH), dim3(256), 0, st, C);
     CA_CHECK();
-    const dim3 fgrid((d * d + d + 255) / 256, BH, 2);
-    hipLaunchKernelGGL(moments_finish_kernel, fgrid, dim3(256), 0, st, C);
+    const bool few = (size_t)2 * BH * (d * d + d) <= (size_t)1 << 18;
+    const int per = few ? 32 : 256;  // elements a workgroup of the finishing kernels
+    hipLaunchKernelGGL((few ? moments_finish_kernel<8> : moments_finish_kernel<1>),
+                       dim3((d * d + d + per - 1) / per, BH, 2), dim3(256), 0, st, C);
     CA_CHECK();
     const int wq = P.dtype == CA_BF16 ? (int)O_TQ : -1, wk = P.dtype == CA_BF16 ? (int)O_TK : -1;
     EighJobs J;
@@ -3726,8 +3764,10 @@ hipError_t launch_cluster(const Prob& P, const void* q, const void* k, const voi
     else
       hipLaunchKernelGGL(split_keys_kernel<0>, kgrid, dim3(256), 0, st, C, L);
     CA_CHECK();
-    hipLaunchKernelGGL(split_select_kernel, dim3(1 << l, 2 * BH), dim3(kSelThreads), 0, st, C, L);
-    CA_CHECK();
+    if (cpn > 1) {  // nodes of one chunk are selected with their keys
+      hipLaunchKernelGGL(split_select_kernel, dim3(1 << l, 2 * BH), dim3(kSelThreads), 0, st, C, L);
+      CA_CHECK();
+    }
     hipLaunchKernelGGL(split_scatter_kernel, dim3(cpn, 1 << l, 2 * BH), dim3(256), 0, st, C, L);
     CA_CHECK();
   }
