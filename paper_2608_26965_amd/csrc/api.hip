@@ -219,7 +219,8 @@ void plan_workspace(const Prob& P, Workspace* W) {
   W->wops = take(BH * 3 * 2 * d * d * 2);
   W->node_state = take(2 * BH * W->max_big_nodes * kNodeInts * 4);
   W->hist = take(2 * BH * W->hist_slots * kBins * 4);
-  W->chunk_cnt = take(2 * BH * W->hist_slots * 2 * 4);
+  W->cand = take(2 * BH * nmax * 4);
+  W->chunk_cnt = take(2 * BH * W->hist_slots * kChunkInts * 4);
   W->dirs = take(basic ? 2 * 2 * BH * W->max_big_nodes * d * 4 : 0);
   W->scores = take(BH * P.nqc * P.nkc * 4);
   W->sched = take(((size_t)8 + 8 * (size_t)attn_sched_cap((int)(BH * P.nqc))) * 4);

@@ -112,7 +112,8 @@ struct Workspace {
   size_t wops;              // bf16 [BH][3][2][d][d] MFMA operands (transposed hi/lo)
   size_t node_state;        // int32 [2][BH][max_big_nodes][kNodeInts]
   size_t hist;              // uint32 [2][BH][hist_slots][kBins] chunk histograms
-  size_t chunk_cnt;         // int32 [2][BH][hist_slots][2] chunk prefixes (less, equal)
+  size_t cand;              // uint32 [2][BH][nmax] keys of the threshold's bin, by node and chunk
+  size_t chunk_cnt;         // int32 [2][BH][hist_slots][kChunkInts] chunk prefixes
   size_t dirs;              // fp32 [2 levels][2][BH][max_big_nodes][d] split directions (basic)
   // selection
   size_t scores;            // fp32 [BH][nqc][nkc]
@@ -143,7 +144,8 @@ inline bool col_copy_used(const Prob& P) {
 constexpr int kMats = 7;
 constexpr int kVecs = 3;
 constexpr int kNodeInts = 16;
-constexpr int kBins = 4096;       // linear bins of the multi-block split select
+constexpr int kChunkInts = 4;
+constexpr int kBins = 256;        // linear bins of the multi-block split select
 constexpr int kChunk = 4096;      // tokens per block in the multi-block split passes
 constexpr int kTail = 2048;       // nodes of at most this size finish in one workgroup
 constexpr int kMomRows = 4096;    // rows per moment-partial block (at most)

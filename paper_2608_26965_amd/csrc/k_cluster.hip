@@ -9,7 +9,8 @@
 //                the normalised query representation and its covariance
 //   project      Y = X T (queries additionally scaled by 1/|q S_k|)
 //   split        levels with nodes larger than the tail size: multi-block
-//                radix select (11/11/10-bit digits) + stable partition;
+//                exact select (256 linear bins, then within one) + stable
+//                partition;
 //                remaining levels: one workgroup per node, in LDS
 //   gather       permuted Q/K/V, centroids of the original vectors, counts
 //
@@ -63,6 +64,7 @@ struct Ctx {
   uint32_t* keys;
   int32_t* node_state;
   uint32_t* hist;
+  uint32_t* cand;
   int32_t* chunk_cnt;
   int max_nodes, hist_slots;
   int split;        // ca_split
@@ -2018,21 +2020,40 @@ __device__ __forceinline__ void bin_range(float mean, float var, int nb, float* 
 }
 
 // Multi-block levels. A node's split threshold is its m_L-th smallest key,
-// found exactly in two steps:
-//   keys:   every chunk block gathers its keys and counts them into kBins
-//           linear bins over [mean - 4 sd, mean + 4 sd] of the node's sample
-//           (the clamped linear map is monotone, so each bin is a contiguous
-//           key range); the chunk's histogram goes to its own slot.
-//   select: one workgroup per node sums the chunk histograms, finds the bin
-//           holding the wanted rank, collects that bin's keys (typically a
-//           few hundred) and selects exactly among them with an 8-bit radix
-//           select; it also turns the per-chunk counts below / equal to the
-//           threshold into exclusive prefixes for the stable scatter.
-// Kernel boundaries order the steps: no grid-wide fences or arrival counters.
+// found exactly in three passes over chunks of its keys:
+//   keys:    every chunk block gathers its keys and counts them into kBins
+//            linear bins over [mean - 4 sd, mean + 4 sd] of the node's sample
+//            (the clamped linear map is monotone, so each bin is a contiguous
+//            key range); the chunk's histogram goes to its own slot.
+//   bins:    every chunk block sums the node's histograms, finds the bin that
+//            holds the wanted rank, and lists its chunk's keys of that bin
+//            (typically one in eighty) behind those of the chunks before it.
+//   scatter: every chunk block selects exactly among the listed keys, counts
+//            those of the chunks before it, and partitions its chunk stably.
+// Kernel boundaries order the passes, but for nodes with more than kListed
+// listed keys (runs of equal keys, keys that outliers crowd into a bin): there
+// the last chunk block of the bins pass to arrive selects for the node, since
+// every chunk reading so long a list would cost chunks times keys (16 heads of
+// 262,144 tokens, 40% of them zero: ca_cluster 11.4 ms so, 6.3 ms with the
+// last block; 10% zero: 7.1 and 5.8 ms; 6.4 and 5.8 ms with 4,096 bins).
+// The histograms are small (kBins) and the select is repeated in every block,
+// so that no pass leaves a node to one workgroup. Before, with 4,096 bins and
+// one workgroup a node for the select (which read all keys of the node again),
+// the keys/select/scatter passes of a level took 12.7/19.7/14.8 us on average
+// at 8 heads of 65,521 tokens, 48/40/46 us at 40 heads of 75,600, and
+// 64/46/52 us at 16 heads of 262,144; now keys/bins/scatter take 11.3/12.4/16.3,
+// 43.9/19.3/51.5 and 60.0/24.8/63.6 us (rocprofv3 kernel trace).
 //
-// Node state (int32): 0 j* (-1: leaf), 1 threshold key, 2 rank among keys
-// equal to the threshold, 3 left size, 4 start, 5 size, 6 bin origin (float),
-// 7 number of chunks, 8 bin scale (float), 9 rank of the threshold.
+// Node state (int32): 0 j* (-1: leaf), 1 threshold key (selected) or number of
+// listed keys, 2 rank of the threshold among the keys equal to it (selected) or
+// among the listed ones, 3 left size, 4 start, 5 size, 6 bin origin (float),
+// 7 number of chunks, 8 bin scale (float), 9 rank of the threshold, 10 selected
+// with its keys (nodes of one chunk) or in the bins pass, 11 bin of the
+// threshold, 12 chunk blocks that have listed their keys.
+// Chunk state (int32): 0 keys below the bin and 1 listed keys in the chunks
+// before it, 2 and 3 smallest and largest listed key of the chunk; of a node
+// selected in the bins pass: 0 keys below and 1 equal to the threshold in the
+// chunks before it.
 __device__ __forceinline__ int32_t* node_ptr(const Ctx& C, int pid, int node) {
   return C.node_state + ((size_t)pid * C.max_nodes + node) * kNodeInts;
 }
@@ -2114,6 +2135,7 @@ __global__ __launch_bounds__(64 * kChooseWaves) void split_choose_kernel(Ctx C, 
     const int mL = left_size(size, S.c);
     ns[0] = js;
     ns[10] = 0;
+    ns[12] = 0;
     ns[1] = 0;
     ns[2] = 0;
     ns[3] = mL;
@@ -2284,7 +2306,7 @@ __global__ __launch_bounds__(kBasicThreads) void basic_choose_kernel(Ctx C, Leve
     float lo = (float)(mp - 4.0 * sd), scale = (float)((double)kBins / (8.0 * sd));
     if (!(sd > 0.0) || !isfinite(lo) || !isfinite(scale)) {
       lo = 0.f;
-      scale = 0.f;  // one bin: the select step falls back to streaming
+      scale = 0.f;  // one bin
     }
     const int mL = left_size(size, S.c);
     ns[0] = 0;
@@ -2292,6 +2314,7 @@ __global__ __launch_bounds__(kBasicThreads) void basic_choose_kernel(Ctx C, Leve
     ns[2] = 0;
     ns[3] = mL;
     ns[10] = 0;
+    ns[12] = 0;
     ns[4] = start;
     ns[5] = size;
     ns[6] = __float_as_int(lo);
@@ -2455,7 +2478,7 @@ __global__ __launch_bounds__(64) void basic_choose64_kernel(Ctx C, LevelArgs L) 
     float lo = (float)(mp - 4.0 * sd), scale = (float)((double)kBins / (8.0 * sd));
     if (!(sd > 0.0) || !isfinite(lo) || !isfinite(scale)) {
       lo = 0.f;
-      scale = 0.f;  // one bin: the select step falls back to streaming
+      scale = 0.f;  // one bin
     }
     const int mL = left_size(size, S.c);
     ns[0] = 0;
@@ -2469,6 +2492,7 @@ __global__ __launch_bounds__(64) void basic_choose64_kernel(Ctx C, LevelArgs L) 
     ns[8] = __float_as_int(scale);
     ns[9] = mL - 1;
     ns[10] = 0;
+    ns[12] = 0;
   }
 }
 
@@ -2685,9 +2709,6 @@ __global__ __launch_bounds__(256) void split_keys_kernel(Ctx C, LevelArgs L) {
         if (o < c1) keys[start + o] = kv[u];
       }
       if (tid == 0) {
-        int32_t* cc = C.chunk_cnt + ((size_t)pid * C.hist_slots + (size_t)node * L.cpn) * 2;
-        cc[0] = 0;
-        cc[1] = 0;
         ns[1] = (int)thr;
         ns[2] = r;
         ns[10] = 1;  // selected
@@ -2705,204 +2726,253 @@ __global__ __launch_bounds__(256) void split_keys_kernel(Ctx C, LevelArgs L) {
     }
   }
   __syncthreads();
-  uint4* gh = reinterpret_cast<uint4*>(
-      C.hist + ((size_t)pid * C.hist_slots + (size_t)node * L.cpn + blockIdx.x) * kBins);
-  for (int b = threadIdx.x; b < kBins / 4; b += 256)
-    gh[b] = make_uint4((uint32_t)lh[4 * b], (uint32_t)lh[4 * b + 1], (uint32_t)lh[4 * b + 2],
-                       (uint32_t)lh[4 * b + 3]);
+  static_assert(kBins == 256, "one bin a thread");
+  C.hist[((size_t)pid * C.hist_slots + (size_t)node * L.cpn + blockIdx.x) * kBins + threadIdx.x] =
+      (uint32_t)lh[threadIdx.x];
 }
 
-constexpr int kSelThreads = 1024;
-constexpr int kCand = 8192;         // candidates held in LDS
-constexpr int kMaxNodeChunks = 1024;  // chunks of one node (4M positions)
-static_assert(kBins == 4 * kSelThreads, "one uint4 of bins per select thread");
+// Listed keys up to which every chunk block of a node selects for itself
+// (16 a thread, in registers).
+constexpr int kListed = 16 * 256;
 
-__global__ __launch_bounds__(kSelThreads) void split_select_kernel(Ctx C, LevelArgs L) {
-  __shared__ uint32_t ckey[kCand];
-  __shared__ uint16_t cchunk[kCand];
-  __shared__ int below_ch[kMaxNodeChunks], less_ch[kMaxNodeChunks], eq_ch[kMaxNodeChunks];
-  __shared__ int rh[256];
-  __shared__ int wsum[kSelThreads / 64];
-  __shared__ int sh_bin, sh_below, sh_ncand, sh_digit, sh_rank;
-  const int pid = blockIdx.y, node = blockIdx.x, side = pid / C.BH;
+// Exact select of a node with more than kListed listed keys, by one workgroup:
+// whether the threshold is the most frequent of 64 of them (a run of equal
+// keys), else 8-bit radix passes after the leading bytes that the smallest and
+// the largest listed key share; and the numbers of keys below and equal to the
+// threshold in the chunks before each.
+struct NodeSelect {
+  int hist[256];
+  int wsum[4];
+  uint32_t kmin, kmax;
+  int digit, rank, lt, eq;
+};
+__device__ __forceinline__ void node_select(int32_t* ns, const uint32_t* cand, int32_t* cc, int n,
+                                            int nch, int rank, NodeSelect& sh) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  // keys below and equal to thr in each chunk (a wavefront each) and in all
+  auto count = [&](uint32_t thr) {
+    if (tid == 0) sh.lt = sh.eq = 0;
+    __syncthreads();
+    for (int g = tid >> 6; g < nch; g += 4) {
+      const int i0 = cc[kChunkInts * g + 1], i1 = g + 1 < nch ? cc[kChunkInts * (g + 1) + 1] : n;
+      int lt = 0, eq = 0;
+      for (int i = i0 + lane; i - lane < i1; i += 64 * 16) {
+        uint32_t k[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) k[u] = i + 64 * u < i1 ? cand[i + 64 * u] : 0xFFFFFFFFu;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+          lt += i + 64 * u < i1 && k[u] < thr;
+          eq += i + 64 * u < i1 && k[u] == thr;
+        }
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        lt += __shfl_xor(lt, o, 64);
+        eq += __shfl_xor(eq, o, 64);
+      }
+      if (lane == 0) {
+        cc[kChunkInts * g + 2] = lt;
+        cc[kChunkInts * g + 3] = eq;
+        atomicAdd(&sh.lt, lt);
+        atomicAdd(&sh.eq, eq);
+      }
+    }
+    __syncthreads();
+  };
+  if (tid == 0) {
+    sh.kmin = 0xFFFFFFFFu;
+    sh.kmax = 0u;
+  }
+  __syncthreads();
+  for (int i = tid; i < nch; i += 256) {
+    atomicMin(&sh.kmin, (uint32_t)cc[kChunkInts * i + 2]);
+    atomicMax(&sh.kmax, (uint32_t)cc[kChunkInts * i + 3]);
+  }
+  __syncthreads();
+  const uint32_t kmin = sh.kmin, diff = sh.kmin ^ sh.kmax;
+  uint32_t thr;
+  {
+    const uint32_t key = cand[(size_t)n * lane / 64];
+    int same = 0;
+    for (int j = 0; j < 64; ++j)
+      same += (uint32_t)__builtin_amdgcn_readlane((int)key, j) == key;
+    const int most = wave_max(same);
+    thr = (uint32_t)__builtin_amdgcn_readlane((int)key, __builtin_ctzll(__ballot(same == most)));
+    sh.lt = sh.eq = 0;
+    if (most > 1) count(thr);  // the same in all wavefronts
+  }
+  __syncthreads();
+  if (rank >= sh.lt && rank < sh.lt + sh.eq) {
+    rank -= sh.lt;
+  } else {
+    const int skip = __builtin_clz(diff | 1u) / 8;  // common leading bytes
+    thr = skip == 0 ? 0u : kmin & (0xFFFFFFFFu << (32 - 8 * skip));
+    for (int shift = 24 - 8 * skip; shift >= 0; shift -= 8) {
+      sh.hist[tid] = 0;
+      __syncthreads();
+      for (int i = tid; i - tid < n; i += 256 * 16) {
+        uint32_t k[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) k[u] = i + 256 * u < n ? cand[i + 256 * u] : 0u;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+          const bool in = i + 256 * u < n &&
+                          (shift == 24 || (k[u] >> (shift + 8)) == (thr >> (shift + 8)));
+          const uint64_t m = __ballot(in);
+          if (!m) continue;
+          // one addition for the lanes that share the first one's digit
+          const int dg = (int)(k[u] >> shift) & 255;
+          const int first = __builtin_ctzll(m), d0 = __builtin_amdgcn_readlane(dg, first);
+          const uint64_t eq = __ballot(in && dg == d0);
+          if (lane == first) atomicAdd(&sh.hist[d0], __popcll(eq));
+          else if (in && dg != d0) atomicAdd(&sh.hist[dg], 1);
+        }
+      }
+      __syncthreads();
+      const int c = sh.hist[tid];
+      int tot;
+      const int before = scan256(c, sh.wsum, &tot);
+      if (rank >= before && rank < before + c) {
+        sh.digit = tid;
+        sh.rank = rank - before;
+      }
+      __syncthreads();
+      thr |= (uint32_t)sh.digit << shift;
+      rank = sh.rank;
+    }
+    count(thr);
+  }
+  // of the chunks before each
+  int lt0 = 0, eq0 = 0;
+  for (int g0 = 0; g0 < nch; g0 += 256) {
+    const int g = g0 + tid;
+    const int lt = g < nch ? cc[kChunkInts * g + 2] : 0;
+    const int eq = g < nch ? cc[kChunkInts * g + 3] : 0;
+    int ltall, eqall;
+    const int ltb = scan256(lt, sh.wsum, &ltall), eqb = scan256(eq, sh.wsum, &eqall);
+    if (g < nch) {
+      cc[kChunkInts * g] += lt0 + ltb;
+      cc[kChunkInts * g + 1] = eq0 + eqb;
+    }
+    lt0 += ltall;
+    eq0 += eqall;
+  }
+  if (tid == 0) {
+    ns[1] = (int)thr;
+    ns[2] = rank;
+    ns[10] = 1;
+  }
+}
+
+__global__ __launch_bounds__(256) void split_bins_kernel(Ctx C, LevelArgs L) {
+  __shared__ NodeSelect sel;
+  __shared__ int wsum[4];
+  __shared__ int sh_last;
+  __shared__ int sh_bin, sh_before, sh_base, sh_n, sh_cnt, sh_below;
+  __shared__ uint32_t sh_min, sh_max;
+  const int pid = blockIdx.z, node = blockIdx.y, side = pid / C.BH, ch = blockIdx.x;
   const Side& S = C.s[side];
   if (L.level >= S.big) return;
   int32_t* ns = node_ptr(C, pid, node);
   if (ns[0] < 0 || ns[10]) return;  // a leaf, or selected with its keys
   const int start = ns[4], size = ns[5], nch = ns[7];
   const float lo = __int_as_float(ns[6]), scale = __int_as_float(ns[8]);
+  const int c0 = ch * kChunk;
+  if (c0 >= size) return;
+  const int c1 = min(size, c0 + kChunk);
   const int tid = threadIdx.x, lane = tid & 63;
-  const uint4* H = reinterpret_cast<const uint4*>(
-      C.hist + ((size_t)pid * C.hist_slots + (size_t)node * L.cpn) * kBins);
   const uint32_t* keys = C.keys + (size_t)pid * C.nmax + start;
-  for (int ch = tid; ch < nch; ch += kSelThreads) {
-    below_ch[ch] = 0;
-    less_ch[ch] = 0;
-    eq_ch[ch] = 0;
+  uint32_t kv[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int o = c0 + tid + 256 * u;
+    kv[u] = o < c1 ? keys[o] : 0u;
   }
-  if (tid == 0) sh_ncand = 0;
-  // 1. node histogram: thread t owns bins 4t .. 4t+3
-  uint32_t nb[4] = {0u, 0u, 0u, 0u};
-  for (int ch0 = 0; ch0 < nch; ch0 += 8) {
-    uint4 hv[8];
+  // bin tid of the node, and of the chunks before this one
+  const uint32_t* H = C.hist + ((size_t)pid * C.hist_slots + (size_t)node * L.cpn) * kBins + tid;
+  int tot = 0, pre = 0;
+  for (int g = 0; g < nch; g += 16) {
+    int hv[16];
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-      hv[u] = ch0 + u < nch ? H[(size_t)(ch0 + u) * (kBins / 4) + tid] : make_uint4(0, 0, 0, 0);
+    for (int u = 0; u < 16; ++u) hv[u] = g + u < nch ? (int)H[(size_t)(g + u) * kBins] : 0;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      nb[0] += hv[u].x;
-      nb[1] += hv[u].y;
-      nb[2] += hv[u].z;
-      nb[3] += hv[u].w;
+    for (int u = 0; u < 16; ++u) {
+      tot += hv[u];
+      pre += g + u < ch ? hv[u] : 0;
     }
-  }
-  const int rank = ns[9];
-  int tot;
-  const int before = block_scan<kSelThreads>((int)(nb[0] + nb[1] + nb[2] + nb[3]), wsum, &tot);
-  {
-    int acc = before;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (rank >= acc && rank < acc + (int)nb[i]) {
-        sh_bin = 4 * tid + i;
-        sh_below = acc;
-      }
-      acc += (int)nb[i];
-    }
-  }
-  __syncthreads();
-  const int bstar = sh_bin, below = sh_below;
-  // 2. per-chunk counts of keys in bins below b*
-  for (int ch0 = 0; ch0 < nch; ch0 += 8) {
-    uint4 hv[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      hv[u] = ch0 + u < nch && 4 * tid < bstar ? H[(size_t)(ch0 + u) * (kBins / 4) + tid]
-                                                : make_uint4(0, 0, 0, 0);
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      int part = (int)hv[u].x + (4 * tid + 1 < bstar ? (int)hv[u].y : 0) +
-                 (4 * tid + 2 < bstar ? (int)hv[u].z : 0) +
-                 (4 * tid + 3 < bstar ? (int)hv[u].w : 0);
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);
-      if (lane == 0 && part) atomicAdd(&below_ch[ch0 + u], part);
-    }
-  }
-  // 3. collect the keys of bin b*
-  constexpr int B = 16;
-  for (int o0 = 0; o0 < size; o0 += B * kSelThreads) {
-    uint32_t kv[B];
-#pragma unroll
-    for (int u = 0; u < B; ++u) {
-      const int o = o0 + tid + kSelThreads * u;
-      kv[u] = o < size ? keys[o] : 0u;
-    }
-#pragma unroll
-    for (int u = 0; u < B; ++u) {
-      const int o = o0 + tid + kSelThreads * u;
-      const bool hit = o < size && lin_bin(kv[u], lo, scale) == bstar;
-      const uint64_t m = __ballot(hit);
-      if (m == 0) continue;
-      int base = 0;
-      if (lane == 0) base = atomicAdd(&sh_ncand, __popcll(m));
-      base = __shfl(base, 0, 64);
-      if (hit) {
-        const int slot = base + (int)__popcll(m & ((1ull << lane) - 1ull));
-        if (slot < kCand) {
-          ckey[slot] = kv[u];
-          cchunk[slot] = (uint16_t)(o / kChunk);
-        }
-      }
-    }
-  }
-  __syncthreads();
-  const int ncand = sh_ncand;
-  const bool in_lds = ncand <= kCand;
-  // 4. exact select among the candidates: four 8-bit digits, high first
-  uint32_t thr = 0u;
-  int r = rank - below;
-  for (int pass = 0; pass < 4; ++pass) {
-    const int shift = 24 - 8 * pass;
-    if (tid < 256) rh[tid] = 0;
-    __syncthreads();
-    auto count = [&](uint32_t key) {
-      if (pass == 0 || (key >> (shift + 8)) == (thr >> (shift + 8)))
-        atomicAdd(&rh[(key >> shift) & 255u], 1);
-    };
-    if (in_lds) {
-      for (int i = tid; i < ncand; i += kSelThreads) count(ckey[i]);
-    } else {
-      for (int o = tid; o < size; o += kSelThreads) {
-        const uint32_t key = keys[o];
-        if (lin_bin(key, lo, scale) == bstar) count(key);
-      }
-    }
-    __syncthreads();
-    if (tid < 64) {
-      int cnt[4], sum = 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        cnt[i] = rh[4 * tid + i];
-        sum += cnt[i];
-      }
-      int incl = sum;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += y;
-      }
-      int acc = incl - sum;
-      if (r >= acc && r < incl) {
-        for (int i = 0; i < 4; ++i) {
-          if (r < acc + cnt[i]) {
-            sh_digit = 4 * tid + i;
-            sh_rank = r - acc;
-            break;
-          }
-          acc += cnt[i];
-        }
-      }
-    }
-    __syncthreads();
-    thr |= (uint32_t)sh_digit << shift;
-    r = sh_rank;
-    __syncthreads();
-  }
-  // 5. per-chunk counts of candidates below / equal to the threshold
-  auto tally = [&](uint32_t key, int ch) {
-    if (key < thr) atomicAdd(&less_ch[ch], 1);
-    else if (key == thr) atomicAdd(&eq_ch[ch], 1);
-  };
-  if (in_lds) {
-    for (int i = tid; i < ncand; i += kSelThreads) tally(ckey[i], cchunk[i]);
-  } else {
-    for (int o = tid; o < size; o += kSelThreads) {
-      const uint32_t key = keys[o];
-      if (lin_bin(key, lo, scale) == bstar) tally(key, o / kChunk);
-    }
-  }
-  __syncthreads();
-  // 6. exclusive prefixes over the node's chunks
-  int32_t* cc = C.chunk_cnt + ((size_t)pid * C.hist_slots + (size_t)node * L.cpn) * 2;
-  int base_l = 0, base_e = 0;
-  for (int g = 0; g < nch; g += kSelThreads) {
-    const int ch = g + tid;
-    const int l = ch < nch ? below_ch[ch] + less_ch[ch] : 0, e = ch < nch ? eq_ch[ch] : 0;
-    int sl, se;
-    const int xl = block_scan<kSelThreads>(l, wsum, &sl);
-    const int xe = block_scan<kSelThreads>(e, wsum, &se);
-    if (ch < nch) {
-      cc[2 * ch] = base_l + xl;
-      cc[2 * ch + 1] = base_e + xe;
-    }
-    base_l += sl;
-    base_e += se;
   }
   if (tid == 0) {
-    ns[1] = (int)thr;
-    ns[2] = r;
+    sh_cnt = 0;
+    sh_below = 0;
+    sh_min = 0xFFFFFFFFu;
+    sh_max = 0u;
   }
+  int all;
+  const int before = scan256(tot, wsum, &all);
+  const int rank = ns[9];
+  if (rank >= before && rank < before + tot) {
+    sh_bin = tid;
+    sh_before = before;
+    sh_base = pre;
+    sh_n = tot;
+  }
+  __syncthreads();
+  const int bin = sh_bin, base = sh_base;
+  int below = tid < bin ? pre : 0;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) below += __shfl_xor(below, o, 64);
+  if (lane == 0) atomicAdd(&sh_below, below);
+  uint32_t* cand = C.cand + (size_t)pid * C.nmax + start;
+  uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int o = c0 + tid + 256 * u;
+    const bool in = o < c1 && lin_bin(kv[u], lo, scale) == bin;
+    const uint64_t m = __ballot(in);
+    if (!m) continue;
+    // (the order inside a chunk is not used)
+    int at = 0;
+    if (lane == 0) at = atomicAdd(&sh_cnt, __popcll(m));
+    at = __builtin_amdgcn_readfirstlane(at);
+    if (in) {
+      const int i = base + at + __popcll(m & ((1ull << lane) - 1ull));
+      if (i < size) cand[i] = kv[u];
+      kmin = min(kmin, kv[u]);
+      kmax = max(kmax, kv[u]);
+    }
+  }
+  if (kmin <= kmax) {
+    atomicMin(&sh_min, kmin);
+    atomicMax(&sh_max, kmax);
+  }
+  __syncthreads();
+  int32_t* cc = C.chunk_cnt + ((size_t)pid * C.hist_slots + (size_t)node * L.cpn) * kChunkInts;
+  const int n = sh_n;
+  if (tid == 0) {
+    cc[kChunkInts * ch] = sh_below;
+    cc[kChunkInts * ch + 1] = base;
+    cc[kChunkInts * ch + 2] = (int32_t)sh_min;
+    cc[kChunkInts * ch + 3] = (int32_t)sh_max;
+  }
+  if (n <= kListed) {
+    if (tid == 0 && ch == 0) {
+      ns[1] = n;
+      ns[2] = rank - sh_before;
+      ns[11] = bin;
+    }
+    return;
+  }
+  // The same branch in all blocks of the node. The lists and chunk states are
+  // released before this block's arrival is counted; the block that finds all
+  // others arrived acquires them. No block waits for another.
+  __threadfence();
+  __syncthreads();
+  if (tid == 0) sh_last = atomicAdd(&ns[12], 1) == nch - 1;
+  __syncthreads();
+  if (!sh_last) return;
+  __threadfence();
+  node_select(ns, cand, cc, n, nch, rank - sh_before, sel);
 }
 
 // Stable partition of every node: the m_L smallest (key, position) pairs go
@@ -2912,7 +2982,129 @@ __global__ __launch_bounds__(kSelThreads) void split_select_kernel(Ctx C, LevelA
 // 16-position runs of consecutive threads start on different banks.
 __device__ __forceinline__ int scat_slot(int i) { return i + (i >> 4); }
 
+// Exact select among a node's at most kListed listed keys (the rank-th smallest)
+// by one chunk block: their bin is cut into 256 again, and the rank found by
+// counting among the at most 64 keys of its part, or, with more of them there
+// (ties, an end bin), by 8-bit radix passes. Gives the threshold, the number of
+// keys equal to it that go left (less one), and the numbers of keys below and
+// equal to it in the chunks before this one.
+struct ChunkSelect {
+  int hist[256];
+  int wsum[4];
+  uint32_t list[64];
+  int digit, rank, less, eq, nlist;
+};
+__device__ __forceinline__ void chunk_select(const Ctx& C, int pid, const int32_t* ns, int slot0,
+                                             ChunkSelect& sh, uint32_t* thr_out, int* need_eq,
+                                             int* less0, int* eq0) {
+  constexpr int R = kListed / 256;  // keys per thread
+  const int tid = threadIdx.x, lane = tid & 63, ch = blockIdx.x;
+  const int n = ns[1], start = ns[4], bin = ns[11];
+  const float lo = __int_as_float(ns[6]), scale = __int_as_float(ns[8]);
+  int rank = ns[2];
+  const uint32_t* cand = C.cand + (size_t)pid * C.nmax + start;
+  const int32_t* cc = C.chunk_cnt + ((size_t)pid * C.hist_slots + slot0 + ch) * kChunkInts;
+  uint32_t kr[R];
+#pragma unroll
+  for (int u = 0; u < R; ++u) {
+    const int i = tid + 256 * u;
+    kr[u] = i < n ? cand[i] : 0u;
+  }
+  const int base = cc[1];
+  if (tid == 0) {
+    sh.less = cc[0];
+    sh.eq = 0;
+    sh.nlist = 0;
+  }
+  sh.hist[tid] = 0;
+  __syncthreads();
+  // f(key, i) over the listed keys
+  auto each = [&](auto&& f) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+      if (256 * u < n) {  // uniform
+        if (tid + 256 * u < n) f(kr[u], tid + 256 * u);
+      }
+  };
+  // digit of the rank in hist (one entry a thread), the rank inside it
+  auto find = [&]() __attribute__((always_inline)) {
+    const int c = sh.hist[tid];
+    int tot;
+    const int before = scan256(c, sh.wsum, &tot);
+    if (rank >= before && rank < before + c) {
+      sh.digit = tid;
+      sh.rank = rank - before;
+    }
+    __syncthreads();
+    return sh.digit;
+  };
+  auto part_of = [&](uint32_t key) {
+    if (key >= 0xFF800000u) return 255;  // +inf, positive NaNs
+    if (key <= 0x007FFFFFu) return 0;    // -inf, negative NaNs
+    const float t = ((key_value(key) - lo) * scale - (float)bin) * 256.f;
+    return (int)fminf(fmaxf(t, 0.f), 255.f);
+  };
+  each([&](uint32_t key, int) { atomicAdd(&sh.hist[part_of(key)], 1); });
+  __syncthreads();
+  const int part = find();
+  const int want = sh.rank;
+  each([&](uint32_t key, int) {
+    if (part_of(key) != part) return;
+    const int i = atomicAdd(&sh.nlist, 1);
+    if (i < 64) sh.list[i] = key;
+  });
+  __syncthreads();
+  uint32_t thr = 0u;
+  const int nl = __builtin_amdgcn_readfirstlane(sh.nlist);
+  if (nl <= 64) {  // the same in every wavefront
+    const uint32_t key = lane < nl ? sh.list[lane] : 0xFFFFFFFFu;
+    int less = 0, eq = 0;
+    for (int j = 0; j < nl; ++j) {
+      const uint32_t kj = (uint32_t)__builtin_amdgcn_readlane((int)key, j);
+      less += kj < key;
+      eq += kj == key;
+    }
+    const uint64_t own = __ballot(lane < nl && want >= less && want < less + eq);
+    const int l = own ? __builtin_ctzll(own) : 0;
+    thr = (uint32_t)__builtin_amdgcn_readlane((int)key, l);
+    rank = want - __builtin_amdgcn_readlane(less, l);
+  } else {
+    for (int shift = 24; shift >= 0; shift -= 8) {
+      sh.hist[tid] = 0;
+      __syncthreads();
+      each([&](uint32_t key, int) {
+        if (shift == 24 || (key >> (shift + 8)) == (thr >> (shift + 8)))
+          atomicAdd(&sh.hist[(key >> shift) & 255u], 1);
+      });
+      __syncthreads();
+      thr |= (uint32_t)find() << shift;
+      rank = sh.rank;
+    }
+  }
+  // the listed keys of the chunks before this one
+  int lt = 0, eq = 0;
+  each([&](uint32_t key, int i) {
+    lt += i < base && key < thr;
+    eq += i < base && key == thr;
+  });
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    lt += __shfl_xor(lt, o, 64);
+    eq += __shfl_xor(eq, o, 64);
+  }
+  if (lane == 0) {
+    atomicAdd(&sh.less, lt);
+    atomicAdd(&sh.eq, eq);
+  }
+  __syncthreads();
+  *thr_out = thr;
+  *need_eq = rank + 1;
+  *less0 = sh.less;
+  *eq0 = sh.eq;
+}
+
 __global__ __launch_bounds__(256) void split_scatter_kernel(Ctx C, LevelArgs L) {
+  __shared__ ChunkSelect sel;
   __shared__ int wsum[4];
   __shared__ uint32_t skey[kChunk + kChunk / 16];
   __shared__ int32_t srow[kChunk + kChunk / 16];
@@ -2937,11 +3129,7 @@ __global__ __launch_bounds__(256) void split_scatter_kernel(Ctx C, LevelArgs L) 
     }
     return;
   }
-  const uint32_t thr = (uint32_t)ns[1];
-  const int need_eq = ns[2] + 1, mL = ns[3];
-  const int32_t* cc =
-      C.chunk_cnt + ((size_t)pid * C.hist_slots + (size_t)node * L.cpn + blockIdx.x) * 2;
-  const int less0 = cc[0], eq0 = cc[1];
+  const int mL = ns[3];
   const uint32_t* keys = C.keys + (size_t)pid * C.nmax;
   // coalesced loads of the chunk's keys and rows into LDS
 #pragma unroll
@@ -2951,6 +3139,17 @@ __global__ __launch_bounds__(256) void split_scatter_kernel(Ctx C, LevelArgs L) 
       skey[scat_slot(i)] = keys[start + c0 + i];
       srow[scat_slot(i)] = L.first ? start + c0 + i : idx_in[start + c0 + i];
     }
+  }
+  uint32_t thr = (uint32_t)ns[1];
+  int less0 = 0, eq0 = 0, need_eq = ns[2] + 1;
+  if (!ns[10]) {
+    chunk_select(C, pid, ns, node * L.cpn, sel, &thr, &need_eq, &less0, &eq0);
+  } else if (ns[7] > 1) {
+    const int32_t* cc =
+        C.chunk_cnt +
+        ((size_t)pid * C.hist_slots + (size_t)node * L.cpn + blockIdx.x) * kChunkInts;
+    less0 = cc[0];
+    eq0 = cc[1];
   }
   __syncthreads();
   // Each thread owns kPer consecutive positions (the scan order).
@@ -3602,6 +3801,7 @@ hipError_t launch_cluster(const Prob& P, const void* q, const void* k, const voi
   C.keys = (uint32_t*)(ws + W.keys);
   C.node_state = (int32_t*)(ws + W.node_state);
   C.hist = (uint32_t*)(ws + W.hist);
+  C.cand = (uint32_t*)(ws + W.cand);
   C.chunk_cnt = (int32_t*)(ws + W.chunk_cnt);
   C.max_nodes = W.max_big_nodes;
   C.hist_slots = W.hist_slots;
@@ -3765,7 +3965,7 @@ hipError_t launch_cluster(const Prob& P, const void* q, const void* k, const voi
       hipLaunchKernelGGL(split_keys_kernel<0>, kgrid, dim3(256), 0, st, C, L);
     CA_CHECK();
     if (cpn > 1) {  // nodes of one chunk are selected with their keys
-      hipLaunchKernelGGL(split_select_kernel, dim3(1 << l, 2 * BH), dim3(kSelThreads), 0, st, C, L);
+      hipLaunchKernelGGL(split_bins_kernel, kgrid, dim3(256), 0, st, C, L);
       CA_CHECK();
     }
     hipLaunchKernelGGL(split_scatter_kernel, dim3(cpn, 1 << l, 2 * BH), dim3(256), 0, st, C, L);

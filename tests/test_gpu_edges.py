@@ -86,6 +86,36 @@ def test_split_tail_edges(dt, n, d, c, xf):
     _cluster_parity(dt, n, d, c, xf)
 
 
+# Levels of several chunks (4,096 tokens each): one token into the next chunk,
+# thresholds in runs of equal keys, all keys equal, and keys that one outlier
+# crowds into a bin (more of them than the chunk blocks select among by themselves).
+@pytest.mark.parametrize("kind", ["normal", "ties", "run", "const", "outlier"])
+@pytest.mark.parametrize("n", [4097, 8191, 12289, 30000])
+def test_split_chunk_edges(n, kind):
+    import numpy as np
+    import torch
+    import paper_2608_26965_amd as ca
+    from oracle import ref
+    d, c = 8, 64
+    X = np.random.default_rng(n).standard_normal((2, n, d)).astype(np.float32)
+    if kind == "ties":
+        X = np.round(X)
+    elif kind == "run":
+        X[np.random.default_rng(1).random(X.shape) < 0.4] = 0.25
+    elif kind == "const":
+        X[:] = 0.5
+    elif kind == "outlier":
+        X = X * 1e-5
+        X[:, n // 3] = 1e6
+    p = ca.Problem(1, 1, n, n, d, c, c, torch.float32, "none")
+    q, k = (torch.from_numpy(x[None, None]).cuda() for x in X)
+    r = ca.cluster(p, q, k, k)
+    for x, side in zip(X, ("q", "k")):
+        perm, cid, _ = ref.split(x.astype(np.float64), c)
+        assert np.array_equal(r["perm_" + side][0].cpu().numpy(), perm)
+        assert np.array_equal(r["cid_" + side][0].cpu().numpy(), cid)
+
+
 # Top-k of rows of 2049-8192 scores: at the edges of the number of groups the
 # filter makes (256 to 2048, at least twice k of them), rows that leave part of
 # a wavefront's range empty, and the inputs it hands over (ties, runs of equal
