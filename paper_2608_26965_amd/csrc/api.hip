@@ -211,7 +211,10 @@ void plan_workspace(const Prob& P, Workspace* W) {
   W->idx0 = take(2 * BH * nmax * 4);
   W->idx1 = take(2 * BH * nmax * 4);
   W->keys = take(2 * BH * nmax * 4);
-  W->mom_part = take(2 * BH * W->nblk_mom * (d * d + d) * 4);
+  // The moments' partial sums are done with before the split lists its keys.
+  const size_t mom = 2 * BH * W->nblk_mom * (d * d + d) * 4, cand = 2 * BH * nmax * 4;
+  W->mom_part = take(bigmax > 0 && cand > mom ? cand : mom);
+  W->cand = W->mom_part;
   W->mats = take(BH * kMats * d * d * 4);
   W->vecs = take(BH * kVecs * d * 4);
   W->inv_q = take(BH * P.nq * 4);
@@ -219,7 +222,6 @@ void plan_workspace(const Prob& P, Workspace* W) {
   W->wops = take(BH * 3 * 2 * d * d * 2);
   W->node_state = take(2 * BH * W->max_big_nodes * kNodeInts * 4);
   W->hist = take(2 * BH * W->hist_slots * kBins * 4);
-  W->cand = take(2 * BH * nmax * 4);
   W->chunk_cnt = take(2 * BH * W->hist_slots * kChunkInts * 4);
   W->dirs = take(basic ? 2 * 2 * BH * W->max_big_nodes * d * 4 : 0);
   W->scores = take(BH * P.nqc * P.nkc * 4);
