@@ -96,34 +96,37 @@ __global__ __launch_bounds__(256) void comp_stage_kernel(const float* __restrict
   }
 }
 
-// Centroids per LDS stage: half a tile, so that two stages and the masks take
-// 42 KB at d = 64 and 75 KB at d = 128: three and two workgroups a CU. (Whole
-// tiles at d = 64 took 75 KB.)
-constexpr int kCompStage = kCompTile / 2;
+// Centroids per LDS stage, which share one reference of the online softmax (the
+// probabilities are rounded to bf16 against it): a whole tile of 128 at d = 64,
+// half a tile at d = 128; two stages take 66 KB either way.
+template <int D>
+constexpr int comp_stage_cents() {
+  return D == 128 ? kCompTile / 2 : kCompTile;
+}
 
 // Query clusters per workgroup. All query clusters of a head stream the same
 // centroid tiles and differ only in the selection mask, so clusters of 64 share
 // a workgroup of four wavefronts two by two, with a mask and a bias row each.
 // What bounds the kernel is the latency of a stage (copy, logits, softmax,
 // value product, three barriers), hence the wavefronts in flight: with a
-// workgroup of two wavefronts per cluster of 64 and whole-tile stages a SIMD
-// held one; now three at d = 64 and two at d = 128. 8 heads, 131,072 tokens,
-// clusters of 64 x 128, k = 64 of 1,024: 695 -> 439 us
-// (query clusters of 128, one a workgroup: 466 -> 403); 40 heads, 20,000
-// tokens, d = 128, clusters of 64, k = 40 of 313: 418 -> 283.
+// workgroup of two wavefronts per cluster of 64 a SIMD held one, now two.
+// 8 heads, 131,072 tokens, clusters of 64 x 128, k = 64 of 1,024: 674 ->
+// 429 us; 40 heads, 20,000 tokens, d = 128, clusters of 64, k = 40 of 313:
+// 438 -> 308. (Half-tile stages at d = 64, three wavefronts a SIMD, took 396 us
+// on the former, but give each half a reference of its own: other roundings.)
 template <int CQ>
 constexpr int comp_clusters() {
   return CQ == 64 ? 2 : 1;
 }
 
 // Waves per SIMD (the second launch bound): as many workgroups as the LDS
-// (two stages and the selection masks) allows, capped at three waves per SIMD.
+// (two stages and the selection masks) allows, capped at two waves per SIMD.
 template <int D, int CQ, int NQ>
 constexpr int comp_waves_per_simd() {
   constexpr int nw = NQ * CQ / 32;
-  constexpr int lds = 2 * kCompStage * (4 * D + 4 + 4 * NQ) + kMaskWords * 4;
+  constexpr int lds = comp_stage_cents<D>() * (2 * (4 * D + 4) + 4 * NQ) + kMaskWords * 4;
   constexpr int by_lds = (160 * 1024) / lds;
-  constexpr int by_waves = 12 / nw;
+  constexpr int by_waves = 8 / nw;
   constexpr int blocks = by_lds < by_waves ? (by_lds < 1 ? 1 : by_lds) : by_waves;
   return blocks * nw / 4 < 1 ? 1 : blocks * nw / 4;
 }
@@ -140,7 +143,7 @@ __global__ __launch_bounds__(CQ * 2 * NQ, (comp_waves_per_simd<D, CQ, NQ>())) vo
   constexpr int NW = NQ * QC;
   constexpr int T = NW * 64;
   constexpr int CT = kCompTile;    // centroids per staged tile
-  constexpr int HC = kCompStage;   // centroids per LDS stage
+  constexpr int HC = comp_stage_cents<D>();   // centroids per LDS stage
   constexpr int SUB = CT / HC;                // stages per tile
   constexpr int MT = HC / 32;
   constexpr int KS = D / 16;
@@ -255,14 +258,15 @@ __global__ __launch_bounds__(CQ * 2 * NQ, (comp_waves_per_simd<D, CQ, NQ>())) vo
     wait_lgkm();
     raw_barrier();  // selmask complete
 
-    // A stage is live if it holds at least one unselected centroid.
-    auto tile_live = [&](int g) {
+    // A stage is live for a cluster if it holds a centroid that the cluster
+    // did not select. A cluster's wavefronts sit out a stage that is live for
+    // the other one only.
+    auto live = [&](int g, int c) {
       int any = 0;
       const int e0 = g * (HC / 32);
       for (int e = e0; e < e0 + HC / 32 && e < nwords; ++e) {
         const uint32_t wmask = e == nwords - 1 && (nkc & 31) ? (1u << (nkc & 31)) - 1u : ~0u;
-#pragma unroll
-        for (int c = 0; c < NQ; ++c) any |= (~selmask[c * MWORDS + e] & wmask) != 0u;
+        any |= (~selmask[c * MWORDS + e] & wmask) != 0u;
       }
       return __builtin_amdgcn_readfirstlane(any) != 0;
     };
@@ -285,7 +289,11 @@ __global__ __launch_bounds__(CQ * 2 * NQ, (comp_waves_per_simd<D, CQ, NQ>())) vo
       else
         wait_vmcnt<0>();
       raw_barrier();
-      if (tile_live(g)) {
+      const bool own = live(g, sub);
+      bool any = own;
+#pragma unroll
+      for (int c = 1; c < NQ; ++c) any = any || live(g, (sub + c) % NQ);
+      if (any) {  // the same in every wavefront
         const char* ks = smem + S * STAGE;
         const char* vs = ks + KBYTES;
         const float* srow = (const float*)(smem + S * STAGE + KBYTES + VBYTES);
@@ -299,76 +307,80 @@ __global__ __launch_bounds__(CQ * 2 * NQ, (comp_waves_per_simd<D, CQ, NQ>())) vo
           cbias[c][t] = sel ? -INFINITY : srow[t];
         }
         f32x16 sacc[MT];
+        if (own) {
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
+          for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
-          for (int r = 0; r < 16; ++r) sacc[mt][r] = 0.f;
+            for (int r = 0; r < 16; ++r) sacc[mt][r] = 0.f;
 #pragma unroll
-          for (int kk = 0; kk < KS; ++kk) {
-            const bf16x8 av = *(const bf16x8*)(ks + 32 * mt * KROW + koff[kk]);
-            sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, qreg[kk], sacc[mt], 0, 0, 0);
+            for (int kk = 0; kk < KS; ++kk) {
+              const bf16x8 av = *(const bf16x8*)(ks + 32 * mt * KROW + koff[kk]);
+              sacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, qreg[kk], sacc[mt], 0, 0, 0);
+            }
           }
         }
         wait_lgkm();
-        raw_barrier();  // bias row final
-        // logits in log2 units: scale*log2e*q.kbar + log2|b|. The bias of
-        // accumulator r of row tile mt is bias[32 mt + (r & 7) + 16 (r >> 3) + 8 h]:
-        // two runs of 8 consecutive entries, read as four 16-byte loads.
-        float mx = -INFINITY;
+        raw_barrier();  // bias rows final
+        if (own) {
+          // logits in log2 units: scale*log2e*q.kbar + log2|b|. The bias of
+          // accumulator r of row tile mt is bias[32 mt + (r & 7) + 16 (r >> 3) + 8 h]:
+          // two runs of 8 consecutive entries, read as four 16-byte loads.
+          float mx = -INFINITY;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          float bv[16];
+          for (int mt = 0; mt < MT; ++mt) {
+            float bv[16];
 #pragma unroll
-          for (int hh = 0; hh < 2; ++hh) {
-            const float4 b0v = *(const float4*)&bias[32 * mt + 16 * hh + 8 * h];
-            const float4 b1v = *(const float4*)&bias[32 * mt + 16 * hh + 8 * h + 4];
-            bv[8 * hh + 0] = b0v.x, bv[8 * hh + 1] = b0v.y, bv[8 * hh + 2] = b0v.z, bv[8 * hh + 3] = b0v.w;
-            bv[8 * hh + 4] = b1v.x, bv[8 * hh + 5] = b1v.y, bv[8 * hh + 6] = b1v.z, bv[8 * hh + 7] = b1v.w;
+            for (int hh = 0; hh < 2; ++hh) {
+              const float4 b0v = *(const float4*)&bias[32 * mt + 16 * hh + 8 * h];
+              const float4 b1v = *(const float4*)&bias[32 * mt + 16 * hh + 8 * h + 4];
+              bv[8 * hh + 0] = b0v.x, bv[8 * hh + 1] = b0v.y, bv[8 * hh + 2] = b0v.z, bv[8 * hh + 3] = b0v.w;
+              bv[8 * hh + 4] = b1v.x, bv[8 * hh + 5] = b1v.y, bv[8 * hh + 6] = b1v.z, bv[8 * hh + 7] = b1v.w;
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const float x = __builtin_fmaf(sacc[mt][r], sl2, bv[r]);
+              sacc[mt][r] = x;
+              mx = fmaxf(mx, x);
+            }
           }
+          mx = fmaxf(mx, wave_xor32(mx));
+          if (__builtin_amdgcn_ballot_w64(mx > m_run + kLazy)) {
+            const float m_new = fmaxf(m_run, mx);
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+            l_run *= alpha;
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const float x = __builtin_fmaf(sacc[mt][r], sl2, bv[r]);
-            sacc[mt][r] = x;
-            mx = fmaxf(mx, x);
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
+            m_run = m_new;
           }
-        }
-        mx = fmaxf(mx, wave_xor32(mx));
-        if (__builtin_amdgcn_ballot_w64(mx > m_run + kLazy)) {
-          const float m_new = fmaxf(m_run, mx);
-          const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-          l_run *= alpha;
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
-          m_run = m_new;
-        }
-        // A query that has seen no live centroid yet has m_run = -inf and only
-        // -inf logits: offset by 0 so that they give 0, not NaN.
-        const float m_use = m_run == -INFINITY ? 0.f : m_run;
-        float lsum = 0.f;
-        bf16x8 pb[MT][2];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-          for (int s2 = 0; s2 < 2; ++s2) {
-            float pv[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-              pv[j] = __builtin_amdgcn_exp2f(sacc[mt][8 * s2 + j] - m_use);
-            pb[mt][s2] = pack8(pv);
-            lsum = sum8(pb[mt][s2], lsum);
-          }
-        l_run += lsum;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
+          // A query that has seen no live centroid yet has m_run = -inf and only
+          // -inf logits: offset by 0 so that they give 0, not NaN.
+          const float m_use = m_run == -INFINITY ? 0.f : m_run;
+          float lsum = 0.f;
+          bf16x8 pb[MT][2];
 #pragma unroll
           for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int s2 = 0; s2 < 2; ++s2) {
-              const bf16x8 av = *(const bf16x8*)(vs + 32 * dt * VROW + voff[mt][s2]);
-              oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, pb[mt][s2], oacc[dt], 0, 0, 0);
+              float pv[8];
+#pragma unroll
+              for (int j = 0; j < 8; ++j)
+                pv[j] = __builtin_amdgcn_exp2f(sacc[mt][8 * s2 + j] - m_use);
+              pb[mt][s2] = pack8(pv);
+              lsum = sum8(pb[mt][s2], lsum);
             }
+          l_run += lsum;
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+              for (int s2 = 0; s2 < 2; ++s2) {
+                const bf16x8 av = *(const bf16x8*)(vs + 32 * dt * VROW + voff[mt][s2]);
+                oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, pb[mt][s2], oacc[dt], 0, 0, 0);
+              }
+        }
       }
       wait_lgkm();
       raw_barrier();  // every wave is done with this stage

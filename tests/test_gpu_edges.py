@@ -184,3 +184,63 @@ def test_compensation_many_key_clusters():
                               lse[0, :n][np.argsort(perm)].astype(np.float64), 1 / 8)
     assert np.abs(G.host(out)[0, 0] - o_w).max() <= G.TOL["bf16"]
     assert np.abs(G.host(lse_out)[0] - l_w).max() <= 1e-4 * np.abs(l_w).max()
+
+
+def _compensate_rows(dt, d, cq, Q, kbar, vbar, lists, k, lse=-1e4):
+    """ca.compensate of one head on rows Q [n, d] in cluster order (identity
+    permutation), centroids kbar, vbar [nkc, d] of full clusters of 64 keys and
+    a sparse part of zeros with weight e^lse: (out [n, d], lse [n])."""
+    import numpy as np
+    import torch
+    import paper_2608_26965_amd as ca
+    from tests import gpu_util as G
+    n, nkc = Q.shape[0], kbar.shape[0]
+    p = ca.Problem(1, 1, n, nkc * 64, d, cq, 64, G.tdtype(dt))
+    perm = np.arange(n, dtype=np.int32)[None]
+    op = torch.zeros(1, p.nq_pad, d, dtype=G.tdtype(dt), device="cuda")
+    out, l = ca.compensate(
+        p, G.permuted_rows(Q[None], perm, cq, G.tdtype(dt)), G.dev(kbar[None]), G.dev(vbar[None]),
+        torch.full((1, nkc), 64, dtype=torch.int32, device="cuda"), G.dev(lists[None], torch.int32), k, op,
+        torch.full((1, p.nq_pad), lse, device="cuda"), G.dev(perm, torch.int32), scale=1.0,
+        want_lse=True)
+    return G.host(out)[0, 0], G.host(l)[0]
+
+
+# The bf16 compensation at d = 64 has one softmax reference per tile of 128
+# centroids (the largest logit of the tile), and probabilities rounded to bf16
+# against it. The logits are a and b > a in the two halves of one tile, so the
+# probabilities are bf16(e^(a - b)) and 1; against a as the reference they would
+# be 1 and bf16(e^(b - a)), whose rounding moves the log-sum by over 1e-3. The
+# tolerance covers logits and log-sums in fp32.
+@pytest.mark.parametrize("cq,n", [(64, 64), (64, 128), (128, 128)])
+def test_compensation_tile_reference(cq, n):
+    import numpy as np
+    from synth import bf16_round
+    d, nkc = 64, 192
+    step = np.float32(1.390625)  # b - a, in bf16
+    Q = np.zeros((n, d), np.float32)
+    Q[:, 0] = 1
+    kbar = np.zeros((nkc, d), np.float32)
+    kbar[64:128, 0] = step
+    lists = np.tile(np.arange(128, 192), (n // cq, 1))
+    _, lse = _compensate_rows("bf16", d, cq, Q, kbar, np.ones((nkc, d), np.float32), lists, 64)
+    up, down = (bf16_round(np.full(1, np.exp(s), np.float32))[0] for s in (step, -step))
+    assert abs(up / np.exp(np.float64(step)) - 1) > 1e-3
+    want = step + np.log(64.0) + np.log(64 * np.float64(down) + 64)
+    assert np.abs(lse - want).max() <= 1e-5
+
+
+def test_compensation_stage_of_one_partner():
+    """Two query clusters share a workgroup's centroid tiles: a tile whose
+    centroids one of them has all selected takes no part in that one's result,
+    even where a value centroid is infinite."""
+    import numpy as np
+    rng = np.random.default_rng(2)
+    for d in (64, 128):
+        Q = rng.standard_normal((128, d)).astype(np.float32)
+        kbar, vbar = (rng.standard_normal((384, d)).astype(np.float32) for _ in range(2))
+        lists = np.stack([np.arange(128), np.arange(200, 328)])
+        want, _ = _compensate_rows("bf16", d, 64, Q, kbar, vbar, lists, 128)
+        vbar[5] = np.inf
+        got, _ = _compensate_rows("bf16", d, 64, Q, kbar, vbar, lists, 128)
+        assert np.array_equal(got[:64], want[:64])
