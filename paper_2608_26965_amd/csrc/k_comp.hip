@@ -430,27 +430,37 @@ struct CentKeys {
   int nkc, d, ntile, lane;
   float scale;
 
+  // bit r: centroid 16 T + 4 (lane / 16) + r exists and is not selected
+  __device__ __forceinline__ uint32_t skipped(int T) const {
+    const int b0 = 16 * T + 4 * (lane >> 4);
+    if (b0 >= nkc) return 0u;
+    const uint32_t on = ~selmask[b0 >> 5] >> (b0 & 31);
+    return nkc - b0 < 4 ? on & ((1u << (nkc - b0)) - 1u) : on;
+  }
   __device__ __forceinline__ void rows(int T, f32x4 (&kf)[DP / 16]) const {
     const int b = min(16 * T + (lane & 15), nkc - 1);  // rows past the end are masked
     f32_load_rows<DP>(ck + (size_t)b * d, d, lane >> 4, kf);
   }
   __device__ __forceinline__ void vals(int T, f32x4 (&vf)[DP / 16]) const {
+    // zero where the weight is zero (a selected centroid's value may be infinite)
+    const uint32_t on = skipped(T);
 #pragma unroll
     for (int t = 0; t < DP / 16; ++t) {
       const int dim = 16 * t + (lane & 15);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int b = 16 * T + 4 * (lane >> 4) + r;
-        vf[t][r] = dim < d && b < nkc ? cv[(size_t)b * d + dim] : 0.f;
+        const int b = min(16 * T + 4 * (lane >> 4) + r, nkc - 1);
+        const float x = dim < d ? cv[(size_t)b * d + dim] : 0.f;
+        vf[t][r] = (on >> r) & 1u ? x : 0.f;
       }
     }
   }
   __device__ __forceinline__ void logits(int T, f32x4& s) const {
+    const uint32_t on = skipped(T);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int b = 16 * T + 4 * (lane >> 4) + r;
-      const bool on = b < nkc && !((selmask[b >> 5] >> (b & 31)) & 1u);
-      s[r] = on ? s[r] * scale + logf((float)cnt[on ? b : 0]) : -INFINITY;
+      const bool o = (on >> r) & 1u;
+      s[r] = o ? s[r] * scale + logf((float)cnt[o ? 16 * T + 4 * (lane >> 4) + r : 0]) : -INFINITY;
     }
   }
 };

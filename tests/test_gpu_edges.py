@@ -244,3 +244,19 @@ def test_compensation_stage_of_one_partner():
         vbar[5] = np.inf
         got, _ = _compensate_rows("bf16", d, 64, Q, kbar, vbar, lists, 128)
         assert np.array_equal(got[:64], want[:64])
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_f32_compensation_selected_infinite_value(d):
+    """A selected key cluster is left out of the fp32 compensation, also where
+    its value centroid is infinite."""
+    import numpy as np
+    rng = np.random.default_rng(3)
+    Q = rng.standard_normal((40, d)).astype(np.float32)
+    kbar, vbar = (rng.standard_normal((77, d)).astype(np.float32) for _ in range(2))
+    lists = np.sort(rng.choice(77, (2, 9)), axis=1)
+    lists[:, 0] = 3
+    want, _ = _compensate_rows("f32", d, 32, Q, kbar, vbar, lists, 9)
+    vbar[3] = -np.inf
+    got, _ = _compensate_rows("f32", d, 32, Q, kbar, vbar, lists, 9)
+    assert np.array_equal(got, want)
