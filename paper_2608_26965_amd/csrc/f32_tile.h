@@ -21,6 +21,8 @@
 // clusters, one head; now 24 + 13 us and 13 + 11 us.
 #pragma once
 
+#include <type_traits>
+
 #include "common.h"
 
 namespace ca {
@@ -37,10 +39,35 @@ template <int DP>
 struct F32Tile {
   static constexpr int NJ = DP / 16;              // 16-wide tiles of the head dimension
   static constexpr int TPS = DP == 128 ? 2 : 4;   // key tiles per step (registers)
-  static constexpr int NW = DP == 128 ? 4 : 8;    // wavefronts of a workgroup
-  static constexpr int NT = 64 * NW;
+  static constexpr int NW = DP == 128 ? 4 : 8;    // wavefronts of a workgroup, at most
   static constexpr int QP = 17;                   // queries per LDS row, padded
 };
+
+// Waves per SIMD of the kernels (their second launch bound): 256 registers.
+constexpr int kF32Waves = 2;
+
+// Calls f(std::integral_constant<int, NW>) with the number of wavefronts of a
+// workgroup, for ntile tiles of 16 keys and a launch of wgs workgroups: where
+// there is more than one workgroup a CU (256 of them), as many as get tiles,
+// since others only keep registers from the next workgroup; else all, which
+// then share the prologue and the output rows. 8 heads of 16,384 queries at
+// d = 64: attention on one tile 228 us with 8 wavefronts, 62 with one;
+// compensation with 8 tiles 424 and 157 (two). One head of 1,024 queries (64
+// workgroups), compensation with one tile: 20 us with 8 wavefronts, 23 with
+// one. Which wavefront has which tiles does not depend on their number, so
+// neither do the results.
+template <int DP, typename F>
+void f32_wavefronts(int ntile, int64_t wgs, F&& f) {
+  constexpr int TPS = F32Tile<DP>::TPS, NW = F32Tile<DP>::NW;
+  if (wgs > 256 && ntile <= TPS)
+    f(std::integral_constant<int, 1>{});
+  else if (wgs > 256 && ntile <= 2 * TPS)
+    f(std::integral_constant<int, 2>{});
+  else if (NW == 4 || (wgs > 256 && ntile <= 4 * TPS))
+    f(std::integral_constant<int, 4>{});
+  else
+    f(std::integral_constant<int, NW>{});
+}
 
 template <int DP>
 struct F32State {
@@ -64,11 +91,13 @@ __device__ __forceinline__ void f32_load_rows(const float* row, int d, int g,
 //   src.rows(T, kf)   the K operand of tile T (lane: key l % 16)
 //   src.vals(T, vf)   the V^T operand (lane: dim l % 16, keys 4 g .. 4 g + 3)
 //   src.logits(T, s)  scales the products and masks keys (-inf)
+//   src.mask_vals(T, vf)  clears values of masked keys that may not be finite
+//                     (late, so that the products above do not wait for them)
 // take any T; tiles at or past src.ntile are all masked.
-template <int DP, typename Src>
+template <int DP, int NW, typename Src>
 __device__ __forceinline__ void f32_online(const Src& src, const f32x4 (&qf)[F32Tile<DP>::NJ],
                                            int w, F32State<DP>& st) {
-  constexpr int NJ = F32Tile<DP>::NJ, TPS = F32Tile<DP>::TPS, NW = F32Tile<DP>::NW;
+  constexpr int NJ = F32Tile<DP>::NJ, TPS = F32Tile<DP>::TPS;
   st.m = -INFINITY;
   st.l = 0.f;
 #pragma unroll
@@ -123,6 +152,8 @@ __device__ __forceinline__ void f32_online(const Src& src, const f32x4 (&qf)[F32
         st.l += s[u][r];
       }
 #pragma unroll
+    for (int u = 0; u < TPS; ++u) src.mask_vals(t0 + u, vf[u]);
+#pragma unroll
     for (int u = 0; u < TPS; ++u)
 #pragma unroll
       for (int r = 0; r < 4; ++r)
@@ -135,20 +166,20 @@ __device__ __forceinline__ void f32_online(const Src& src, const f32x4 (&qf)[F32
 }
 
 // LDS of the merge of the wavefronts' states
-template <int DP>
+template <int DP, int NW>
 struct F32Merge {
-  float o[F32Tile<DP>::NW][DP][F32Tile<DP>::QP];
-  float f[F32Tile<DP>::NW][16];  // weight of wavefront w's part for a query
-  float m[F32Tile<DP>::NW][16], l[F32Tile<DP>::NW][16];
+  float o[NW][DP][F32Tile<DP>::QP];
+  float f[NW][16];               // weight of wavefront w's part for a query
+  float m[NW][16], l[NW][16];
   float mx[16], sum[16];         // reference and sum of a query over all parts
 };
 
 // Merges the wavefronts' states: afterwards query q's sum of exponentials is
 // sum[q] against the reference mx[q] (sum 0: no key), and its output before
 // the division is sum_w f[w][q] o[w][t][q] (f32_merged).
-template <int DP>
-__device__ __forceinline__ void f32_merge(F32Merge<DP>& M, const F32State<DP>& st, int w, int lane) {
-  constexpr int NJ = F32Tile<DP>::NJ, NW = F32Tile<DP>::NW;
+template <int DP, int NW>
+__device__ __forceinline__ void f32_merge(F32Merge<DP, NW>& M, const F32State<DP>& st, int w, int lane) {
+  constexpr int NJ = F32Tile<DP>::NJ;
   const int q = lane & 15, g = lane >> 4;
 #pragma unroll
   for (int j = 0; j < NJ; ++j)
@@ -177,11 +208,11 @@ __device__ __forceinline__ void f32_merge(F32Merge<DP>& M, const F32State<DP>& s
   __syncthreads();
 }
 
-template <int DP>
-__device__ __forceinline__ float f32_merged(const F32Merge<DP>& M, int q, int t) {
+template <int DP, int NW>
+__device__ __forceinline__ float f32_merged(const F32Merge<DP, NW>& M, int q, int t) {
   float x = 0.f;
 #pragma unroll
-  for (int i = 0; i < F32Tile<DP>::NW; ++i) x += M.f[i][q] * M.o[i][t][q];
+  for (int i = 0; i < NW; ++i) x += M.f[i][q] * M.o[i][t][q];
   return x;
 }
 

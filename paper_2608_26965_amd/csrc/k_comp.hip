@@ -442,18 +442,23 @@ struct CentKeys {
     f32_load_rows<DP>(ck + (size_t)b * d, d, lane >> 4, kf);
   }
   __device__ __forceinline__ void vals(int T, f32x4 (&vf)[DP / 16]) const {
-    // zero where the weight is zero (a selected centroid's value may be infinite)
-    const uint32_t on = skipped(T);
 #pragma unroll
     for (int t = 0; t < DP / 16; ++t) {
       const int dim = 16 * t + (lane & 15);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int b = min(16 * T + 4 * (lane >> 4) + r, nkc - 1);
-        const float x = dim < d ? cv[(size_t)b * d + dim] : 0.f;
-        vf[t][r] = (on >> r) & 1u ? x : 0.f;
+        vf[t][r] = dim < d ? cv[(size_t)b * d + dim] : 0.f;
       }
     }
+  }
+  // zero where the weight is zero (a selected centroid's value may be infinite)
+  __device__ __forceinline__ void mask_vals(int T, f32x4 (&vf)[DP / 16]) const {
+    const uint32_t on = skipped(T);
+#pragma unroll
+    for (int t = 0; t < DP / 16; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) vf[t][r] = (on >> r) & 1u ? vf[t][r] : 0.f;
   }
   __device__ __forceinline__ void logits(int T, f32x4& s) const {
     const uint32_t on = skipped(T);
@@ -466,8 +471,8 @@ struct CentKeys {
 };
 
 // fp32 path: one workgroup per 16 queries of a cluster (f32_tile.h).
-template <int DP>
-__global__ __launch_bounds__(F32Tile<DP>::NT) void comp_f32_kernel(
+template <int DP, int NW>
+__global__ __launch_bounds__(64 * NW, kF32Waves) void comp_f32_kernel(
     const float* __restrict__ qp, const float* __restrict__ cent_k,
     const float* __restrict__ cent_v, const int32_t* __restrict__ count_k,
     const int32_t* __restrict__ lists, const int32_t* __restrict__ lens, int nq, int H, int nqc,
@@ -475,8 +480,8 @@ __global__ __launch_bounds__(F32Tile<DP>::NT) void comp_f32_kernel(
     const float* __restrict__ lse_s,
     const int32_t* __restrict__ perm_q, float* __restrict__ out, float* __restrict__ lse_out,
     Lay lo) {
-  constexpr int NT = F32Tile<DP>::NT;
-  __shared__ F32Merge<DP> M;
+  constexpr int NT = 64 * NW;
+  __shared__ F32Merge<DP, NW> M;
   __shared__ uint32_t selmask[kMaskWords];
   __shared__ float ws[16], wc[16];  // weights of the sparse part and of the merged centroid part
   __shared__ size_t orow[16];
@@ -505,8 +510,8 @@ __global__ __launch_bounds__(F32Tile<DP>::NT) void comp_f32_kernel(
     const CentKeys<DP> src{cent_k + (size_t)bh * nkc * d, cent_v + (size_t)bh * nkc * d,
                            count_k + (size_t)bh * nkc, selmask, nkc, d, ntile, lane, scale};
     F32State<DP> st;
-    f32_online<DP>(src, qf, w, st);
-    f32_merge<DP>(M, st, w, lane);
+    f32_online<DP, NW>(src, qf, w, st);
+    f32_merge<DP, NW>(M, st, w, lane);
   }
   if (tid < nrow) {
     const int prow = a * cq + q0 + tid;
@@ -530,7 +535,7 @@ __global__ __launch_bounds__(F32Tile<DP>::NT) void comp_f32_kernel(
   for (int e = tid; e < nrow * d; e += NT) {
     const int q = e / d, t = e - q * d;
     float x = ws[q] * op[(qrow0 + q0) * d + e];
-    if (do_comp) x += wc[q] * f32_merged<DP>(M, q, t);
+    if (do_comp) x += wc[q] * f32_merged<DP, NW>(M, q, t);
     out[orow[q] + t] = x;
   }
 }
@@ -601,11 +606,16 @@ hipError_t launch_comp(const Prob& P, const void* qp, const float* cent_k, const
     return hipErrorInvalidValue;
   }
   const dim3 grid(P.nqc * ((P.cq + 15) / 16), P.BH);
-#define CA_COMP_F32(DP)                                                                       \
-  hipLaunchKernelGGL(comp_f32_kernel<DP>, grid, dim3(F32Tile<DP>::NT), 0, st,                 \
-                     (const float*)qp, cent_k, cent_v, count_k, lists, lens, P.nq, P.H, P.nqc, \
-                     P.nkc, P.cq, P.d, k, scale, enable, (const float*)op, lse, perm_q,       \
-                     (float*)out, lse_out, P.lo)
+  const bool do_comp = enable && (k < P.nkc || lens);
+  const int ntile = do_comp ? (P.nkc + 15) / 16 : 1;
+#define CA_COMP_F32(DP)                                                                        \
+  f32_wavefronts<DP>(ntile, (int64_t)grid.x * grid.y, [&](auto nw) {                       \
+    constexpr int NW = decltype(nw)::value;                                                    \
+    hipLaunchKernelGGL((comp_f32_kernel<DP, NW>), grid, dim3(64 * NW), 0, st,                  \
+                       (const float*)qp, cent_k, cent_v, count_k, lists, lens, P.nq, P.H,      \
+                       P.nqc, P.nkc, P.cq, P.d, k, scale, enable, (const float*)op, lse,       \
+                       perm_q, (float*)out, lse_out, P.lo);                                    \
+  })
   if (P.d <= 32)
     CA_COMP_F32(32);
   else if (P.d <= 64)

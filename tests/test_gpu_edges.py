@@ -260,3 +260,33 @@ def test_f32_compensation_selected_infinite_value(d):
     vbar[3] = -np.inf
     got, _ = _compensate_rows("f32", d, 32, Q, kbar, vbar, lists, 9)
     assert np.array_equal(got, want)
+
+
+# fp32: the number of wavefronts of a workgroup follows the tiles of 16 keys (1,
+# 2, 4 or 8 with 4 tiles each; 1, 2 or 4 with 2 at d = 128) where there are more
+# than 256 workgroups: the last tile count of each and the next one, against one
+# head alone (64 workgroups, all wavefronts): the same bits.
+@pytest.mark.parametrize("d,tiles", [(64, t) for t in (1, 4, 5, 8, 9, 16, 17)] +
+                         [(128, t) for t in (2, 3, 4, 5)] + [(32, 16)])
+def test_f32_wavefronts_of_a_workgroup(d, tiles):
+    import torch
+    import paper_2608_26965_amd as ca
+    g = torch.Generator(device="cuda")
+    g.manual_seed(tiles)
+    H, n, c, nkc = 5, 1024, 64, 16 * tiles
+
+    def case(heads, ck, k, x):
+        p = ca.Problem(1, heads, n, nkc * ck, d, c, ck, torch.float32)
+        qp, kp, vp, kbar, vbar = (t[:heads] for t in x)
+        cnt = torch.full((heads, nkc), ck, dtype=torch.int32, device="cuda")
+        lists = torch.arange(k, dtype=torch.int32, device="cuda").repeat(heads, p.nqc, 1)
+        perm = torch.arange(n, dtype=torch.int32, device="cuda").repeat(heads, 1)
+        op, lse = ca.block_sparse_attn(p, qp, kp, vp, cnt, lists, k)
+        out, _ = ca.compensate(p, qp, kbar, vbar, cnt, lists, k, op, lse, perm)
+        return op[0], lse[0], out[0, 0]
+
+    for ck, k in ((16, tiles), (1, tiles)):
+        x = [torch.randn(H, *s, device="cuda", generator=g) for s in
+             ((n, d), (nkc * ck, d), (nkc, d, ck), (nkc, d), (nkc, d))]
+        for a, b in zip(case(1, ck, k, x), case(H, ck, k, x)):
+            assert torch.equal(a, b)
