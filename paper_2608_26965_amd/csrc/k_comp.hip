@@ -540,6 +540,13 @@ __global__ __launch_bounds__(64 * NW, kF32Waves) void comp_f32_kernel(
   }
 }
 
+// Launches of more query clusters than this pair them: with one cluster a CU
+// or less, a pair only leaves CUs idle (1,024 to 16,384 queries of one head,
+// clusters of 64 x 64, k = 64: of 128 key clusters 19.0 us alone and 20.3 in
+// pairs at d = 64, 22.9 and 24.6 at d = 128; of 1,024, 34.5 and 38.0, 48.3 and
+// 48.0). 20,480 queries: 37.4 and 36.0 us at d = 64, 54.4 and 51.0 at d = 128.
+constexpr int kPairsFrom = 256;
+
 template <int D, int CQ>
 hipError_t run_bf16(const Prob& P, const void* qp, const float* cent_k, const float* cent_v,
                     const int32_t* count_k, const int32_t* lists, const int32_t* lens, int k,
@@ -564,7 +571,7 @@ hipError_t run_bf16(const Prob& P, const void* qp, const float* cent_k, const fl
   // clusters that share a workgroup share the mask words (with enable = 0 the
   // key clusters may be any number, and no mask is formed)
   constexpr int NQ = comp_clusters<CQ>();
-  if (NQ == 1 || !do_comp || P.nkc <= kMaskWords * 32 / NQ)
+  if (NQ == 1 || (P.BH * P.nqc > kPairsFrom && (!do_comp || P.nkc <= kMaskWords * 32 / NQ)))
     launch(std::integral_constant<int, NQ>{});
   else
     launch(std::integral_constant<int, 1>{});

@@ -145,17 +145,55 @@ def test_topk_filter_edges(nkc, k, kind):
     assert np.array_equal(got.cpu().numpy()[0], ref.topk(S.astype(np.float64), k))
 
 
-# bf16 compensation: two query clusters of 64 share a workgroup; heads with an
-# odd number of clusters (the last one alone), a single one, a remainder.
-@pytest.mark.parametrize("d,n,k", [(64, 130, 2), (64, 40, 1), (128, 300, 3), (128, 64, 1),
-                                   (64, 256, 4)])
-def test_compensation_cluster_pairs(d, n, k):
-    _compensation_parity("bf16", d, 64, 64, n, k, True)
+# bf16 compensation: from 257 query clusters of 64 on, two share a workgroup;
+# heads with an odd number of clusters (the last one alone), a single one, a
+# remainder, several stages of centroids, partners with different lists, and a
+# tile of 128 centroids selected whole by one partner only.
+@pytest.mark.parametrize("d,n,heads", [(64, 130, 86), (64, 40, 257), (128, 300, 52), (128, 64, 257),
+                                       (64, 256, 65)])
+def test_compensation_cluster_pairs(d, n, heads):
+    import math
+    import numpy as np
+    import torch
+    import paper_2608_26965_amd as ca
+    from oracle import ref
+    from tests import gpu_util as G
+    from synth import bf16_round
+    rng = np.random.default_rng([d, n])
+    c, nk, k = 64, 64 * 389 + 5, 140
+    p = ca.Problem(1, heads, n, nk, d, c, c, torch.bfloat16)
+    Q = bf16_round(rng.standard_normal((2, n, d)).astype(np.float32))
+    kbar, vbar = (rng.standard_normal((2, p.nkc, d)).astype(np.float32) for _ in range(2))
+    perm = np.stack([rng.permutation(n) for _ in range(2)]).astype(np.int32)
+    lists = G.random_lists(rng, 2, p.nqc, p.nkc, k)
+    lists[:, p.nqc - 1] = np.arange(128, 128 + k)
+    cq_n, ck_n = G.counts(n, c), G.counts(nk, c)
+    o_s = bf16_round(rng.standard_normal((2, n, d)).astype(np.float32)).astype(np.float64)
+    l_s = (rng.standard_normal((2, n)) + 9.0).astype(np.float32)  # about the log of the keys kept
+    op, lse = np.zeros((2, p.nq_pad, d), np.float32), np.zeros((2, p.nq_pad), np.float32)
+    for h in range(2):
+        op[h, :n], lse[h, :n] = o_s[h][perm[h]], l_s[h][perm[h]]
+    hs = np.arange(heads) % 2
+    out, lse_out = ca.compensate(
+        p, G.permuted_rows(Q, perm, c, torch.bfloat16)[hs], G.dev(kbar)[hs], G.dev(vbar)[hs],
+        G.dev(np.stack([ck_n] * heads), torch.int32), G.dev(lists, torch.int32)[hs].contiguous(), k,
+        G.dev(op, torch.bfloat16)[hs], G.dev(lse)[hs], G.dev(perm, torch.int32)[hs].contiguous(),
+        want_lse=True)
+    out, lse_out = G.host(out)[0], G.host(lse_out)
+    for h in range(2):
+        o_w, l_w = ref.compensate(Q[h].astype(np.float64), kbar[h], vbar[h], ck_n, perm[h], cq_n,
+                                  lists[h], o_s[h], l_s[h].astype(np.float64), 1 / math.sqrt(d))
+        assert np.abs(out[h] - o_w).max() <= G.TOL["bf16"]
+        assert np.abs(lse_out[h] - l_w).max() <= 1e-4 * np.abs(l_w).max()
+    for h in range(2, heads):
+        assert np.array_equal(out[h], out[h % 2]) and np.array_equal(lse_out[h], lse_out[h % 2])
 
 
-def test_compensation_many_key_clusters():
-    """More key clusters than two query clusters' masks hold together (32,768):
-    one query cluster a workgroup."""
+@pytest.mark.parametrize("nkc", [32768, 32769])
+def test_compensation_many_key_clusters(nkc):
+    """As many key clusters as two query clusters' masks hold together, and one
+    more: one query cluster a workgroup, whatever their number. Checked for the
+    first clusters, one in the middle and the last one."""
     import numpy as np
     import torch
     import paper_2608_26965_amd as ca
@@ -163,47 +201,57 @@ def test_compensation_many_key_clusters():
     from tests import gpu_util as G
     from synth import bf16_round
     rng = np.random.default_rng(9)
-    n, nkc, d, c, k = 150, 33000, 64, 64, 40
-    Q = bf16_round(rng.standard_normal((1, n, d)).astype(np.float32))
-    kbar = rng.standard_normal((nkc, d)).astype(np.float32)
-    vbar = rng.standard_normal((nkc, d)).astype(np.float32)
+    n, d, c, k = 64 * 256 + 22, 64, 64, 40
+    Q = bf16_round(rng.standard_normal((n, d)).astype(np.float32))
+    kbar, vbar = (rng.standard_normal((nkc, d)).astype(np.float32) for _ in range(2))
     p = ca.Problem(1, 1, n, nkc * c, d, c, c, torch.bfloat16)
-    perm = rng.permutation(n).astype(np.int32)
+    perm = np.arange(n, dtype=np.int32)
     lists = G.random_lists(rng, 1, p.nqc, nkc, k)
-    cq_n, ck_n = G.counts(n, c), np.full(nkc, c, np.int32)
-    o_s = bf16_round(rng.standard_normal((n, d)).astype(np.float32)).astype(np.float64)
-    l_s = rng.standard_normal(n) + 8.0  # about the log of the keys kept
-    op = np.zeros((1, p.nq_pad, d), np.float32)
-    lse = np.zeros((1, p.nq_pad), np.float32)
-    op[0, :n], lse[0, :n] = o_s[perm], l_s[perm]
+    lists[0, :, -1] = nkc - 1
+    o_s = bf16_round(rng.standard_normal((n, d)).astype(np.float32))
+    l_s = (rng.standard_normal(n) + 8.0).astype(np.float32)  # about the log of the keys kept
+    op, lse = np.zeros((1, p.nq_pad, d), np.float32), np.zeros((1, p.nq_pad), np.float32)
+    op[0, :n], lse[0, :n] = o_s, l_s
     out, lse_out = ca.compensate(
-        p, G.permuted_rows(Q, perm[None], c, torch.bfloat16), G.dev(kbar[None]), G.dev(vbar[None]),
-        G.dev(ck_n[None], torch.int32), G.dev(lists, torch.int32), k, G.dev(op, torch.bfloat16),
-        G.dev(lse), G.dev(perm[None], torch.int32), want_lse=True)
-    o_w, l_w = ref.compensate(Q[0].astype(np.float64), kbar, vbar, ck_n, perm, cq_n, lists[0], o_s,
-                              lse[0, :n][np.argsort(perm)].astype(np.float64), 1 / 8)
-    assert np.abs(G.host(out)[0, 0] - o_w).max() <= G.TOL["bf16"]
-    assert np.abs(G.host(lse_out)[0] - l_w).max() <= 1e-4 * np.abs(l_w).max()
+        p, G.permuted_rows(Q[None], perm[None], c, torch.bfloat16), G.dev(kbar[None]),
+        G.dev(vbar[None]), torch.full((1, nkc), c, dtype=torch.int32, device="cuda"),
+        G.dev(lists, torch.int32), k, G.dev(op, torch.bfloat16), G.dev(lse),
+        G.dev(perm[None], torch.int32), want_lse=True)
+    out, lse_out = G.host(out)[0, 0], G.host(lse_out)[0]
+    for a in (0, 1, 130, p.nqc - 1):
+        r = slice(a * c, min(n, (a + 1) * c))
+        m = r.stop - r.start
+        o_w, l_w = ref.compensate(Q[r].astype(np.float64), kbar, vbar, np.full(nkc, c, np.int32),
+                                  np.arange(m), np.array([m]), lists[0, a:a + 1],
+                                  o_s[r].astype(np.float64), l_s[r].astype(np.float64), 1 / 8)
+        assert np.abs(out[r] - o_w).max() <= G.TOL["bf16"]
+        assert np.abs(lse_out[r] - l_w).max() <= 1e-4 * np.abs(l_w).max()
 
 
-def _compensate_rows(dt, d, cq, Q, kbar, vbar, lists, k, lse=-1e4):
-    """ca.compensate of one head on rows Q [n, d] in cluster order (identity
-    permutation), centroids kbar, vbar [nkc, d] of full clusters of 64 keys and
-    a sparse part of zeros with weight e^lse: (out [n, d], lse [n])."""
+def _compensate_rows(dt, d, cq, Q, kbar, vbar, lists, k, heads=1, lse=-1e4):
+    """ca.compensate of heads that are all alike, on rows Q [n, d] in cluster
+    order (identity permutation), centroids kbar, vbar [nkc, d] of full clusters
+    of 64 keys and a sparse part of zeros with weight e^lse: (out [n, d], lse [n])
+    of the last head."""
     import numpy as np
     import torch
     import paper_2608_26965_amd as ca
     from tests import gpu_util as G
     n, nkc = Q.shape[0], kbar.shape[0]
-    p = ca.Problem(1, 1, n, nkc * 64, d, cq, 64, G.tdtype(dt))
+    p = ca.Problem(1, heads, n, nkc * 64, d, cq, 64, G.tdtype(dt))
     perm = np.arange(n, dtype=np.int32)[None]
-    op = torch.zeros(1, p.nq_pad, d, dtype=G.tdtype(dt), device="cuda")
+
+    def all_heads(x):
+        return x.expand(heads, *x.shape[1:]).contiguous()
+
     out, l = ca.compensate(
-        p, G.permuted_rows(Q[None], perm, cq, G.tdtype(dt)), G.dev(kbar[None]), G.dev(vbar[None]),
-        torch.full((1, nkc), 64, dtype=torch.int32, device="cuda"), G.dev(lists[None], torch.int32), k, op,
-        torch.full((1, p.nq_pad), lse, device="cuda"), G.dev(perm, torch.int32), scale=1.0,
-        want_lse=True)
-    return G.host(out)[0, 0], G.host(l)[0]
+        p, all_heads(G.permuted_rows(Q[None], perm, cq, G.tdtype(dt))), all_heads(G.dev(kbar[None])),
+        all_heads(G.dev(vbar[None])), torch.full((heads, nkc), 64, dtype=torch.int32, device="cuda"),
+        all_heads(G.dev(lists[None], torch.int32)), k,
+        torch.zeros(heads, p.nq_pad, d, dtype=G.tdtype(dt), device="cuda"),
+        torch.full((heads, p.nq_pad), lse, device="cuda"), all_heads(G.dev(perm, torch.int32)),
+        scale=1.0, want_lse=True)
+    return G.host(out)[0, -1], G.host(l)[-1]
 
 
 # The bf16 compensation at d = 64 has one softmax reference per tile of 128
@@ -212,8 +260,8 @@ def _compensate_rows(dt, d, cq, Q, kbar, vbar, lists, k, lse=-1e4):
 # probabilities are bf16(e^(a - b)) and 1; against a as the reference they would
 # be 1 and bf16(e^(b - a)), whose rounding moves the log-sum by over 1e-3. The
 # tolerance covers logits and log-sums in fp32.
-@pytest.mark.parametrize("cq,n", [(64, 64), (64, 128), (128, 128)])
-def test_compensation_tile_reference(cq, n):
+@pytest.mark.parametrize("cq,n,heads", [(64, 64, 1), (64, 64, 300), (64, 128, 150), (128, 128, 1)])
+def test_compensation_tile_reference(cq, n, heads):
     import numpy as np
     from synth import bf16_round
     d, nkc = 64, 192
@@ -223,7 +271,7 @@ def test_compensation_tile_reference(cq, n):
     kbar = np.zeros((nkc, d), np.float32)
     kbar[64:128, 0] = step
     lists = np.tile(np.arange(128, 192), (n // cq, 1))
-    _, lse = _compensate_rows("bf16", d, cq, Q, kbar, np.ones((nkc, d), np.float32), lists, 64)
+    _, lse = _compensate_rows("bf16", d, cq, Q, kbar, np.ones((nkc, d), np.float32), lists, 64, heads)
     up, down = (bf16_round(np.full(1, np.exp(s), np.float32))[0] for s in (step, -step))
     assert abs(up / np.exp(np.float64(step)) - 1) > 1e-3
     want = step + np.log(64.0) + np.log(64 * np.float64(down) + 64)
@@ -240,9 +288,9 @@ def test_compensation_stage_of_one_partner():
         Q = rng.standard_normal((128, d)).astype(np.float32)
         kbar, vbar = (rng.standard_normal((384, d)).astype(np.float32) for _ in range(2))
         lists = np.stack([np.arange(128), np.arange(200, 328)])
-        want, _ = _compensate_rows("bf16", d, 64, Q, kbar, vbar, lists, 128)
+        want, _ = _compensate_rows("bf16", d, 64, Q, kbar, vbar, lists, 128, 150)
         vbar[5] = np.inf
-        got, _ = _compensate_rows("bf16", d, 64, Q, kbar, vbar, lists, 128)
+        got, _ = _compensate_rows("bf16", d, 64, Q, kbar, vbar, lists, 128, 150)
         assert np.array_equal(got[:64], want[:64])
 
 
