@@ -241,26 +241,18 @@ constexpr int kTopBins = 2048;  // linear bins of the top-k pre-pass
 // key of a lower bin precedes it); the radix select then only counts that
 // bin's keys, which keeps the LDS atomics of long rows from piling onto the
 // few digits a narrow score range has in common. Rows longer than 8192
-// scores take it, and the rows that the filter kernel below gives up on;
-// shorter rows the wave, block and filter kernels.
-struct TopkAny {
-  int hist[256];
-  int bins[kTopBins];
-  int warp[4];
-  float f[4];
-  uint32_t prefix;
-  int rank, bin;
-};
-__device__ void topk_any(const float* __restrict__ s, int nkc, int k, int32_t* __restrict__ out,
-                         TopkAny& sh) {
-  int* hist = sh.hist;
-  int* bins = sh.bins;
-  int* sh_warp = sh.warp;
-  float* sh_f = sh.f;
-  uint32_t& sh_prefix = sh.prefix;
-  int& sh_rank = sh.rank;
-  int& sh_bin = sh.bin;
+// scores take this kernel; shorter ones the wave and block kernels below.
+__global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ S, int nkc, int k,
+                                                   int32_t* __restrict__ lists) {
+  __shared__ int hist[256];
+  __shared__ int bins[kTopBins];
+  __shared__ int sh_warp[4];
+  __shared__ float sh_f[4];
+  __shared__ uint32_t sh_prefix;
+  __shared__ int sh_rank, sh_bin;
+  const size_t row = blockIdx.x;
   const int tid = threadIdx.x;
+  const float* s = S + row * nkc;
 
   float lo = INFINITY, hi = -INFINITY;
   for (int b = tid; b < nkc; b += 256) {
@@ -372,6 +364,7 @@ __device__ void topk_any(const float* __restrict__ s, int nkc, int k, int32_t* _
     }
   }
   const int sel_before = block_scan_256(sel, sh_warp, &tot);
+  int32_t* out = lists + row * k;
   int pos = sel_before;
   er = eq_before;
   for (int b = b_lo; b < b_hi; ++b) {
@@ -385,12 +378,6 @@ __device__ void topk_any(const float* __restrict__ s, int nkc, int k, int32_t* _
     }
     if (take && pos < k) out[pos++] = b;
   }
-}
-
-__global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ S, int nkc, int k,
-                                                   int32_t* __restrict__ lists) {
-  __shared__ TopkAny sh;
-  topk_any(S + (size_t)blockIdx.x * nkc, nkc, k, lists + (size_t)blockIdx.x * k, sh);
 }
 
 // Exact top-k of rows of at most 64 * VPL scores, one row per wavefront, the
@@ -646,40 +633,44 @@ __global__ __launch_bounds__(256) void topk_wave_kernel(const float* __restrict_
 // (linear bins over [min, max], candidates of the k-th's bin, 8-bit radix
 // select on order-preserving keys, ties to the lower index) with the
 // histograms shared by the block; the output is written in index order.
-template <int VPL, int NWV>
-__global__ __launch_bounds__(64 * NWV, 4) void topk_block_kernel(const float* __restrict__ S, int nkc,
-                                                              int k, int vec4,
-                                                              int32_t* __restrict__ lists) {
+//
+// One more key in bin b for every lane with `in`; AGG: the lanes that share the
+// first one's bin add once (rows handed over by the filter below, whose scores
+// crowd into few bins: 16,384 rows of 8,192 equal scores, 619 us without,
+// about 325 with).
+template <bool AGG>
+__device__ __forceinline__ void count(int* bins, int b, bool in, int lane) {
+  if constexpr (AGG) {
+    const uint64_t m = __ballot(in);
+    if (m == 0ull) return;  // uniform
+    const int first = __builtin_ctzll(m), b0 = __builtin_amdgcn_readlane(b, first);
+    const uint64_t same = __ballot(in && b == b0);
+    if (lane == first)
+      atomicAdd(&bins[b0], (int)__popcll(same));
+    else if (in && b != b0)
+      atomicAdd(&bins[b], 1);
+  } else {
+    if (in) atomicAdd(&bins[b], 1);
+  }
+}
+
+template <int NWV>
+struct TopkBlock {
+  int bins[kWaveBins];
+  int hist[256];
+  uint32_t ckey[NWV][kWaveCand];
+  float red_lo[NWV], red_hi[NWV];
+  int wcnt[2][NWV];
+  uint32_t wkey[2][NWV];
+  int over;
+};
+template <int VPL, int NWV, bool AGG>
+__device__ __forceinline__ void topk_block(const float (&v)[VPL], int nkc, int k,
+                                           int32_t* __restrict__ out, TopkBlock<NWV>& sh) {
   constexpr int NT = 64 * NWV, G = VPL / 4;
-  static_assert(VPL % 4 == 0, "float4 groups");
-  __shared__ int bins[kWaveBins];
-  __shared__ int hist[256];
-  __shared__ uint32_t ckey[NWV][kWaveCand];
-  __shared__ float red_lo[NWV], red_hi[NWV];
-  __shared__ int wcnt[2][NWV];
-  __shared__ uint32_t wkey[2][NWV];
-  __shared__ int sh_over;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, tid = threadIdx.x;
-  const size_t row = blockIdx.x;
-  const float* s = S + row * nkc;
   const int wbase = 64 * VPL * w;
   auto pos_of = [&](int g, int e) { return wbase + 256 * g + 4 * lane + e; };
-  float v[VPL];
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    const int p0 = pos_of(g, 0);
-    if (vec4) {
-      float4 x = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-      if (p0 < nkc) x = *(const float4*)(s + p0);  // nkc % 4 == 0: whole float4
-      v[4 * g] = x.x;
-      v[4 * g + 1] = x.y;
-      v[4 * g + 2] = x.z;
-      v[4 * g + 3] = x.w;
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[4 * g + e] = p0 + e < nkc ? s[p0 + e] : -INFINITY;
-    }
-  }
   // Positions past the row hold -inf (sorted after every score); only the
   // range below leaves them out.
   float lo = INFINITY, hi = -INFINITY;
@@ -697,15 +688,15 @@ __global__ __launch_bounds__(64 * NWV, 4) void topk_block_kernel(const float* __
     hi = fmaxf(hi, __shfl_xor(hi, o, 64));
   }
   if (lane == 0) {
-    red_lo[w] = lo;
-    red_hi[w] = hi;
+    sh.red_lo[w] = lo;
+    sh.red_hi[w] = hi;
   }
-  for (int i = tid; i < kWaveBins; i += NT) bins[i] = 0;
+  for (int i = tid; i < kWaveBins; i += NT) sh.bins[i] = 0;
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < NWV; ++i) {
-    lo = fminf(lo, red_lo[i]);
-    hi = fmaxf(hi, red_hi[i]);
+    lo = fminf(lo, sh.red_lo[i]);
+    hi = fmaxf(hi, sh.red_hi[i]);
   }
   const float inv0 = (float)kWaveBins / (hi - lo);
   const float inv = hi > lo && inv0 < INFINITY ? inv0 : 0.f;  // too narrow: one bin
@@ -716,11 +707,11 @@ __global__ __launch_bounds__(64 * NWV, 4) void topk_block_kernel(const float* __
   // (not the positions past the row: they would pile onto the last bin)
   if (nkc == 64 * VPL * NWV) {
 #pragma unroll
-    for (int j = 0; j < VPL; ++j) atomicAdd(&bins[bin_of(v[j])], 1);
+    for (int j = 0; j < VPL; ++j) count<AGG>(sh.bins, bin_of(v[j]), true, lane);
   } else {
 #pragma unroll
     for (int j = 0; j < VPL; ++j)
-      if (pos_of(j >> 2, j & 3) < nkc) atomicAdd(&bins[bin_of(v[j])], 1);
+      count<AGG>(sh.bins, bin_of(v[j]), pos_of(j >> 2, j & 3) < nkc, lane);
   }
   __syncthreads();
   // the bin holding rank k - 1 (every wavefront finds the same)
@@ -729,7 +720,7 @@ __global__ __launch_bounds__(64 * NWV, 4) void topk_block_kernel(const float* __
     constexpr int PB = kWaveBins / 64;
     int sum = 0;
 #pragma unroll
-    for (int i = 0; i < PB; ++i) sum += bins[PB * lane + i];
+    for (int i = 0; i < PB; ++i) sum += sh.bins[PB * lane + i];
     const int incl = wave_incl_scan(sum, lane);
     const bool mine = k - 1 >= incl - sum && k - 1 < incl;
     const int owner = __ffsll((long long)__ballot(mine)) - 1;
@@ -737,7 +728,7 @@ __global__ __launch_bounds__(64 * NWV, 4) void topk_block_kernel(const float* __
     if (mine) {
       int acc = incl - sum;
       for (int i = 0; i < PB; ++i) {
-        const int c = bins[PB * lane + i];
+        const int c = sh.bins[PB * lane + i];
         if (k - 1 < acc + c) {
           fb = PB * lane + i;
           fr = k - 1 - acc;
@@ -760,7 +751,7 @@ __global__ __launch_bounds__(64 * NWV, 4) void topk_block_kernel(const float* __
     const int pos = ncand + (int)__popcll(m & ((1ull << lane) - 1ull));
     const uint32_t u = desc_key(v[j]);
     if (hit) {
-      if (pos < kWaveCand) ckey[w][pos] = u;
+      if (pos < kWaveCand) sh.ckey[w][pos] = u;
       kmin = min(kmin, u);
       kmax = max(kmax, u);
     }
@@ -771,45 +762,45 @@ __global__ __launch_bounds__(64 * NWV, 4) void topk_block_kernel(const float* __
     kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o, 64));
     kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o, 64));
   }
-  if (tid == 0) sh_over = 0;
+  if (tid == 0) sh.over = 0;
   __syncthreads();
   if (lane == 0) {
-    if (ncand > kWaveCand) sh_over = 1;
-    wkey[0][w] = kmin;
-    wkey[1][w] = kmax;
+    if (ncand > kWaveCand) sh.over = 1;
+    sh.wkey[0][w] = kmin;
+    sh.wkey[1][w] = kmax;
   }
   __syncthreads();
-  const bool in_lds = sh_over == 0;
+  const bool in_lds = sh.over == 0;
 #pragma unroll
   for (int i = 0; i < NWV; ++i) {
-    kmin = min(kmin, wkey[0][i]);
-    kmax = max(kmax, wkey[1][i]);
+    kmin = min(kmin, sh.wkey[0][i]);
+    kmax = max(kmax, sh.wkey[1][i]);
   }
   uint32_t prefix;
   const int p0 = common_bytes(kmin, kmax, &prefix);
   for (int pass = p0; pass < 4; ++pass) {
     const int shift = 24 - 8 * pass;
     const uint32_t hmask = pass == 0 ? 0u : (0xFFFFFFFFu << (shift + 8));
-    for (int i = tid; i < 256; i += NT) hist[i] = 0;
+    for (int i = tid; i < 256; i += NT) sh.hist[i] = 0;
     __syncthreads();
     if (in_lds) {
       for (int i = lane; i < ncand; i += 64) {
-        const uint32_t u = ckey[w][i];
-        if ((u & hmask) == prefix) atomicAdd(&hist[(u >> shift) & 255], 1);
+        const uint32_t u = sh.ckey[w][i];
+        if ((u & hmask) == prefix) atomicAdd(&sh.hist[(u >> shift) & 255], 1);
       }
     } else {
 #pragma unroll
-      for (int j = 0; j < VPL; ++j)
-        if (bin_of(v[j]) == B) {
-          const uint32_t u = desc_key(v[j]);
-          if ((u & hmask) == prefix) atomicAdd(&hist[(u >> shift) & 255], 1);
-        }
+      for (int j = 0; j < VPL; ++j) {
+        const uint32_t u = desc_key(v[j]);
+        count<AGG>(sh.hist, (int)(u >> shift) & 255,
+                   bin_of(v[j]) == B && (u & hmask) == prefix, lane);
+      }
     }
     __syncthreads();
     int c[4], sum = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      c[i] = hist[4 * lane + i];
+      c[i] = sh.hist[4 * lane + i];
       sum += c[i];
     }
     const int incl = wave_incl_scan(sum, lane);
@@ -852,18 +843,18 @@ __global__ __launch_bounds__(64 * NWV, 4) void topk_block_kernel(const float* __
     lt_w += __shfl_xor(lt_w, o, 64);
   }
   if (lane == 0) {
-    wcnt[0][w] = eq_w;
-    wcnt[1][w] = lt_w;
+    sh.wcnt[0][w] = eq_w;
+    sh.wcnt[1][w] = lt_w;
   }
   __syncthreads();
   int eq_run = 0, sel_base = 0;  // equal keys and selected keys before this wavefront's range
   for (int i = 0; i < w; ++i) {
-    sel_base += wcnt[1][i] + min(max(need_eq - eq_run, 0), wcnt[0][i]);
-    eq_run += wcnt[0][i];
+    sel_base += sh.wcnt[1][i] + min(max(need_eq - eq_run, 0), sh.wcnt[0][i]);
+    eq_run += sh.wcnt[0][i];
   }
   // the selected positions, per float4 group in lane order, written from
   // the wavefront's base (the totals of the wavefronts before it)
-  auto walk = [&](int32_t* out) {
+  {
     int er = eq_run, pos_run = sel_base;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -895,8 +886,40 @@ __global__ __launch_bounds__(64 * NWV, 4) void topk_block_kernel(const float* __
       const int gsel = __builtin_amdgcn_readlane(sel_incl, 63);
       pos_run += gsel;
     }
-  };
-  walk(lists + row * k);
+  }
+}
+
+// REST: only the rows that the filter below left, marked by a first entry of -1.
+template <int VPL, int NWV, bool REST>
+__global__ __launch_bounds__(64 * NWV, 4) void topk_block_kernel(const float* __restrict__ S, int nkc,
+                                                              int k, int vec4,
+                                                              int32_t* __restrict__ lists) {
+  constexpr int G = VPL / 4;
+  static_assert(VPL % 4 == 0, "float4 groups");
+  __shared__ TopkBlock<NWV> sh;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const size_t row = blockIdx.x;
+  if (REST && lists[row * k] >= 0) return;
+  const float* s = S + row * nkc;
+  const int wbase = 64 * VPL * w;
+  auto pos_of = [&](int g, int e) { return wbase + 256 * g + 4 * lane + e; };
+  float v[VPL];
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const int p0 = pos_of(g, 0);
+    if (vec4) {
+      float4 x = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+      if (p0 < nkc) x = *(const float4*)(s + p0);  // nkc % 4 == 0: whole float4
+      v[4 * g] = x.x;
+      v[4 * g + 1] = x.y;
+      v[4 * g + 2] = x.z;
+      v[4 * g + 3] = x.w;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[4 * g + e] = p0 + e < nkc ? s[p0 + e] : -INFINITY;
+    }
+  }
+  topk_block<VPL, NWV, REST>(v, nkc, k, lists + row * k, sh);
 }
 
 // Exact top-k of a row that is longer than k, one row per block of four
@@ -906,18 +929,27 @@ __global__ __launch_bounds__(64 * NWV, 4) void topk_block_kernel(const float* __
 //     many groups), and the k-th largest group maximum is at most the k-th
 //     largest score. So is the lower edge of its linear bin over the maxima's
 //     range, and the scores above that edge (t < bound) hold the k largest:
-//     typically 1.1 to 2 k of them, which go to a list.
+//     typically 1.1 to 2 k of them, which go to a list. Infinities take no part
+//     in the range. Where the k-th maximum's bin holds more than k + 64 of them
+//     (a few far outliers stretch the range), the bins are taken again over that
+//     bin's maxima, up to twice.
 //  2. The k-th largest of the listed scores: linear bins again, over the listed
-//     range, then a count among the at most 64 scores of its bin. Bitmaps over
-//     the row's positions put the selected ones in index order.
-// Rows with too few or too many listed scores, or more than 64 in the last bin
-// (ties, infinities, a narrow cluster of scores), take topk_any.
+//     range, then a count among the at most 64 scores of its bin, or, with more
+//     of them there (ties), 8-bit radix passes over that bin's listed keys
+//     after their common leading bytes. Bitmaps over the row's positions put
+//     the selected ones in index order.
+// Rows with too few or too many listed scores (fewer than k finite ones; more
+// than kFiltCand that the bound lets through, most of them equal to the k-th)
+// are marked for topk_block_kernel, launched behind (in the same kernel it
+// would cost the registers of both: 145 us for the first figure below).
 //
 // What bounds it: reading the row. The block kernel counts every score into LDS
 // bins, recomputes bins and keys in each later pass and writes its list by a
 // scan of every float4 group; here a score costs a maximum, a multiply-add and
-// two comparisons. 16,384 rows of 8,192, k = 64: 274 -> 115 us
-// (4.7 TB/s); k = 819: 273 -> 168; rows of 5,000, k = 312: 399 -> 142.
+// two comparisons. 16,384 rows of 8,192, k = 64: 286 -> 117 us (both launches,
+// 4.6 TB/s); k = 819: 290 -> 171; rows of 5,000, k = 312: 404 -> 142. Scores
+// of 17 values 357 -> 150, a random rest masked by -inf 799 -> 128,
+// under one outlier 849 -> 151, all equal 619 -> 442 (all k = 64 of 8,192).
 constexpr int kFiltCand = 2048;  // listed scores
 
 template <int VPL, int NG>
@@ -931,14 +963,12 @@ __global__ __launch_bounds__(256, 4) void topk_filter_kernel(const float* __rest
     uint16_t at[kFiltCand];
     uint32_t lt[WORDS], eq[WORDS];
     uint32_t last[64];
+    uint32_t kmin, kmax;
     float lo[4], hi[4];
     int groups[4], scan[4];
     int nlist, nlast;
   };
-  __shared__ union {
-    Filter f;
-    TopkAny any;
-  } sh;
+  __shared__ Filter sh;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, tid = threadIdx.x;
   const size_t row = blockIdx.x;
   const float* s = S + row * nkc;
@@ -952,10 +982,14 @@ __global__ __launch_bounds__(256, 4) void topk_filter_kernel(const float* __rest
   for (int g = 0; g < G; ++g) {
     load_scores4(s, pos_of(g, 0), nkc, &v[4 * g]);
   }
-  for (int i = tid; i < 2 * kWaveBins; i += 256) (&sh.f.bins[0][0])[i] = 0;
-  for (int i = tid; i < WORDS; i += 256) sh.f.lt[i] = sh.f.eq[i] = 0u;
-  if (tid == 0) sh.f.nlist = sh.f.nlast = 0;
-  // group maxima, and the range of those of groups that hold a score
+  for (int i = tid; i < 2 * kWaveBins; i += 256) (&sh.bins[0][0])[i] = 0;
+  for (int i = tid; i < WORDS; i += 256) sh.lt[i] = sh.eq[i] = 0u;
+  if (tid == 0) {
+    sh.nlist = sh.nlast = 0;
+    sh.kmin = 0xFFFFFFFFu;
+    sh.kmax = 0u;
+  }
+  // group maxima, and the range of the finite ones
   float gm[NG], lo = INFINITY, hi = -INFINITY;
 #pragma unroll
   for (int q = 0; q < NG; ++q) gm[q] = -INFINITY;
@@ -968,85 +1002,96 @@ __global__ __launch_bounds__(256, 4) void topk_filter_kernel(const float* __rest
     }
   int nreal = 0;  // groups 0 .. nreal - 1 hold a score
 #pragma unroll
-  for (int q = 0; q < NG; ++q)
-    if (pos_of(q >> 2, q & 3) < nkc) {
+  for (int q = 0; q < NG; ++q) {
+    if (pos_of(q >> 2, q & 3) < nkc) nreal = q + 1;
+    if (fabsf(gm[q]) < INFINITY) {
       lo = fminf(lo, gm[q]);
       hi = fmaxf(hi, gm[q]);
-      nreal = q + 1;
     }
+  }
   int real = nreal;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    lo = fminf(lo, __shfl_xor(lo, o, 64));
-    hi = fmaxf(hi, __shfl_xor(hi, o, 64));
-    real += __shfl_xor(real, o, 64);
-  }
-  if (lane == 0) {
-    sh.f.lo[w] = lo;
-    sh.f.hi[w] = hi;
-    sh.f.groups[w] = real;
-  }
-  __syncthreads();
-  real = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    lo = fminf(lo, sh.f.lo[i]);
-    hi = fmaxf(hi, sh.f.hi[i]);
-    real += sh.f.groups[i];
-  }
-  const float inv0 = (float)kWaveBins / (hi - lo);
-  const float inv = hi > lo && inv0 < INFINITY ? inv0 : 0.f;  // too narrow: one bin
+  for (int o = 32; o > 0; o >>= 1) real += __shfl_xor(real, o, 64);
+  if (lane == 0) sh.groups[w] = real;
   auto bin_at = [](float t) {
     return t < (float)kWaveBins ? (t > 0.f ? (int)t : 0) : kWaveBins - 1;
   };
-#pragma unroll
-  for (int q = 0; q < NG; ++q)
-    if (q < nreal) atomicAdd(&sh.f.bins[0][bin_at((hi - gm[q]) * inv)], 1);
-  __syncthreads();
   // the bin of rank r (descending) in a histogram, and the rank inside it;
   // every wavefront finds the same
-  auto find_bin = [&](const int* bins, int r, int* rank) {
+  auto find_bin = [&](const int* bins, int r, int* rank, int* size) {
     constexpr int PB = kWaveBins / 64;
-    int c[PB], sum = 0;
+    static_assert(PB <= 64, "one bin a lane");
+    int sum = 0;
 #pragma unroll
     for (int i = 0; i < PB; i += 4) {
       const int4 x = *(const int4*)&bins[PB * lane + i];
-      c[i] = x.x;
-      c[i + 1] = x.y;
-      c[i + 2] = x.z;
-      c[i + 3] = x.w;
+      sum += (x.x + x.y) + (x.z + x.w);
     }
-#pragma unroll
-    for (int i = 0; i < PB; ++i) sum += c[i];
     const int incl = wave_incl_scan(sum, lane);
     const uint64_t own = __ballot(r >= incl - sum && r < incl);
     const int l = own ? __builtin_ctzll(own) : 63;
-    int acc = incl - sum, b = 0, rb = 0;
-#pragma unroll
-    for (int i = 0; i < PB; ++i) {
-      if (r >= acc && r < acc + c[i]) {
-        b = PB * lane + i;
-        rb = r - acc;
-      }
-      acc += c[i];
-    }
-    *rank = __builtin_amdgcn_readlane(rb, l);
-    return __builtin_amdgcn_readlane(b, l);
+    // lane l's bins, one a lane
+    const int c = lane < PB ? bins[PB * l + lane] : 0;
+    const int acc = wave_incl_scan(c, lane) - c + __builtin_amdgcn_readlane(incl - sum, l);
+    const uint64_t hit = __ballot(r >= acc && r < acc + c);
+    const int b = hit ? __builtin_ctzll(hit) : 0;
+    *rank = r - __builtin_amdgcn_readlane(acc, b);
+    *size = __builtin_amdgcn_readlane(c, b);
+    return PB * l + b;
   };
-  int rank;
-  const int B = find_bin(sh.f.bins[0], k - 1, &rank);
-  const float bound = B == kWaveBins - 1 ? INFINITY : (float)(B + 1);
-  // the scores above the bound (positions past the row hold -inf: their t is
-  // infinite or NaN, never listed): counted, then listed from the wavefront's
-  // place
+  const uint64_t below = (1ull << lane) - 1ull;
+  float inv, bound;
+  int rank, size;
+  for (int pass = 0;; ++pass) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      lo = fminf(lo, __shfl_xor(lo, o, 64));
+      hi = fmaxf(hi, __shfl_xor(hi, o, 64));
+    }
+    if (lane == 0) {
+      sh.lo[w] = lo;
+      sh.hi[w] = hi;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      lo = fminf(lo, sh.lo[i]);
+      hi = fmaxf(hi, sh.hi[i]);
+    }
+    // Any positive finite scale keeps the order: +inf has t = -inf (bin 0) and
+    // -inf and the positions past the row t = inf or NaN (the last bin, not
+    // listed), also where the range is empty, too narrow or too wide for a
+    // scale of its own.
+    const float inv0 = (float)kWaveBins / (hi - lo);
+    inv = inv0 > 0.f && inv0 < INFINITY ? inv0 : 1e-30f;
+#pragma unroll
+    for (int q = 0; q < NG; ++q)
+      if (q < nreal) atomicAdd(&sh.bins[0][bin_at((hi - gm[q]) * inv)], 1);
+    __syncthreads();
+    const int B = find_bin(sh.bins[0], k - 1, &rank, &size);
+    bound = B == kWaveBins - 1 ? INFINITY : (float)(B + 1);
+    // the same decision in every wavefront
+    if (size <= k + 64 || pass == 2 || !(lo < hi)) break;
+    lo = INFINITY;
+    float nhi = -INFINITY;
+#pragma unroll
+    for (int q = 0; q < NG; ++q)
+      if (q < nreal && fabsf(gm[q]) < INFINITY && bin_at((hi - gm[q]) * inv) == B) {
+        lo = fminf(lo, gm[q]);
+        nhi = fmaxf(nhi, gm[q]);
+      }
+    hi = nhi;
+    __syncthreads();  // the bins are read
+    for (int i = tid; i < kWaveBins; i += 256) sh.bins[0][i] = 0;
+  }
+  // the scores above the bound: counted, then listed from the wavefront's place
   auto listed = [&](int j) { return (hi - v[j]) * inv < bound; };
   int n = 0;
 #pragma unroll
   for (int j = 0; j < VPL; ++j) n += (int)__popcll(__ballot(listed(j)));
   int base = 0;
-  if (lane == 0 && n > 0) base = atomicAdd(&sh.f.nlist, n);
+  if (lane == 0 && n > 0) base = atomicAdd(&sh.nlist, n);
   base = __builtin_amdgcn_readfirstlane(base);
-  const uint64_t below = (1ull << lane) - 1ull;
   if (n > 0 && base + n <= kFiltCand) {
     int p = base;
 #pragma unroll
@@ -1056,35 +1101,41 @@ __global__ __launch_bounds__(256, 4) void topk_filter_kernel(const float* __rest
       if (m == 0ull) continue;  // uniform
       if (hit) {
         const int i = p + (int)__popcll(m & below);
-        sh.f.val[i] = v[j];
-        sh.f.at[i] = (uint16_t)pos_of(j >> 2, j & 3);
+        sh.val[i] = v[j];
+        sh.at[i] = (uint16_t)pos_of(j >> 2, j & 3);
       }
       p += (int)__popcll(m);
     }
   }
   __syncthreads();
-  const int total = sh.f.nlist;
-  bool over = real < k || total < k || total > kFiltCand;
+  const int total = sh.nlist;
+  real = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) real += sh.groups[i];
   uint32_t thr = 0u;
   int need_eq = 0;
-  if (!over) {
+  if (real >= k && total >= k && total <= kFiltCand) {  // the same decision in every wavefront
     const float inv2 = bound == INFINITY ? 1.f : (float)kWaveBins / bound;
     auto bin2_of = [&](float x) { return bin_at((hi - x) * inv * inv2); };
-    for (int i = tid; i < total; i += 256) atomicAdd(&sh.f.bins[1][bin2_of(sh.f.val[i])], 1);
+    for (int i = tid; i < total; i += 256)
+      count<true>(sh.bins[1], bin2_of(sh.val[i]), true, lane);
     __syncthreads();
-    const int B2 = find_bin(sh.f.bins[1], k - 1, &rank);
+    const int B2 = find_bin(sh.bins[1], k - 1, &rank, &size);
     for (int i = tid; i < total; i += 256) {
-      const float x = sh.f.val[i];
-      if (bin2_of(x) == B2) {
-        const int j = atomicAdd(&sh.f.nlast, 1);
-        if (j < 64) sh.f.last[j] = desc_key(x);
-      }
+      const float x = sh.val[i];
+      const bool hit = bin2_of(x) == B2;
+      const uint64_t m = __ballot(hit);
+      if (m == 0ull) continue;  // uniform
+      const int first = __builtin_ctzll(m);
+      int at = 0;
+      if (lane == first) at = atomicAdd(&sh.nlast, (int)__popcll(m));
+      at = __builtin_amdgcn_readlane(at, first) + (int)__popcll(m & below);
+      if (hit && at < 64) sh.last[at] = desc_key(x);
     }
     __syncthreads();
-    const int nl = __builtin_amdgcn_readfirstlane(sh.f.nlast);
-    over = nl > 64;
-    if (!over) {
-      const uint32_t key = lane < nl ? sh.f.last[lane] : 0xFFFFFFFFu;
+    const int nl = __builtin_amdgcn_readfirstlane(sh.nlast);
+    if (nl <= 64) {  // the same in every wavefront
+      const uint32_t key = lane < nl ? sh.last[lane] : 0xFFFFFFFFu;
       int less = 0, eq = 0;
       for (int j = 0; j < nl; ++j) {
         const uint32_t kj = (uint32_t)__builtin_amdgcn_readlane((int)key, j);
@@ -1094,36 +1145,84 @@ __global__ __launch_bounds__(256, 4) void topk_filter_kernel(const float* __rest
       const uint64_t own = __ballot(lane < nl && rank >= less && rank < less + eq);
       const int l = own ? __builtin_ctzll(own) : 0;
       thr = (uint32_t)__builtin_amdgcn_readlane((int)key, l);
-      need_eq = rank - __builtin_amdgcn_readlane(less, l) + 1;
+      rank -= __builtin_amdgcn_readlane(less, l);
+    } else {
+      uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
+      for (int i = tid; i < total; i += 256) {
+        const float x = sh.val[i];
+        const uint32_t u = desc_key(x);
+        if (bin2_of(x) == B2) {
+          kmin = min(kmin, u);
+          kmax = max(kmax, u);
+        }
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o, 64));
+        kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o, 64));
+      }
+      if (lane == 0) {
+        atomicMin(&sh.kmin, kmin);
+        atomicMax(&sh.kmax, kmax);
+      }
+      __syncthreads();
+      int* hist = sh.bins[0];
+      for (int b = common_bytes(sh.kmin, sh.kmax, &thr); b < 4; ++b) {
+        const int shift = 24 - 8 * b;
+        const uint32_t hmask = b == 0 ? 0u : (0xFFFFFFFFu << (shift + 8));
+        hist[tid] = 0;
+        __syncthreads();
+        for (int i = tid; i < total; i += 256) {
+          const float x = sh.val[i];
+          const uint32_t u = desc_key(x);
+          count<true>(hist, (int)(u >> shift) & 255, bin2_of(x) == B2 && (u & hmask) == thr, lane);
+        }
+        __syncthreads();
+        const int4 c = *(const int4*)&hist[4 * lane];
+        const int sum = (c.x + c.y) + (c.z + c.w);
+        const int before = wave_incl_scan(sum, lane) - sum;
+        const uint64_t own = __ballot(rank >= before && rank < before + sum);
+        const int l = own ? __builtin_ctzll(own) : 0;
+        int r = rank - before, dg = 4 * lane;
+        const int cs[3] = {c.x, c.y, c.z};
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+          if (dg == 4 * lane + e && r >= cs[e]) {
+            r -= cs[e];
+            ++dg;
+          }
+        thr |= (uint32_t)__builtin_amdgcn_readlane(dg, l) << shift;
+        rank = __builtin_amdgcn_readlane(r, l);
+        __syncthreads();  // hist is cleared again by the next pass
+      }
     }
-  }
-  if (over) {  // the same decision in every wavefront
-    __syncthreads();  // the filter's arrays are done with
-    topk_any(s, nkc, k, out, sh.any);
+    need_eq = rank + 1;
+  } else {
+    if (tid == 0) out[0] = -1;
     return;
   }
   // positions of the keys below the threshold (taken) and equal to it (the
   // first need_eq taken), in index order
   for (int i = tid; i < total; i += 256) {
-    const uint32_t u = desc_key(sh.f.val[i]);
+    const uint32_t u = desc_key(sh.val[i]);
     if (u <= thr) {
-      const int p = sh.f.at[i];
-      atomicOr(u < thr ? &sh.f.lt[p >> 5] : &sh.f.eq[p >> 5], 1u << (p & 31));
+      const int p = sh.at[i];
+      atomicOr(u < thr ? &sh.lt[p >> 5] : &sh.eq[p >> 5], 1u << (p & 31));
     }
   }
   __syncthreads();
   uint32_t take = 0u, equal = 0u;
   if (tid < WORDS) {
-    take = sh.f.lt[tid];
-    equal = sh.f.eq[tid];
+    take = sh.lt[tid];
+    equal = sh.eq[tid];
   }
   // (equal, below) counts of the words before this one
   const int cnt = ((int)__popc(equal) << 16) | (int)__popc(take);
   const int incl = wave_incl_scan(cnt, lane);
-  if (lane == 63) sh.f.scan[w] = incl;
+  if (lane == 63) sh.scan[w] = incl;
   __syncthreads();
   int pre = incl - cnt;
-  for (int i = 0; i < w; ++i) pre += sh.f.scan[i];
+  for (int i = 0; i < w; ++i) pre += sh.scan[i];
   const int eb = pre >> 16;
   int p = (pre & 0xFFFF) + min(eb, need_eq);
   for (int i = eb; i < need_eq && equal != 0u; ++i) {  // the lowest of the word's equal ones
@@ -1347,6 +1446,8 @@ hipError_t launch_select(const Prob& P, const float* cq, const float* ck, const 
   if (P.nkc <= 256 * V && (int64_t)P.nkc * NG >= (int64_t)2 * k * V) {                         \
     hipLaunchKernelGGL((topk_filter_kernel<V, NG>), dim3((unsigned)nrows), dim3(256), 0, st, S, \
                        P.nkc, k, lists);                                                       \
+    hipLaunchKernelGGL((topk_block_kernel<V, 4, true>), dim3((unsigned)nrows), dim3(256), 0,    \
+                       st, S, P.nkc, k, vec4, lists);                                          \
     return hipGetLastError();                                                                  \
   }
     CA_TOPK_FILTER(16, 1)
@@ -1360,7 +1461,7 @@ hipError_t launch_select(const Prob& P, const float* cq, const float* ck, const 
 #undef CA_TOPK_FILTER
 #define CA_TOPK_BLOCK(V)                                                                      \
   if (P.nkc <= 256 * V) {                                                                     \
-    hipLaunchKernelGGL((topk_block_kernel<V, 4>), dim3((unsigned)nrows), dim3(256), 0, st, S, \
+    hipLaunchKernelGGL((topk_block_kernel<V, 4, false>), dim3((unsigned)nrows), dim3(256), 0, st, S, \
                        P.nkc, k, vec4, lists);                                                \
     return hipGetLastError();                                                                 \
   }

@@ -118,12 +118,15 @@ def test_split_chunk_edges(n, kind):
 
 # Top-k of rows of 2049-8192 scores: at the edges of the number of groups the
 # filter makes (256 to 2048, at least twice k of them), rows that leave part of
-# a wavefront's range empty, and the inputs it hands over (ties, runs of equal
-# scores at the threshold, infinities, scores that crowd under one outlier, long
-# runs of the largest scores).
+# a wavefront's range empty, and the inputs that leave its common path: ties and
+# runs of equal scores at the threshold, all scores equal (but for a few
+# infinite ones), infinities, fewer than k finite scores, one or two outliers
+# that the others crowd under (narrower bins), long runs of the largest scores,
+# close scores in a bin by the hundred (radix passes), rows of several kinds.
 @pytest.mark.parametrize("nkc,k", [(2049, 64), (2049, 513), (4095, 128), (4096, 129), (4097, 1),
                                    (8192, 128), (8192, 129), (8191, 1023), (8192, 1025)])
-@pytest.mark.parametrize("kind", ["normal", "ties", "inf", "outlier", "run"])
+@pytest.mark.parametrize("kind", ["normal", "ties", "halves", "const", "const_inf", "inf", "mask",
+                                  "few", "outlier", "outliers", "run", "close", "mixed"])
 def test_topk_filter_edges(nkc, k, kind):
     import numpy as np
     import torch
@@ -133,6 +136,25 @@ def test_topk_filter_edges(nkc, k, kind):
     S = rng.standard_normal((6, nkc)).astype(np.float32)
     if kind == "ties":
         S = np.round(2 * S)
+    elif kind == "halves":
+        S = np.sign(S)
+    elif kind == "const":
+        S[:] = 2.5
+    elif kind == "const_inf":
+        S[:] = 2.5
+        S[:, 5::1000], S[:, 7::50] = np.inf, -np.inf
+    elif kind == "mask":  # all after a position of each row's own, and a run before it
+        S[np.arange(nkc) >= rng.integers(nkc // 2 + 40, nkc, (6, 1))] = -np.inf
+        S[:, 64:64 + nkc // 8] = -np.inf
+    elif kind == "few":
+        S[:, k // 2:] = -np.inf
+    elif kind == "outliers":
+        S = S * 1e-5
+        S[:, nkc // 2], S[:, nkc // 3], S[:, 11] = 1e20, 1, -1e30
+    elif kind == "close":  # more than 64 distinct scores in a bin of the listed ones
+        S = np.where(rng.random(S.shape) < 0.3, 3 + 1e-6 * S, S).astype(np.float32)
+    elif kind == "mixed":
+        S[1], S[3, k // 2:], S[4] = 1, -np.inf, np.round(S[4])
     elif kind == "inf":
         S[:, ::7], S[:, 3::1000] = -np.inf, np.inf
     elif kind == "outlier":
