@@ -1120,6 +1120,7 @@ __global__ __launch_bounds__(eigh_threads<DM>()) void eigh_kernel(Ctx C, EighJob
     }
     const float o = (o4[0] + o4[1]) + (o4[2] + o4[3]);
     sgn[tid] = o < 0.f ? -1.f : 1.f;
+    inv[tid] = tid;  // (the ranks below leave entries out where eigenvalues are NaN)
   }
   __syncthreads();
   if (tid < d) {
@@ -1903,7 +1904,7 @@ __device__ int choose_coordinate(const float* __restrict__ Y, int d, const int32
   }
   if (mean_out) *mean_out = bmean;
   if (var_out) *var_out = best;
-  return bt;
+  return bt < d ? bt : 0;  // no variance is a number (values that are not, or overflow): any serves
 }
 
 // The same choice by several wavefronts and mostly in fp32. The fp64 sums above

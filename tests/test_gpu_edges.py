@@ -86,6 +86,34 @@ def test_split_tail_edges(dt, n, d, c, xf):
     _cluster_parity(dt, n, d, c, xf)
 
 
+# Inputs that are not finite, or whose products overflow, leave no coordinate of
+# the split with a variance: the results are unspecified, but every call ends and
+# the orders stay orders, through levels of several workgroups and of one.
+@pytest.mark.parametrize("n,d", [(700, 64), (5000, 64), (9000, 128)])
+@pytest.mark.parametrize("xf", ["none", "pca", "metric", "adaptive"])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_split_of_non_finite_coordinates(dt, xf, n, d):
+    import torch
+    import paper_2608_26965_amd as ca
+    from tests import gpu_util as G
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    q, k = (torch.randn(1, 3, n, d, device="cuda", generator=g) for _ in range(2))
+    q[:, 0] = float("nan")
+    q[:, 1, n // 2] = float("inf")
+    k[:, 0] *= 1e30
+    k[:, 1, :, 0] = float("nan")
+    k[:, 2, ::3] = float("-inf")
+    q, k = q.to(G.tdtype(dt)), k.to(G.tdtype(dt))
+    p = ca.Problem(1, 3, n, n, d, 32, 32, G.tdtype(dt), xf)
+    r = ca.cluster(p, q, k, k)
+    want = torch.arange(n, dtype=torch.int32, device="cuda")
+    for side in ("q", "k"):
+        for h in range(3):
+            assert torch.equal(r["perm_" + side][h].sort().values, want)
+        assert int(r["count_" + side].sum()) == 3 * n
+
+
 # Levels of several chunks (4,096 tokens each): one token into the next chunk,
 # thresholds in runs of equal keys, all keys equal, and keys that one outlier
 # crowds into a bin (more of them than the chunk blocks select among by themselves).
