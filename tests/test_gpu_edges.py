@@ -120,11 +120,22 @@ def test_split_of_non_finite_coordinates(dt, xf, n, d):
 @pytest.mark.parametrize("kind", ["normal", "ties", "run", "const", "outlier"])
 @pytest.mark.parametrize("n", [4097, 8191, 12289, 30000])
 def test_split_chunk_edges(n, kind):
+    _split_against_oracle(n, 8, 64, kind)
+
+
+# Samples without spread: equal rows (some of a signed zero), rows whose squared
+# differences underflow in fp32, and one coordinate that differs in one sample row.
+@pytest.mark.parametrize("kind", ["const", "zeros", "tiny", "single"])
+@pytest.mark.parametrize("n,d,c", [(9000, 100, 64), (9000, 64, 32), (2000, 128, 16)])
+def test_split_of_flat_samples(n, d, c, kind):
+    _split_against_oracle(n, d, c, kind)
+
+
+def _split_against_oracle(n, d, c, kind):
     import numpy as np
     import torch
     import paper_2608_26965_amd as ca
     from oracle import ref
-    d, c = 8, 64
     X = np.random.default_rng(n).standard_normal((2, n, d)).astype(np.float32)
     if kind == "ties":
         X = np.round(X)
@@ -132,6 +143,13 @@ def test_split_chunk_edges(n, kind):
         X[np.random.default_rng(1).random(X.shape) < 0.4] = 0.25
     elif kind == "const":
         X[:] = 0.5
+    elif kind == "zeros":
+        X = X * 0
+    elif kind == "tiny":
+        X = X * np.float32(1e-30)
+    elif kind == "single":
+        X[:] = 0.5
+        X[:, ((2 * d - 1) * n) // (2 * d), d // 2] = 0.75
     elif kind == "outlier":
         X = X * 1e-5
         X[:, n // 3] = 1e6
