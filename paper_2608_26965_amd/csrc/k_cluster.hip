@@ -3492,17 +3492,8 @@ __global__ __launch_bounds__(kTailThreads, 4) void split_tail_kernel(Ctx C, int 
     // ---- that bin's keys
 #pragma unroll
     for (int u = 0; u < kTailPer; ++u) {
-      const bool hit = bin[u] >= 0 && bin[u] == sub_bin[sl[u]];
-      const uint64_t m = __ballot(hit);
-      if (m == 0ull) continue;  // uniform
-      // the lanes of the first one's sub-node take their places at once
-      const int first = __builtin_ctzll(m), s0 = __builtin_amdgcn_readlane(sl[u], first);
-      const uint64_t same = __ballot(hit && sl[u] == s0);
-      int i = 0;
-      if (lane == first) i = atomicAdd(&sub_n[s0], (int)__popcll(same));
-      i = __builtin_amdgcn_readlane(i, first) + (int)__popcll(same & ((1ull << lane) - 1ull));
-      if (hit) {
-        if (sl[u] != s0) i = atomicAdd(&sub_n[sl[u]], 1);
+      if (bin[u] >= 0 && bin[u] == sub_bin[sl[u]]) {
+        const int i = atomicAdd(&sub_n[sl[u]], 1);
         if (i < cap) cand[sl[u] * cap + i] = kv[u];
       }
     }
