@@ -202,6 +202,7 @@ void plan_workspace(const Prob& P, Workspace* W) {
   int bigmax = W->big_q > W->big_k ? W->big_q : W->big_k;
   W->max_big_nodes = bigmax > 0 ? (1 << (bigmax - 1)) : 1;
   W->hist_slots = split_hist_slots(P, W->big_q, W->big_k);
+  W->ghist_slots = split_group_slots(P, W->big_q, W->big_k);
 
   W->y_q = take(BH * P.nq * d * 4);
   W->y_k = take(BH * P.nk * d * 4);
@@ -222,6 +223,7 @@ void plan_workspace(const Prob& P, Workspace* W) {
   W->wops = take(BH * 3 * 2 * d * d * 2);
   W->node_state = take(2 * BH * W->max_big_nodes * kNodeInts * 4);
   W->hist = take(2 * BH * W->hist_slots * kBins * 4);
+  W->ghist = take(2 * BH * W->ghist_slots * kBins * 4);
   W->chunk_cnt = take(2 * BH * W->hist_slots * kChunkInts * 4);
   W->dirs = take(basic ? 2 * 2 * BH * W->max_big_nodes * d * 4 : 0);
   W->scores = take(BH * P.nqc * P.nkc * 4);

@@ -112,6 +112,7 @@ struct Workspace {
   size_t wops;              // bf16 [BH][3][2][d][d] MFMA operands (transposed hi/lo)
   size_t node_state;        // int32 [2][BH][max_big_nodes][kNodeInts]
   size_t hist;              // uint32 [2][BH][hist_slots][kBins] chunk histograms
+  size_t ghist;             // uint32 [2][BH][ghist_slots][kBins] their sums by groups of chunks
   size_t cand;              // uint32 [2][BH][nmax] keys of the threshold's bin, by node and chunk
   size_t chunk_cnt;         // int32 [2][BH][hist_slots][kChunkInts] chunk prefixes
   size_t dirs;              // fp32 [2 levels][2][BH][max_big_nodes][d] split directions (basic)
@@ -129,6 +130,7 @@ struct Workspace {
   int big_q, big_k;         // levels done by the multi-block kernels
   int max_big_nodes;        // nodes at the deepest multi-block level
   int hist_slots;           // chunk slots of the busiest multi-block level
+  int ghist_slots;          // most group slots of a level that sums its chunks by groups
 };
 
 // Leading split coordinates also kept coordinate-major (one contiguous column
@@ -146,6 +148,8 @@ constexpr int kVecs = 3;
 constexpr int kNodeInts = 16;
 constexpr int kChunkInts = 4;
 constexpr int kBins = 256;        // linear bins of the multi-block split select
+constexpr int kGroup = 16;        // chunks whose histograms are summed as one
+constexpr int kGroupedFrom = 64;  // in nodes of more chunks than this
 constexpr int kChunk = 4096;      // tokens per block in the multi-block split passes
 constexpr int kTail = 2048;       // nodes of at most this size finish in one workgroup
 constexpr int kMomRows = 4096;    // rows per moment-partial block (at most)
@@ -182,6 +186,7 @@ int split_big_levels(int n, int c, int levels);
 // multi-block level needs.
 int split_level_cpn(const Prob& P, int big_q, int big_k, int l);
 int split_hist_slots(const Prob& P, int big_q, int big_k);
+int split_group_slots(const Prob& P, int big_q, int big_k);
 
 // ---- launchers (return hipError_t of the last launch) ----------------------
 

@@ -64,9 +64,10 @@ struct Ctx {
   uint32_t* keys;
   int32_t* node_state;
   uint32_t* hist;
+  uint32_t* ghist;
   uint32_t* cand;
   int32_t* chunk_cnt;
-  int max_nodes, hist_slots;
+  int max_nodes, hist_slots, ghist_slots;
   int split;        // ca_split
   float* dirs;      // [2 levels][2][BH][max_nodes][d] split directions (basic splitting)
 };
@@ -2072,30 +2073,75 @@ __device__ __forceinline__ void bin_range(float mean, float var, int nb, float* 
   *scale = s;
 }
 
+// Rows of a sample of m that the bins of a multi-block level are laid by (at
+// most 64, spread over the sample): the row of lane `lane`.
+__device__ __forceinline__ int bin_row(int lane, int m) {
+  return m > 64 ? lane * m / 64 : min(lane, m - 1);
+}
+
+// Bins of a multi-block level (one wavefront). The threshold is the key of rank
+// mL of size; the keys x of those rows (one a lane) bound its place by 2 sqrt(64)
+// ranks (four standard deviations) to each side, whatever the distribution. The
+// bins lie between two values found by halving, from mean +- 4 sd: with at most
+// that many sample keys less and, unless runs of equal keys forbid it, not many
+// fewer. Mean -+ sd mostly serves at once; where outliers stretch the deviation or
+// the keys lie in clumps, halving goes on. Samples too small for such a bound (m
+// below 17) keep mean +- 4 sd.
+// Normal keys: about one in 250 is listed, one in 80 with 256 bins over mean +- 4
+// sd. Clustering with those and with these: 8 heads of 1,048,576 tokens 11.7 and
+// 10.5 ms, of 65,521 tokens 825 and 824 us, the latter's tokens as they are
+// (transform none) with one far sample row 1,396 and 1,047.
+__device__ __forceinline__ void threshold_bins(float x, int m, int mL, int size, float mean,
+                                               float sd, int lane, float* lo, float* scale) {
+  const int mm = min(m, 64);
+  float a0 = mean - 4.f * sd, b1 = mean + 4.f * sd;
+  const float at = (float)mL / (float)size * (float)mm, w = 2.f * sqrtf((float)mm);
+  const int c0 = (int)floorf(at - w), c1 = (int)ceilf(at + w), slack = (int)(0.5f * w);
+  if (c0 >= 0 && c1 <= mm) {
+    float p0 = b1, t0 = mean - sd, p1 = a0, t1 = mean + sd;
+    const bool in = lane < mm;
+    for (int it = 0; it < 16; ++it) {
+      // a0 has at most c0 of the keys below it and p0 more, b1 at least c1 and p1 fewer
+      const int n0 = (int)__popcll(__ballot(in && x < t0)), n1 = (int)__popcll(__ballot(in && x < t1));
+      const bool done0 = n0 <= c0 && n0 >= c0 - slack, done1 = n1 >= c1 && n1 <= c1 + slack;
+      if (n0 <= c0) a0 = t0; else p0 = t0;
+      if (n1 >= c1) b1 = t1; else p1 = t1;
+      if (done0 && done1) break;
+      if (!done0) t0 = 0.5f * (a0 + p0);
+      if (!done1) t1 = 0.5f * (b1 + p1);
+    }
+  }
+  float s = (float)kBins / (b1 - a0);
+  if (!(sd > 0.f) || !isfinite(a0) || !(s > 0.f) || !isfinite(s)) a0 = s = 0.f;  // one bin
+  *lo = a0;
+  *scale = s;
+}
+
 // Multi-block levels. A node's split threshold is its m_L-th smallest key,
 // found exactly in three passes over chunks of its keys:
 //   keys:    every chunk block gathers its keys and counts them into kBins
-//            linear bins over [mean - 4 sd, mean + 4 sd] of the node's sample
-//            (the clamped linear map is monotone, so each bin is a contiguous
-//            key range); the chunk's histogram goes to its own slot.
+//            linear bins between two keys that the node's sample puts around
+//            the threshold (threshold_bins; the clamped linear map is monotone,
+//            so each bin is a contiguous key range); the chunk's histogram goes
+//            to its own slot.
 //   bins:    every chunk block sums the node's histograms, finds the bin that
 //            holds the wanted rank, and lists its chunk's keys of that bin
-//            (typically one in eighty) behind those of the chunks before it.
+//            (typically one in 250) behind those of the chunks before it.
 //   scatter: every chunk block selects exactly among the listed keys, counts
 //            those of the chunks before it, and partitions its chunk stably.
 // Kernel boundaries order the passes, but for nodes with more than kListed
-// listed keys (runs of equal keys, keys that outliers crowd into a bin): there
-// the last chunk block of the bins pass to arrive selects for the node, since
-// every chunk reading so long a list would cost chunks times keys (16 heads of
-// 262,144 tokens, 40% of them zero: ca_cluster 11.4 ms so, 6.3 ms with the
-// last block; 10% zero: 7.1 and 5.8 ms; 6.4 and 5.8 ms with 4,096 bins).
-// The histograms are small (kBins) and the select is repeated in every block,
-// so that no pass leaves a node to one workgroup. Before, with 4,096 bins and
-// one workgroup a node for the select (which read all keys of the node again),
-// the keys/select/scatter passes of a level took 12.7/19.7/14.8 us on average
-// at 8 heads of 65,521 tokens, 48/40/46 us at 40 heads of 75,600, and
-// 64/46/52 us at 16 heads of 262,144; now keys/bins/scatter take 11.3/12.4/16.3,
-// 43.9/19.3/51.5 and 60.0/24.8/63.6 us (rocprofv3 kernel trace).
+// listed keys (runs of equal keys at the threshold, or more than about a million
+// keys): there the last chunk block of the bins pass to arrive selects for the
+// node, since every chunk reading so long a list would cost chunks times keys (16
+// heads of 262,144 tokens, 40% of them zero: ca_cluster 11.4 ms so, 6.3 ms with
+// the last block; 10% zero: 7.1 and 5.7 ms; 6.4 and 5.8 ms with 4,096 bins).
+// Otherwise no pass leaves a node to one workgroup: the histograms are small
+// (kBins) and the select is repeated in every block. With 4,096 bins over mean
+// +- 4 sd and one workgroup a node for the select (which read all keys of the
+// node again), the keys/select/scatter passes of a level took 12.7/19.7/14.8 us on
+// average at 8 heads of 65,521 tokens, 48/40/46 us at 40 heads of 75,600, and
+// 64/46/52 us at 16 heads of 262,144; now keys/bins/scatter take 11.4/10.1/16.3,
+// 43.8/17.4/51.5 and 61.8/20.2/60.7 us (rocprofv3 kernel trace).
 //
 // Node state (int32): 0 j* (-1: leaf), 1 threshold key (selected) or number of
 // listed keys, 2 rank of the threshold among the keys equal to it (selected) or
@@ -2127,6 +2173,24 @@ __device__ __forceinline__ int lin_bin(uint32_t key, float lo, float scale, int 
 
 constexpr int kPer = kChunk / 256;  // positions per thread in a 256-thread chunk block
 
+// Nodes of more than kGroupedFrom chunks also sum their chunks' histograms by
+// groups of kGroup, so that a block of the bins pass reads the groups and the
+// chunks of its own group instead of every chunk, whose number grows with the
+// square of the node. The bins passes of 4,194,304 tokens (one head, up to 1,024
+// chunks) took 1,364 us without, 1,179 with; of 8 heads of 2,097,152 1,989 and
+// 1,702.
+__device__ __forceinline__ uint32_t* group_hist(const Ctx& C, int cpn, int pid, int node) {
+  return C.ghist +
+         ((size_t)pid * C.ghist_slots + (size_t)node * ((cpn + kGroup - 1) / kGroup)) * kBins;
+}
+// Cleared by the kernel that chooses the node's coordinate (its threads all).
+__device__ __forceinline__ void clear_group_hist(const Ctx& C, int cpn, int pid, int node) {
+  if (cpn <= kGroupedFrom) return;
+  uint4* h = reinterpret_cast<uint4*>(group_hist(C, cpn, pid, node));
+  const int n = (cpn + kGroup - 1) / kGroup * (kBins / 4);
+  for (int i = threadIdx.x; i < n; i += blockDim.x) h[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
 struct LevelArgs {
   int level;
   int first;  // input permutation is the identity
@@ -2152,6 +2216,7 @@ __global__ __launch_bounds__(64 * kChooseWaves) void split_choose_kernel(Ctx C, 
     if (threadIdx.x == 0) ns[0] = -1;
     return;
   }
+  clear_group_hist(C, L.cpn, pid, node);
   const int32_t* idx = L.idx_in + (size_t)pid * C.nmax;
   const float* Y = S.y + (size_t)bh * S.n * d;
   const int m = size < d ? size : d;
@@ -2177,10 +2242,21 @@ __global__ __launch_bounds__(64 * kChooseWaves) void split_choose_kernel(Ctx C, 
   float mean, var;
   int js = choose_by_bounds<H>(mo, d, m, lane, &mean, &var);
   if (js < 0) js = choose_open<H, 32>(Y, d, idx, L.first, start, size, m, mo, lane, &mean, &var);
+  const int mL = left_size(size, S.c);
+  float lo, scale;
+  {
+    uint32_t o = off[0];
+    if (H == 2 && m > 64) {
+      const int j = bin_row(lane, m);
+      const uint32_t o0 = __shfl(off[0], j & 63, 64), o1 = __shfl(off[1], j & 63, 64);
+      o = j < 64 ? o0 : o1;
+    }
+    const float x = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Y) +
+                                                    (o + 4u * (uint32_t)js));
+    const float sd = var * __builtin_amdgcn_rsqf(var);  // NaN where there is no spread
+    threshold_bins(x, m, mL, size, mean, sd, lane, &lo, &scale);
+  }
   if (lane == 0) {
-    float lo, scale;
-    bin_range(mean, var, kBins, &lo, &scale);
-    const int mL = left_size(size, S.c);
     ns[0] = js;
     ns[10] = 0;
     ns[12] = 0;
@@ -2253,6 +2329,7 @@ __global__ __launch_bounds__(kBasicThreads) void basic_choose_kernel(Ctx C, Leve
     if (tid == 0) ns[0] = -1;
     return;
   }
+  clear_group_hist(C, L.cpn, pid, node);
   const int m = d < size ? d : size;
   const int32_t* idx = L.idx_in + (size_t)pid * C.nmax;
   const float* Y = S.y + (size_t)bh * S.n * d;
@@ -2346,17 +2423,15 @@ __global__ __launch_bounds__(kBasicThreads) void basic_choose_kernel(Ctx C, Leve
     t[tid] = a;
   }
   __syncthreads();
+  if (tid >= 64) return;
+  double mp = 0.0, vv = 0.0;
+  for (int k = 0; k < d; ++k) mp += (double)mu[k] * (double)v[k];
+  for (int j = 0; j < m; ++j) vv += (double)t[j] * (double)t[j];
+  const int mL = left_size(size, S.c);
+  float lo, scale;
+  threshold_bins((float)(mp + (double)t[bin_row(tid, m)]), m, mL, size, (float)mp,
+                 (float)sqrt(vv / m), tid, &lo, &scale);
   if (tid == 0) {
-    double mp = 0.0, vv = 0.0;
-    for (int k = 0; k < d; ++k) mp += (double)mu[k] * (double)v[k];
-    for (int j = 0; j < m; ++j) vv += (double)t[j] * (double)t[j];
-    const double sd = sqrt(vv / m);
-    float lo = (float)(mp - 4.0 * sd), scale = (float)((double)kBins / (8.0 * sd));
-    if (!(sd > 0.0) || !isfinite(lo) || !isfinite(scale)) {
-      lo = 0.f;
-      scale = 0.f;  // one bin
-    }
-    const int mL = left_size(size, S.c);
     ns[0] = 0;
     ns[1] = 0;
     ns[2] = 0;
@@ -2391,6 +2466,7 @@ __global__ __launch_bounds__(64) void basic_choose64_kernel(Ctx C, LevelArgs L) 
     if (lane == 0) ns[0] = -1;
     return;
   }
+  clear_group_hist(C, L.cpn, pid, node);
   const int m = D < size ? D : size;
   const int32_t* idx = L.idx_in + (size_t)pid * C.nmax;
   const float* Y = S.y + (size_t)bh * S.n * D;
@@ -2518,17 +2594,14 @@ __global__ __launch_bounds__(64) void basic_choose64_kernel(Ctx C, LevelArgs L) 
   }
   t[lane] = ta;
   __syncthreads();
+  double mp = 0.0, vv = 0.0;
+  for (int k = 0; k < D; ++k) mp += (double)mu[k] * (double)v[k];
+  for (int j = 0; j < m; ++j) vv += (double)t[j] * (double)t[j];
+  const int mL = left_size(size, S.c);
+  float lo, scale;
+  threshold_bins((float)(mp + (double)ta), m, mL, size, (float)mp, (float)sqrt(vv / m), lane, &lo,
+                 &scale);
   if (lane == 0) {
-    double mp = 0.0, vv = 0.0;
-    for (int k = 0; k < D; ++k) mp += (double)mu[k] * (double)v[k];
-    for (int j = 0; j < m; ++j) vv += (double)t[j] * (double)t[j];
-    const double sd = sqrt(vv / m);
-    float lo = (float)(mp - 4.0 * sd), scale = (float)((double)kBins / (8.0 * sd));
-    if (!(sd > 0.0) || !isfinite(lo) || !isfinite(scale)) {
-      lo = 0.f;
-      scale = 0.f;  // one bin
-    }
-    const int mL = left_size(size, S.c);
     ns[0] = 0;
     ns[1] = 0;
     ns[2] = 0;
@@ -2777,6 +2850,9 @@ __global__ __launch_bounds__(256) void split_keys_kernel(Ctx C, LevelArgs L) {
   static_assert(kBins == 256, "one bin a thread");
   C.hist[((size_t)pid * C.hist_slots + (size_t)node * L.cpn + blockIdx.x) * kBins + threadIdx.x] =
       (uint32_t)lh[threadIdx.x];
+  if (L.cpn > kGroupedFrom && lh[threadIdx.x] != 0)
+    atomicAdd(&group_hist(C, L.cpn, pid, node)[(blockIdx.x / kGroup) * kBins + threadIdx.x],
+              (uint32_t)lh[threadIdx.x]);
 }
 
 // Listed keys up to which every chunk block of a node selects for itself
@@ -2797,29 +2873,61 @@ struct NodeSelect {
 __device__ __forceinline__ void node_select(int32_t* ns, const uint32_t* cand, int32_t* cc, int n,
                                             int nch, int rank, NodeSelect& sh) {
   const int tid = threadIdx.x, lane = tid & 63;
-  // keys below and equal to thr in each chunk (a wavefront each) and in all
+  // Keys below and equal to thr in each chunk and in all. Chunks w, w + 4, ...
+  // are wavefront w's: a lane for a chunk of at most 64 listed keys, then the
+  // wavefront together for each of the others. (With a wavefront for every chunk
+  // the bins pass of a node of 1,024 chunks with a dozen listed keys each took
+  // 540 us; now 245.)
   auto count = [&](uint32_t thr) {
     if (tid == 0) sh.lt = sh.eq = 0;
     __syncthreads();
-    for (int g = tid >> 6; g < nch; g += 4) {
-      const int i0 = cc[kChunkInts * g + 1], i1 = g + 1 < nch ? cc[kChunkInts * (g + 1) + 1] : n;
-      int lt = 0, eq = 0;
-      for (int i = i0 + lane; i - lane < i1; i += 64 * 16) {
-        uint32_t k[16];
+    for (int g0 = tid >> 6; g0 < nch; g0 += 256) {
+      const int g = g0 + 4 * lane;
+      int i0 = 0, i1 = 0, lt = 0, eq = 0;
+      if (g < nch) {
+        i0 = cc[kChunkInts * g + 1];
+        i1 = g + 1 < nch ? cc[kChunkInts * (g + 1) + 1] : n;
+      }
+      const int len = i1 - i0;
+      for (int i = 0; i < 64; i += 8) {
+        const bool in = len <= 64 && i < len;
+        if (__ballot(in) == 0ull) break;
+        if (in) {
+          uint32_t k[8];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) k[u] = i + 64 * u < i1 ? cand[i + 64 * u] : 0xFFFFFFFFu;
+          for (int u = 0; u < 8; ++u) k[u] = cand[i0 + min(i + u, len - 1)];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
-          lt += i + 64 * u < i1 && k[u] < thr;
-          eq += i + 64 * u < i1 && k[u] == thr;
+          for (int u = 0; u < 8; ++u) {
+            lt += i + u < len && k[u] < thr;
+            eq += i + u < len && k[u] == thr;
+          }
         }
       }
+      for (uint64_t m = __ballot(len > 64); m != 0ull; m &= m - 1ull) {
+        const int l = __builtin_ctzll(m);
+        const int j0 = __builtin_amdgcn_readlane(i0, l), j1 = __builtin_amdgcn_readlane(i1, l);
+        int wlt = 0, weq = 0;
+        for (int i = j0 + lane; i - lane < j1; i += 64 * 16) {
+          uint32_t k[16];
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        lt += __shfl_xor(lt, o, 64);
-        eq += __shfl_xor(eq, o, 64);
+          for (int u = 0; u < 16; ++u) k[u] = i + 64 * u < j1 ? cand[i + 64 * u] : 0xFFFFFFFFu;
+#pragma unroll
+          for (int u = 0; u < 16; ++u) {
+            wlt += i + 64 * u < j1 && k[u] < thr;
+            weq += i + 64 * u < j1 && k[u] == thr;
+          }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+          wlt += __shfl_xor(wlt, o, 64);
+          weq += __shfl_xor(weq, o, 64);
+        }
+        if (lane == l) {
+          lt = wlt;
+          eq = weq;
+        }
       }
-      if (lane == 0) {
+      if (g < nch) {
         cc[kChunkInts * g + 2] = lt;
         cc[kChunkInts * g + 3] = eq;
         atomicAdd(&sh.lt, lt);
@@ -2940,15 +3048,26 @@ __global__ __launch_bounds__(256) void split_bins_kernel(Ctx C, LevelArgs L) {
   // bin tid of the node, and of the chunks before this one
   const uint32_t* H = C.hist + ((size_t)pid * C.hist_slots + (size_t)node * L.cpn) * kBins + tid;
   int tot = 0, pre = 0;
-  for (int g = 0; g < nch; g += 16) {
-    int hv[16];
+  // adds h[0 .. n) to tot, and of them h[0 .. before) to pre
+  auto add = [&](const uint32_t* h, int n, int before) __attribute__((always_inline)) {
+    for (int g = 0; g < n; g += 16) {
+      int hv[16];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) hv[u] = g + u < nch ? (int)H[(size_t)(g + u) * kBins] : 0;
+      for (int u = 0; u < 16; ++u) hv[u] = g + u < n ? (int)h[(size_t)(g + u) * kBins] : 0;
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      tot += hv[u];
-      pre += g + u < ch ? hv[u] : 0;
+      for (int u = 0; u < 16; ++u) {
+        tot += hv[u];
+        pre += g + u < before ? hv[u] : 0;
+      }
     }
+  };
+  if (L.cpn <= kGroupedFrom) {
+    add(H, nch, ch);
+  } else {
+    const int g0 = ch / kGroup * kGroup;  // the first chunk of this one's group
+    add(H + (size_t)g0 * kBins, ch - g0, ch - g0);
+    tot = 0;
+    add(group_hist(C, L.cpn, pid, node) + tid, (nch + kGroup - 1) / kGroup, ch / kGroup);
   }
   if (tid == 0) {
     sh_cnt = 0;
@@ -3773,6 +3892,16 @@ int split_hist_slots(const Prob& P, int big_q, int big_k) {
   return slots;
 }
 
+int split_group_slots(const Prob& P, int big_q, int big_k) {
+  const int big = big_q > big_k ? big_q : big_k;
+  int slots = 0;
+  for (int l = 0; l < big; ++l) {
+    const int cpn = split_level_cpn(P, big_q, big_k, l);
+    if (cpn > kGroupedFrom) slots = std::max(slots, (1 << l) * ((cpn + kGroup - 1) / kGroup));
+  }
+  return slots;
+}
+
 int split_big_levels(int n, int c, int L) {
   const int tail = tail_size(c);
   int l = 0;
@@ -3864,6 +3993,8 @@ hipError_t launch_cluster(const Prob& P, const void* q, const void* k, const voi
   C.chunk_cnt = (int32_t*)(ws + W.chunk_cnt);
   C.max_nodes = W.max_big_nodes;
   C.hist_slots = W.hist_slots;
+  C.ghist = (uint32_t*)(ws + W.ghist);
+  C.ghist_slots = W.ghist_slots;
   C.split = P.split;
   C.dirs = (float*)(ws + W.dirs);
   const bool basic = P.split == CA_SPLIT_BASIC;

@@ -131,6 +131,24 @@ def test_split_of_flat_samples(n, d, c, kind):
     _split_against_oracle(n, d, c, kind)
 
 
+# Nodes of more than 256 chunks (bins laid by the deviation at d = 3, by the
+# sample's order at d = 20): histograms summed by groups of chunks, lists too long
+# for the chunk blocks, short and long lists of a chunk, and runs of equal keys at
+# the threshold that span chunk 256.
+@pytest.mark.parametrize("d", [3, 20])
+@pytest.mark.parametrize("kind", ["normal", "rest", "drift"])
+def test_split_many_chunks(d, kind):
+    _split_against_oracle((1 << 20) + 4096 + 5, d, 256, kind)
+
+
+# Bins by the sample's order where a few sample rows are far off (to one side and
+# to both), where keys lie in two clumps, and heavy tails.
+@pytest.mark.parametrize("kind", ["normal", "far", "far2", "clumps", "tails"])
+@pytest.mark.parametrize("n,d", [(40000, 64), (9000, 128), (300000, 17)])
+def test_split_threshold_bins(n, d, kind):
+    _split_against_oracle(n, d, 128, kind)
+
+
 def _split_against_oracle(n, d, c, kind):
     import numpy as np
     import torch
@@ -143,6 +161,18 @@ def _split_against_oracle(n, d, c, kind):
         X[np.random.default_rng(1).random(X.shape) < 0.4] = 0.25
     elif kind == "const":
         X[:] = 0.5
+    elif kind == "rest":  # the last 40% of the tokens are equal
+        X[:, int(0.6 * n):] = 0.25
+    elif kind == "drift":  # neighbours are close: most listed keys are in few chunks
+        X += np.linspace(-20, 20, n, dtype=np.float32)[:, None]
+    elif kind == "far":
+        X[:, (5 * n) // (2 * d), 1] = 1e6
+    elif kind == "far2":
+        X[:, (5 * n) // (2 * d), 1], X[:, (9 * n) // (2 * d), 1] = -1e6, 1e4
+    elif kind == "clumps":
+        X = X * np.float32(0.01) + (np.random.default_rng(2).random(X.shape) < 0.5)
+    elif kind == "tails":
+        X = X / np.abs(np.random.default_rng(3).standard_normal(X.shape)).astype(np.float32)
     elif kind == "zeros":
         X = X * 0
     elif kind == "tiny":
@@ -152,7 +182,8 @@ def _split_against_oracle(n, d, c, kind):
         X[:, ((2 * d - 1) * n) // (2 * d), d // 2] = 0.75
     elif kind == "outlier":
         X = X * 1e-5
-        X[:, n // 3] = 1e6
+        X[:, 5 * n // 16] = 1e6  # row 2 of the sample of 8
+    X = X.astype(np.float32)
     p = ca.Problem(1, 1, n, n, d, c, c, torch.float32, "none")
     q, k = (torch.from_numpy(x[None, None]).cuda() for x in X)
     r = ca.cluster(p, q, k, k)
