@@ -637,7 +637,7 @@ __global__ __launch_bounds__(256) void topk_wave_kernel(const float* __restrict_
 // One more key in bin b for every lane with `in`; AGG: the lanes that share the
 // first one's bin add once (rows handed over by the filter below, whose scores
 // crowd into few bins: 16,384 rows of 8,192 equal scores, 619 us without,
-// about 325 with).
+// about 355 with).
 template <bool AGG>
 __device__ __forceinline__ void count(int* bins, int b, bool in, int lane) {
   if constexpr (AGG) {
@@ -889,37 +889,52 @@ __device__ __forceinline__ void topk_block(const float (&v)[VPL], int nkc, int k
   }
 }
 
-// REST: only the rows that the filter below left, marked by a first entry of -1.
+// REST: only the rows that the filter below left, marked by a first entry of -1;
+// a block looks at every gridDim.x-th row (a block for each of 65,536 rows took
+// 14 us to find none).
+constexpr int kRestRows = 32;  // rows a block looks at, at most
 template <int VPL, int NWV, bool REST>
 __global__ __launch_bounds__(64 * NWV, 4) void topk_block_kernel(const float* __restrict__ S, int nkc,
-                                                              int k, int vec4,
+                                                              int k, int vec4, int nrows,
                                                               int32_t* __restrict__ lists) {
   constexpr int G = VPL / 4;
   static_assert(VPL % 4 == 0, "float4 groups");
   __shared__ TopkBlock<NWV> sh;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const size_t row = blockIdx.x;
-  if (REST && lists[row * k] >= 0) return;
-  const float* s = S + row * nkc;
   const int wbase = 64 * VPL * w;
   auto pos_of = [&](int g, int e) { return wbase + 256 * g + 4 * lane + e; };
-  float v[VPL];
+  auto select = [&](size_t row) __attribute__((always_inline)) {
+    const float* s = S + row * nkc;
+    float v[VPL];
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    const int p0 = pos_of(g, 0);
-    if (vec4) {
-      float4 x = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-      if (p0 < nkc) x = *(const float4*)(s + p0);  // nkc % 4 == 0: whole float4
-      v[4 * g] = x.x;
-      v[4 * g + 1] = x.y;
-      v[4 * g + 2] = x.z;
-      v[4 * g + 3] = x.w;
-    } else {
+    for (int g = 0; g < G; ++g) {
+      const int p0 = pos_of(g, 0);
+      if (vec4) {
+        float4 x = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+        if (p0 < nkc) x = *(const float4*)(s + p0);  // nkc % 4 == 0: whole float4
+        v[4 * g] = x.x;
+        v[4 * g + 1] = x.y;
+        v[4 * g + 2] = x.z;
+        v[4 * g + 3] = x.w;
+      } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[4 * g + e] = p0 + e < nkc ? s[p0 + e] : -INFINITY;
+        for (int e = 0; e < 4; ++e) v[4 * g + e] = p0 + e < nkc ? s[p0 + e] : -INFINITY;
+      }
+    }
+    topk_block<VPL, NWV, REST>(v, nkc, k, lists + row * k, sh);
+  };
+  if constexpr (!REST) {
+    select(blockIdx.x);
+  } else {
+    // every wavefront reads all marks before the block's first list is written
+    const size_t mine = blockIdx.x + (size_t)lane * gridDim.x;
+    uint64_t left = __ballot(lane < kRestRows && mine < (size_t)nrows &&
+                             lists[mine < (size_t)nrows ? mine * k : 0] < 0);
+    for (; left != 0ull; left &= left - 1ull) {
+      __syncthreads();
+      select(blockIdx.x + (size_t)__builtin_ctzll(left) * gridDim.x);
     }
   }
-  topk_block<VPL, NWV, REST>(v, nkc, k, lists + row * k, sh);
 }
 
 // Exact top-k of a row that is longer than k, one row per block of four
@@ -946,10 +961,10 @@ __global__ __launch_bounds__(64 * NWV, 4) void topk_block_kernel(const float* __
 // What bounds it: reading the row. The block kernel counts every score into LDS
 // bins, recomputes bins and keys in each later pass and writes its list by a
 // scan of every float4 group; here a score costs a maximum, a multiply-add and
-// two comparisons. 16,384 rows of 8,192, k = 64: 286 -> 117 us (both launches,
-// 4.6 TB/s); k = 819: 290 -> 171; rows of 5,000, k = 312: 404 -> 142. Scores
-// of 17 values 357 -> 150, a random rest masked by -inf 799 -> 128,
-// under one outlier 849 -> 151, all equal 619 -> 442 (all k = 64 of 8,192).
+// two comparisons. 16,384 rows of 8,192, k = 64: 286 -> 114 us (both launches,
+// 4.7 TB/s); k = 819: 290 -> 167; rows of 5,000, k = 312: 404 -> 138. Scores
+// of 17 values 357 -> 146, a random rest masked by -inf 799 -> 117,
+// under one outlier 849 -> 146, all equal 619 -> 472 (all k = 64 of 8,192).
 constexpr int kFiltCand = 2048;  // listed scores
 
 template <int VPL, int NG>
@@ -1442,12 +1457,15 @@ hipError_t launch_select(const Prob& P, const float* cq, const float* ck, const 
     // than with a whole row in one wavefront's registers); by the filter where
     // the row makes at least 2 k groups (with fewer, the bound lets most of the
     // row through; just past the line, k = 1,024 of 8,192, 177 against 279 us)
+    // (enough blocks for the second launch to fill the chip, should all rows be left)
+    const dim3 rest((unsigned)std::max(std::min(nrows, (size_t)2048),
+                                       (nrows + kRestRows - 1) / kRestRows));
 #define CA_TOPK_FILTER(V, NG)                                                                  \
   if (P.nkc <= 256 * V && (int64_t)P.nkc * NG >= (int64_t)2 * k * V) {                         \
     hipLaunchKernelGGL((topk_filter_kernel<V, NG>), dim3((unsigned)nrows), dim3(256), 0, st, S, \
                        P.nkc, k, lists);                                                       \
-    hipLaunchKernelGGL((topk_block_kernel<V, 4, true>), dim3((unsigned)nrows), dim3(256), 0,    \
-                       st, S, P.nkc, k, vec4, lists);                                          \
+    hipLaunchKernelGGL((topk_block_kernel<V, 4, true>), rest, dim3(256), 0, st, S, P.nkc, k,    \
+                       vec4, (int)nrows, lists);                                               \
     return hipGetLastError();                                                                  \
   }
     CA_TOPK_FILTER(16, 1)
@@ -1462,7 +1480,7 @@ hipError_t launch_select(const Prob& P, const float* cq, const float* ck, const 
 #define CA_TOPK_BLOCK(V)                                                                      \
   if (P.nkc <= 256 * V) {                                                                     \
     hipLaunchKernelGGL((topk_block_kernel<V, 4, false>), dim3((unsigned)nrows), dim3(256), 0, st, S, \
-                       P.nkc, k, vec4, lists);                                                \
+                       P.nkc, k, vec4, (int)nrows, lists);                                    \
     return hipGetLastError();                                                                 \
   }
     CA_TOPK_BLOCK(16)

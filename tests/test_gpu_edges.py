@@ -244,6 +244,24 @@ def test_topk_filter_edges(nkc, k, kind):
     assert np.array_equal(got.cpu().numpy()[0], ref.topk(S.astype(np.float64), k))
 
 
+@pytest.mark.parametrize("nkc,k", [(2100, 20), (4500, 300)])
+def test_topk_filter_many_rows(nkc, k):
+    """More rows than the blocks that look for the filter's leftovers: some rows
+    of each kind, most of them without any."""
+    import numpy as np
+    import torch
+    import paper_2608_26965_amd as ca
+    from oracle import ref
+    rng = np.random.default_rng(nkc)
+    S = rng.standard_normal((4301, nkc)).astype(np.float32)
+    S[::7] = 1.5
+    S[5:3000:11, k // 2:] = -np.inf
+    S[4300] = -np.inf
+    p = ca.Problem(1, 1, 4301 * 64, nkc * 64, 64, 64, 64, torch.float32)
+    got, _ = ca.select(p, None, None, k, scores_in=torch.from_numpy(S[None]).cuda())
+    assert np.array_equal(got.cpu().numpy()[0], ref.topk(S.astype(np.float64), k))
+
+
 # bf16 compensation: from 257 query clusters of 64 on, two share a workgroup;
 # heads with an odd number of clusters (the last one alone), a single one, a
 # remainder, several stages of centroids, partners with different lists, and a
