@@ -384,7 +384,7 @@ __device__ __forceinline__ double recip64(double x) {
 // Number of eigenvalues below x of the block [s, t) of the scaled
 // tridiagonal matrix, tq[i] = (diagonal i, squared off-diagonal i - 1): the
 // sign changes of the sequence 1, p_s, ..., p_{t-1} of leading minors of
-// T - x I (a zero minor counts as a change).
+// T - x I (a zero minor counts as positive).
 __device__ __forceinline__ int sturm_below(const double2* tq, int s, int t, double x) {
   // The minors' sign bits are shifted into a word and the changes counted
   // eight at a time: four instructions a step, and with one wavefront a SIMD
@@ -1831,9 +1831,8 @@ __device__ __forceinline__ int sample_pos(int j, int size, int m) {
 // wavefront: lane t owns coordinates t and t + 64. fp64, two passes over the
 // rows in order, mean = sum/m, variance = sum((y - mean)^2)/m, no contraction;
 // ties go to the lowest coordinate. The sample rows are located first (lane j
-// holds the row of sample j and j + 64), then read in batches of B
-// independent loads; with at most B samples both passes use the one batch, so
-// the whole choice costs two memory round trips (B = 64 where registers allow).
+// holds the row of sample j and j + 64), then read in batches of B independent
+// loads, once for each pass; at most B samples are read once.
 template <int B>
 __device__ int choose_coordinate(const float* __restrict__ Y, int d, const int32_t* idx,
                                  bool identity, int start, int size, int lane,
@@ -1876,7 +1875,7 @@ __device__ int choose_coordinate(const float* __restrict__ Y, int d, const int32
     const double mean = acc / (double)m;
     double acc2 = 0.0;
     for (int j0 = 0; j0 < m; j0 += B) {
-      if (B < 64 || m > B) load(j0);  // (a single batch of 64 is still in registers)
+      if (m > B) load(j0);  // (a single batch is still in registers)
 #pragma unroll
       for (int u = 0; u < B; ++u)
         if (j0 + u < m) {

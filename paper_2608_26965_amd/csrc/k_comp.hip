@@ -496,7 +496,6 @@ __global__ __launch_bounds__(64 * NW, kF32Waves) void comp_f32_kernel(
   if (do_comp) {
     f32x4 qf[DP / 16];
     f32_load_rows<DP>(qp + (qrow0 + min(q0 + (lane & 15), cq - 1)) * d, d, lane >> 4, qf);
-    // tiles past the end read the bitmap up to the next whole step
     const int ntile = (nkc + 15) / 16;
     const int nwords = min(kMaskWords, (nkc + 31) / 32);
     for (int e = tid; e < nwords; e += NT) selmask[e] = 0u;

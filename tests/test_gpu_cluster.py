@@ -229,16 +229,16 @@ def test_basic_split_parity(dt, n, d, c, xf):
             assert np.abs(nrm[nrm > 0] - 1.0).max() < 1e-4
 
 
-# Inputs whose multi-block split levels take the select pass's fallback
-# paths. "duplicates": 60% of the queries and 70% of the keys are one repeated
+# Inputs whose multi-block split levels list more keys than the chunk blocks
+# select among (4,096), so that one workgroup selects for the node.
+# "duplicates": 60% of the queries and 70% of the keys are one repeated
 # row, so at the root the wanted rank falls inside a run of more than 8192
 # equal keys (a run of D equal values covers rank r whatever its position when
-# D > max(r, s - r)); that linear bin overflows the select pass's candidate
-# buffer and the threshold is found by streaming the node's keys from memory.
-# "flat_root_sample": the root's subsample rows are all equal, so its spread
-# is zero and every key lands in one bin (and streams). "all_identical": every
-# node of every level is in that case, and the order is decided by the
-# original index alone.
+# D > max(r, s - r)), all in the threshold's bin; the most frequent of a few
+# listed keys is the threshold. "flat_root_sample": the root's subsample rows are
+# all equal, so its spread is zero and every key lands in one bin (radix passes
+# over all of them). "all_identical": every node of every level is in that case,
+# and the order is decided by the original index alone.
 DEGENERATE = [
     # kind, n, transform, split
     ("duplicates", 40000, "none", "diag"),
@@ -283,8 +283,8 @@ def _reaches_fallback(kind, Y, c):
 def test_split_select_fallbacks(kind, n, xf, split):
     """Permutations bit-exact against the oracle's split of the exported
     coordinates on inputs with long runs of equal split keys and subsamples
-    without spread (padding rows, repeated tokens), which take the select
-    pass's streaming and one-bin paths; permuted copies, counts and centroids
+    without spread (padding rows, repeated tokens), whose thresholds' bins hold
+    thousands of keys; permuted copies, counts and centroids
     as in the other cluster tests."""
     import torch
     import paper_2608_26965_amd as ca
