@@ -20,6 +20,7 @@
 // order and no contraction, so it is reproducible bit for bit.
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "attn_tile.h"
@@ -3865,6 +3866,26 @@ __global__ __launch_bounds__(256) void gather_fast_kernel(Ctx C) {
 
 int tail_size(int c) { return c * 64 < kTail ? c * 64 : kTail; }
 
+// Largest node of level l: the sizes of a level are few (whole clusters in two
+// numbers, the node with the remainder, empty slots), so the levels are gone down by
+// distinct size. With node_range of each of a level's slots a call's plan took 164
+// us of host time where all levels are multi-block (basic splitting of 238,577
+// tokens, 13 levels); now 9.
+int level_max(int n, int c, int l) {
+  int sizes[16] = {n}, m = 1;
+  for (; l > 0; --l) {
+    int next[16], k = 0;
+    for (int i = 0; i < m; ++i) {
+      const int s = sizes[i], mL = s > c ? left_size(s, c) : s;
+      for (const int x : {mL, s - mL})
+        if (k < 16 && std::find(next, next + k, x) == next + k) next[k++] = x;
+    }
+    std::copy(next, next + k, sizes);
+    m = k;
+  }
+  return *std::max_element(sizes, sizes + m);
+}
+
 }  // namespace
 
 int split_level_cpn(const Prob& P, int big_q, int big_k, int l) {
@@ -3872,11 +3893,7 @@ int split_level_cpn(const Prob& P, int big_q, int big_k, int l) {
   for (int side = 0; side < 2; ++side) {
     const int n = side == 0 ? P.nq : P.nk, c = side == 0 ? P.cq : P.ck;
     if (l >= (side == 0 ? big_q : big_k)) continue;
-    for (int node = 0; node < (1 << l); ++node) {
-      int st, s;
-      node_range(n, c, l, node, &st, &s);
-      if (s > maxs) maxs = s;
-    }
+    maxs = std::max(maxs, level_max(n, c, l));
   }
   return (maxs + kChunk - 1) / kChunk;
 }
@@ -3904,16 +3921,7 @@ int split_group_slots(const Prob& P, int big_q, int big_k) {
 int split_big_levels(int n, int c, int L) {
   const int tail = tail_size(c);
   int l = 0;
-  while (l < L) {
-    int maxs = 0;
-    for (int node = 0; node < (1 << l); ++node) {
-      int st, s;
-      node_range(n, c, l, node, &st, &s);
-      if (s > maxs) maxs = s;
-    }
-    if (maxs <= tail) break;
-    ++l;
-  }
+  while (l < L && level_max(n, c, l) > tail) ++l;
   return l;
 }
 
