@@ -46,27 +46,34 @@ struct F32Tile {
 // Waves per SIMD of the kernels (their second launch bound): 256 registers.
 constexpr int kF32Waves = 2;
 
-// Calls f(std::integral_constant<int, NW>) with the number of wavefronts of a
-// workgroup, for ntile tiles of 16 keys and a launch of wgs workgroups: where
+// Calls f with two std::integral_constant<int>, the number of wavefronts of a
+// workgroup and the number of parts that its tiles are cut into, for ntile tiles of 16 keys and a launch of wgs workgroups: where
 // there is more than one workgroup a CU (256 of them), as many as get tiles,
 // since others only keep registers from the next workgroup; else all, which
 // then share the prologue and the output rows. 8 heads of 16,384 queries at
 // d = 64: attention on one tile 228 us with 8 wavefronts, 62 with one;
 // compensation with 8 tiles 424 and 157 (two). One head of 1,024 queries (64
 // workgroups), compensation with one tile: 20 us with 8 wavefronts, 23 with
-// one. Which wavefront has which tiles does not depend on their number, so
-// neither do the results.
+// one. Large launches with more tiles than four wavefronts' first steps take
+// four wavefronts, two parts each: two workgroups fit a CU, and one's loads and
+// merge run beside the other's products (40 heads of 6,553 tokens at d = 64:
+// attention on 79 tiles 1.84 -> 1.60 ms, compensation with 26 tiles 1.04 -> 0.83; one
+// head of 4,160 queries, 260 workgroups, both calls 70 -> 62 us). Which part has
+// which tiles does not depend on the number of wavefronts, so neither do the
+// results.
 template <int DP, typename F>
 void f32_wavefronts(int ntile, int64_t wgs, F&& f) {
   constexpr int TPS = F32Tile<DP>::TPS, NW = F32Tile<DP>::NW;
   if (wgs > 256 && ntile <= TPS)
-    f(std::integral_constant<int, 1>{});
+    f(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{});
   else if (wgs > 256 && ntile <= 2 * TPS)
-    f(std::integral_constant<int, 2>{});
+    f(std::integral_constant<int, 2>{}, std::integral_constant<int, 2>{});
   else if (NW == 4 || (wgs > 256 && ntile <= 4 * TPS))
-    f(std::integral_constant<int, 4>{});
+    f(std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
+  else if (wgs > 256)
+    f(std::integral_constant<int, 4>{}, std::integral_constant<int, NW>{});
   else
-    f(std::integral_constant<int, NW>{});
+    f(std::integral_constant<int, NW>{}, std::integral_constant<int, NW>{});
 }
 
 template <int DP>
@@ -86,15 +93,15 @@ __device__ __forceinline__ void f32_load_rows(const float* row, int d, int g,
   }
 }
 
-// Online softmax of one wavefront over tiles w * TPS + u + i * NW * TPS of
-// src, for which
+// Online softmax of one wavefront over tiles w * TPS + u + i * NP * TPS of
+// src (part w of NP), for which
 //   src.rows(T, kf)   the K operand of tile T (lane: key l % 16)
 //   src.vals(T, vf)   the V^T operand (lane: dim l % 16, keys 4 g .. 4 g + 3)
 //   src.logits(T, s)  scales the products and masks keys (-inf)
 //   src.mask_vals(T, vf)  clears values of masked keys that may not be finite
 //                     (late, so that the products above do not wait for them)
 // take any T; tiles at or past src.ntile are all masked.
-template <int DP, int NW, typename Src>
+template <int DP, int NP, typename Src>
 __device__ __forceinline__ void f32_online(const Src& src, const f32x4 (&qf)[F32Tile<DP>::NJ],
                                            int w, F32State<DP>& st) {
   constexpr int NJ = F32Tile<DP>::NJ, TPS = F32Tile<DP>::TPS;
@@ -102,7 +109,7 @@ __device__ __forceinline__ void f32_online(const Src& src, const f32x4 (&qf)[F32
   st.l = 0.f;
 #pragma unroll
   for (int j = 0; j < NJ; ++j) st.o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int t0 = w * TPS; t0 < src.ntile; t0 += NW * TPS) {
+  for (int t0 = w * TPS; t0 < src.ntile; t0 += NP * TPS) {
     f32x4 kf[TPS][NJ], vf[TPS][NJ], s[TPS];
 #pragma unroll
     for (int u = 0; u < TPS; ++u) src.rows(t0 + u, kf[u]);
@@ -165,20 +172,18 @@ __device__ __forceinline__ void f32_online(const Src& src, const f32x4 (&qf)[F32
   st.l += __shfl_xor(st.l, 32, 64);
 }
 
-// LDS of the merge of the wavefronts' states
-template <int DP, int NW>
+// LDS of the merge of the parts' states
+template <int DP, int NP>
 struct F32Merge {
-  float o[NW][DP][F32Tile<DP>::QP];
-  float f[NW][16];               // weight of wavefront w's part for a query
-  float m[NW][16], l[NW][16];
+  float o[NP][DP][F32Tile<DP>::QP];
+  float f[NP][16];               // weight of part w for a query
+  float m[NP][16], l[NP][16];
   float mx[16], sum[16];         // reference and sum of a query over all parts
 };
 
-// Merges the wavefronts' states: afterwards query q's sum of exponentials is
-// sum[q] against the reference mx[q] (sum 0: no key), and its output before
-// the division is sum_w f[w][q] o[w][t][q] (f32_merged).
-template <int DP, int NW>
-__device__ __forceinline__ void f32_merge(F32Merge<DP, NW>& M, const F32State<DP>& st, int w, int lane) {
+// Part w's state, for the merge
+template <int DP, int NP>
+__device__ __forceinline__ void f32_store(F32Merge<DP, NP>& M, const F32State<DP>& st, int w, int lane) {
   constexpr int NJ = F32Tile<DP>::NJ;
   const int q = lane & 15, g = lane >> 4;
 #pragma unroll
@@ -189,15 +194,35 @@ __device__ __forceinline__ void f32_merge(F32Merge<DP, NW>& M, const F32State<DP
     M.m[w][q] = st.m;
     M.l[w][q] = st.l;
   }
+}
+
+// The online softmax of all parts by NW wavefronts, stored for the merge
+template <int DP, int NW, int NP, typename Src>
+__device__ __forceinline__ void f32_parts(const Src& src, const f32x4 (&qf)[F32Tile<DP>::NJ],
+                                          F32Merge<DP, NP>& M, int w, int lane) {
+#pragma unroll 1
+  for (int p = w; p < NP; p += NW) {
+    F32State<DP> st;
+    f32_online<DP, NP>(src, qf, p, st);
+    f32_store<DP, NP>(M, st, p, lane);
+  }
+}
+
+// Merges the parts' states: afterwards query q's sum of exponentials is
+// sum[q] against the reference mx[q] (sum 0: no key), and its output before
+// the division is sum_w f[w][q] o[w][t][q] (f32_merged).
+template <int DP, int NP>
+__device__ __forceinline__ void f32_merge(F32Merge<DP, NP>& M, int w, int lane) {
+  const int q = lane & 15, g = lane >> 4;
   __syncthreads();
   if (w == 0 && g == 0) {
     float mx = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < NW; ++i) mx = fmaxf(mx, M.m[i][q]);
+    for (int i = 0; i < NP; ++i) mx = fmaxf(mx, M.m[i][q]);
     const float mu = mx == -INFINITY ? 0.f : mx;
     float sum = 0.f;
 #pragma unroll
-    for (int i = 0; i < NW; ++i) {
+    for (int i = 0; i < NP; ++i) {
       const float f = expf(M.m[i][q] - mu);
       M.f[i][q] = f;
       sum += f * M.l[i][q];
@@ -208,11 +233,11 @@ __device__ __forceinline__ void f32_merge(F32Merge<DP, NW>& M, const F32State<DP
   __syncthreads();
 }
 
-template <int DP, int NW>
-__device__ __forceinline__ float f32_merged(const F32Merge<DP, NW>& M, int q, int t) {
+template <int DP, int NP>
+__device__ __forceinline__ float f32_merged(const F32Merge<DP, NP>& M, int q, int t) {
   float x = 0.f;
 #pragma unroll
-  for (int i = 0; i < NW; ++i) x += M.f[i][q] * M.o[i][t][q];
+  for (int i = 0; i < NP; ++i) x += M.f[i][q] * M.o[i][t][q];
   return x;
 }
 

@@ -652,13 +652,13 @@ struct ListKeys {
 };
 
 // fp32 path: one workgroup per 16 queries of a cluster (f32_tile.h).
-template <int DP, int NW>
+template <int DP, int NW, int NP>
 __global__ __launch_bounds__(64 * NW, kF32Waves) void attn_f32_kernel(
     const float* __restrict__ qp, const float* __restrict__ kp, const float* __restrict__ vp,
     const int32_t* __restrict__ count_k, const int32_t* __restrict__ lists,
     const int32_t* __restrict__ lens, int nqc, int nkc, int cq, int ck, int d, int k, float scale,
     float* __restrict__ op, float* __restrict__ lse) {
-  __shared__ F32Merge<DP, NW> M;
+  __shared__ F32Merge<DP, NP> M;
   const int qt = (cq + 15) / 16;  // query tiles of a cluster
   const int a = blockIdx.x / qt, q0 = 16 * (blockIdx.x % qt), bh = blockIdx.y;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -670,13 +670,12 @@ __global__ __launch_bounds__(64 * NW, kF32Waves) void attn_f32_kernel(
   const ListKeys<DP> src{kp + (size_t)bh * nkc * ck * d, vp + (size_t)bh * nkc * d * ck,
                          lists + ((size_t)bh * nqc + a) * k, count_k + (size_t)bh * nkc,
                          nkc, ck, d, tpc, nt * tpc, lane, scale};
-  F32State<DP> st;
-  f32_online<DP, NW>(src, qf, w, st);
-  f32_merge<DP, NW>(M, st, w, lane);
+  f32_parts<DP, NW>(src, qf, M, w, lane);
+  f32_merge(M, w, lane);
   const int nq = min(16, cq - q0);
   for (int e = threadIdx.x; e < nq * d; e += 64 * NW) {
     const int q = e / d, t = e - q * d;
-    op[(qrow0 + q0) * d + e] = f32_merged<DP, NW>(M, q, t) * (1.f / M.sum[q]);
+    op[(qrow0 + q0) * d + e] = f32_merged(M, q, t) * (1.f / M.sum[q]);
   }
   if (threadIdx.x < nq) lse[qrow0 + q0 + threadIdx.x] = M.mx[threadIdx.x] + logf(M.sum[threadIdx.x]);
 }
@@ -836,9 +835,9 @@ hipError_t launch_attn(const Prob& P, const void* qp, const void* kp, const void
   const dim3 grid(P.nqc * ((P.cq + 15) / 16), P.BH);
   const int ntile = k * ((P.ck + 15) / 16);  // (k ck is at most the padded tokens)
 #define CA_ATTN_F32(DP)                                                                        \
-  f32_wavefronts<DP>(ntile, (int64_t)grid.x * grid.y, [&](auto nw) {                       \
-    constexpr int NW = decltype(nw)::value;                                                    \
-    hipLaunchKernelGGL((attn_f32_kernel<DP, NW>), grid, dim3(64 * NW), 0, st, (const float*)qp, \
+  f32_wavefronts<DP>(ntile, (int64_t)grid.x * grid.y, [&](auto nw, auto np) {              \
+    constexpr int NW = decltype(nw)::value, NP = decltype(np)::value;                          \
+    hipLaunchKernelGGL((attn_f32_kernel<DP, NW, NP>), grid, dim3(64 * NW), 0, st, (const float*)qp, \
                        (const float*)kp, (const float*)vp, count_k, lists, lens, P.nqc, P.nkc, \
                        P.cq, P.ck, P.d, k, scale, (float*)op, lse);                            \
   })

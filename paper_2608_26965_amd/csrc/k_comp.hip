@@ -478,7 +478,7 @@ struct CentKeys {
 // queries were a tenth of the call (4 heads of 131,072 tokens at d = 32, 4,096 key
 // clusters: 8.26 ms, now 7.27; 40 heads of 6,553 at d = 64, 820 key clusters: 1.79
 // and 1.71 ms; the former one-thread-a-query kernel 8.05 and 1.51).
-template <int DP, int NW>
+template <int DP, int NW, int NP>
 __global__ __launch_bounds__(64 * NW, kF32Waves) void comp_f32_kernel(
     const float* __restrict__ qp, const float* __restrict__ cent_k,
     const float* __restrict__ cent_v, const int32_t* __restrict__ count_k,
@@ -488,7 +488,7 @@ __global__ __launch_bounds__(64 * NW, kF32Waves) void comp_f32_kernel(
     const int32_t* __restrict__ perm_q, float* __restrict__ out, float* __restrict__ lse_out,
     Lay lo) {
   constexpr int NT = 64 * NW;
-  __shared__ F32Merge<DP, NW> M;
+  __shared__ F32Merge<DP, NP> M;
   __shared__ uint32_t selmask[kMaskWords];
   __shared__ float logs[kMaxC + 1];
   __shared__ float ws[16], wc[16];  // weights of the sparse part and of the merged centroid part
@@ -517,9 +517,8 @@ __global__ __launch_bounds__(64 * NW, kF32Waves) void comp_f32_kernel(
     __syncthreads();
     const CentKeys<DP> src{cent_k + (size_t)bh * nkc * d, cent_v + (size_t)bh * nkc * d,
                            count_k + (size_t)bh * nkc, selmask, logs, nkc, d, ntile, lane, scale};
-    F32State<DP> st;
-    f32_online<DP, NW>(src, qf, w, st);
-    f32_merge<DP, NW>(M, st, w, lane);
+    f32_parts<DP, NW>(src, qf, M, w, lane);
+    f32_merge(M, w, lane);
   }
   if (tid < nrow) {
     const int prow = a * cq + q0 + tid;
@@ -543,7 +542,7 @@ __global__ __launch_bounds__(64 * NW, kF32Waves) void comp_f32_kernel(
   for (int e = tid; e < nrow * d; e += NT) {
     const int q = e / d, t = e - q * d;
     float x = ws[q] * op[(qrow0 + q0) * d + e];
-    if (do_comp) x += wc[q] * f32_merged<DP, NW>(M, q, t);
+    if (do_comp) x += wc[q] * f32_merged(M, q, t);
     out[orow[q] + t] = x;
   }
 }
@@ -624,9 +623,9 @@ hipError_t launch_comp(const Prob& P, const void* qp, const float* cent_k, const
   const bool do_comp = enable && (k < P.nkc || lens);
   const int ntile = do_comp ? (P.nkc + 15) / 16 : 1;
 #define CA_COMP_F32(DP)                                                                        \
-  f32_wavefronts<DP>(ntile, (int64_t)grid.x * grid.y, [&](auto nw) {                       \
-    constexpr int NW = decltype(nw)::value;                                                    \
-    hipLaunchKernelGGL((comp_f32_kernel<DP, NW>), grid, dim3(64 * NW), 0, st,                  \
+  f32_wavefronts<DP>(ntile, (int64_t)grid.x * grid.y, [&](auto nw, auto np) {              \
+    constexpr int NW = decltype(nw)::value, NP = decltype(np)::value;                          \
+    hipLaunchKernelGGL((comp_f32_kernel<DP, NW, NP>), grid, dim3(64 * NW), 0, st,              \
                        (const float*)qp, cent_k, cent_v, count_k, lists, lens, P.nq, P.H,      \
                        P.nqc, P.nkc, P.cq, P.d, k, scale, enable, (const float*)op, lse,       \
                        perm_q, (float*)out, lse_out, P.lo);                                    \

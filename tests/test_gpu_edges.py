@@ -428,11 +428,12 @@ def test_f32_compensation_selected_infinite_value(d):
 
 
 # fp32: the number of wavefronts of a workgroup follows the tiles of 16 keys (1,
-# 2, 4 or 8 with 4 tiles each; 1, 2 or 4 with 2 at d = 128) where there are more
-# than 256 workgroups: the last tile count of each and the next one, against one
-# head alone (64 workgroups, all wavefronts): the same bits.
-@pytest.mark.parametrize("d,tiles", [(64, t) for t in (1, 4, 5, 8, 9, 16, 17)] +
-                         [(128, t) for t in (2, 3, 4, 5)] + [(32, 16)])
+# 2 or 4 with 4 tiles each, then 4 with two parts; 1, 2 or 4 with 2 at d = 128)
+# where there are more than 256 workgroups: the last tile count of each, the next
+# one, and parts of several steps, against one head alone (64 workgroups, all
+# wavefronts): the same bits.
+@pytest.mark.parametrize("d,tiles", [(64, t) for t in (1, 4, 5, 8, 9, 16, 17, 33, 70)] +
+                         [(128, t) for t in (2, 3, 4, 5)] + [(32, 16), (32, 17), (32, 70)])
 def test_f32_wavefronts_of_a_workgroup(d, tiles):
     import torch
     import paper_2608_26965_amd as ca
