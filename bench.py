@@ -44,8 +44,8 @@ PEAK_HBM_GBS = 8000.0
 # plain-copy calibration (FETCH_SIZE x 2, WRITE_SIZE x 1; the traffic summaries
 # under profiles/ give the commands), valid for the kernel sources with the
 # given fingerprint only (else reported as null).
-ATTN_TRAFFIC = {"fingerprint": "852d342d9fb7b262", "bytes": 8.4679e10}
-CLUSTER_TRAFFIC = {"fingerprint": "8484df8fb5b641fc", "bytes": 1.7796e10}
+ATTN_TRAFFIC = {"fingerprint": "ed22be8d13bcc2a7", "bytes": 8.4383e10}
+CLUSTER_TRAFFIC = {"fingerprint": "6d47f55d64496792", "bytes": 1.7790e10}
 
 
 def _fingerprint(files):
