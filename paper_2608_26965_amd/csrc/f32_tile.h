@@ -18,7 +18,7 @@
 // barrier until the merge. One thread per query with K and V through LDS took
 // 278 + 63 us (attention + compensation) for 2 heads of 1,000 queries x 12 of
 // 47 clusters of 64 keys at d = 64 and 118 + 36 us for 1,024 tokens x 4 of 16
-// clusters, one head; now 24 + 13 us and 13 + 11 us.
+// clusters, one head; now 23 + 13 us and 13 + 13 us.
 #pragma once
 
 #include <type_traits>
