@@ -637,7 +637,7 @@ __global__ __launch_bounds__(256) void topk_wave_kernel(const float* __restrict_
 // One more key in bin b for every lane with `in`; AGG: the lanes that share the
 // first one's bin add once (rows handed over by the filter below, whose scores
 // crowd into few bins: 16,384 rows of 8,192 equal scores, 619 us without,
-// about 355 with).
+// about 320 with).
 template <bool AGG>
 __device__ __forceinline__ void count(int* bins, int b, bool in, int lane) {
   if constexpr (AGG) {
@@ -655,7 +655,7 @@ __device__ __forceinline__ void count(int* bins, int b, bool in, int lane) {
 }
 
 template <int NWV>
-struct TopkBlock {
+struct alignas(16) TopkBlock {  // (bins are read 16 bytes at a time)
   int bins[kWaveBins];
   int hist[256];
   uint32_t ckey[NWV][kWaveCand];
@@ -964,7 +964,7 @@ __global__ __launch_bounds__(64 * NWV, 4) void topk_block_kernel(const float* __
 // two comparisons. 16,384 rows of 8,192, k = 64: 286 -> 114 us (both launches,
 // 4.7 TB/s); k = 819: 290 -> 167; rows of 5,000, k = 312: 404 -> 138. Scores
 // of 17 values 357 -> 146, a random rest masked by -inf 799 -> 117,
-// under one outlier 849 -> 146, all equal 619 -> 472 (all k = 64 of 8,192).
+// under one outlier 849 -> 146, all equal 619 -> 434 (all k = 64 of 8,192).
 constexpr int kFiltCand = 2048;  // listed scores
 
 template <int VPL, int NG>
@@ -972,7 +972,7 @@ __global__ __launch_bounds__(256, 4) void topk_filter_kernel(const float* __rest
                                                              int k, int32_t* __restrict__ lists) {
   constexpr int G = VPL / 4, WORDS = 256 * VPL / 32;
   static_assert(NG <= 8 && G % (NG > 4 ? 2 : 1) == 0, "groups");
-  struct Filter {
+  struct alignas(16) Filter {
     int bins[2][kWaveBins];
     float val[kFiltCand];
     uint16_t at[kFiltCand];
